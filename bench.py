@@ -54,7 +54,7 @@ HEADLINE_KERNEL = "sim_regs_kernel<8, 2>"
 VALU_PEAK_GINST = 256 * 4 * 2.4 / 4
 # what the simulation kernel is built from: its sources and the build flags
 SIM_SOURCES = [os.path.join(ROOT, "paper_2609_09643_amd", "csrc", f)
-               for f in ("sim.hip", "unison_device.h")] + \
+               for f in ("sim.hip", "lane.hip", "sim_device.h", "unison_device.h")] + \
               [os.path.join(ROOT, "paper_2609_09643_amd", "build.py")]
 
 

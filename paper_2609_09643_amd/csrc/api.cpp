@@ -607,6 +607,7 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
                      (unsigned long long)sim_variant_max_slots(v), (unsigned long long)max_res);
   if (v < 0) {
     v = sim_auto_variant(ctx->max_sess_batch, max_res);
+    if (sim_variant_lanes(v) && a.n_sims <= kLaneSims) v = kLaneKernel;
     if (sim_variant_capacity(v) < ctx->max_sess_batch)
       return ctx->fail(UNISON_E_CAPACITY, "%u sessions exceed every kernel variant (largest %u)",
                        ctx->max_sess_batch, sim_variant_capacity(v));

@@ -1,0 +1,1097 @@
+// lane.hip -- one wavefront per simulation with the residents sorted across
+// its lanes (gfx950).
+//
+// What bounds a single simulation is the chain of dependent instructions of
+// one event after the other, at about 8 cycles each for a lone wavefront.  So
+// everything about an event that does not depend on the pool leaves that
+// chain: a window of 64 events is prepared with one event per lane (the gap
+// EMAs of eq. (ema) and eq. (ema-int) along each session's events, the keys,
+// the KV sizes, the TIDE budgets of eq. (budget)), from table entries gathered
+// one window ahead, and what an event only reports (hits, tokens, bytes, its
+// scan victim) is noted in its lane and summed 64 events at a time.
+//
+// The chain that is left works on residents that are kept in victim order:
+// position i of the order sits in lane i % 64 of register i / 64, as (key,
+// session, slot, tier).  The scan victim of an event is position 0, TIDE's
+// candidates are the last HBM and the first SRAM position, and one comparison
+// per register finds where a key belongs; entries move over by one lane with
+// a whole-wavefront DPP shift.  A session being served is no candidate
+// (Alg. 1), so it only holds its slot (id, KV bytes, flags).
+//
+// Every branch of the chain is uniform and every loop in it has one exit (a
+// divergent branch, or a loop left from two places, makes the compiler
+// linearise the control flow around it, with copies of all live state at every
+// join); decision records are queued in LDS and hashed 64 at a time outside it.
+//
+// Measured (67,192 events, 1,415 sessions, 64 slots): 0.48 us per event under
+// SPEAR+TIDE and 0.33 under LRU, about 1,080 and 735 cycles in the chain and 60
+// in the window's preparation, against 1.28 for residents in unsorted register
+// slots with three wavefront reductions per event and the table in LDS.
+// 128 VGPRs keep four wavefronts on a SIMD: with 200 (sums and window
+// constants in registers) 4,096 simulations of 16 sessions took 225 us, now 167.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "sim_device.h"
+
+#pragma clang fp contract(off)
+
+// Writes one lane of a register (v_writelane_b32): clang has the instruction as
+// an LLVM intrinsic only.
+extern "C" __device__ __attribute__((const)) int unison_writelane(int v, int lane, int old) __asm(
+    "llvm.amdgcn.writelane.i32");
+
+namespace unison {
+
+namespace {
+
+__device__ __forceinline__ uint32_t rl(uint32_t v, uint32_t l) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+}
+__device__ __forceinline__ uint64_t rl(uint64_t v, uint32_t l) {
+  return ((uint64_t)rl((uint32_t)(v >> 32), l) << 32) | rl((uint32_t)v, l);
+}
+__device__ __forceinline__ uint32_t wl(uint32_t old, uint32_t l, uint32_t v) {
+  return (uint32_t)unison_writelane((int)v, (int)l, (int)old);
+}
+__device__ __forceinline__ uint64_t wl(uint64_t old, uint32_t l, uint64_t v) {
+  return ((uint64_t)wl((uint32_t)(old >> 32), l, (uint32_t)(v >> 32)) << 32) |
+         wl((uint32_t)old, l, (uint32_t)v);
+}
+// Lane i takes lane i + 1's value (lane 63: 0), or lane i - 1's (lane 0: 0).
+__device__ __forceinline__ uint32_t from_above(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t from_below(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint64_t from_above(uint64_t v) {
+  return ((uint64_t)from_above((uint32_t)(v >> 32)) << 32) | from_above((uint32_t)v);
+}
+__device__ __forceinline__ uint64_t from_below(uint64_t v) {
+  return ((uint64_t)from_below((uint32_t)(v >> 32)) << 32) | from_below((uint32_t)v);
+}
+__device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ uint32_t pop64(uint64_t m) { return (uint32_t)__builtin_popcountll(m); }
+
+// Orders the wavefront's own memory accesses before and after this point.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// 1 when a <= b, else 0, for uniform values in scalar registers (gfx950 has no
+// scalar 64-bit order comparison; the compiler would go through vector
+// registers).
+__device__ __forceinline__ uint32_t le64(uint64_t a, uint64_t b) {
+  uint32_t r;
+  asm("s_sub_u32 %0, %3, %1\n\ts_subb_u32 %0, %4, %2\n\ts_cselect_b32 %0, 0, 1"
+      : "=&s"(r)
+      : "s"((uint32_t)a), "s"((uint32_t)(a >> 32)), "s"((uint32_t)b), "s"((uint32_t)(b >> 32))
+      : "scc");
+  return r;
+}
+// The lowest set bit's index, kNone for none.
+__device__ __forceinline__ uint32_t first_set(uint64_t m) {
+  uint32_t r;
+  asm("s_ff1_i32_b64 %0, %1" : "=s"(r) : "s"(m));
+  return r;
+}
+// The highest set bit's index, kNone for none.
+__device__ __forceinline__ uint32_t last_set(uint64_t m) {
+  uint32_t r;
+  asm("s_flbit_i32_b64 %0, %1" : "=s"(r) : "s"(m));
+  return r == kNone ? kNone : 63u - r;
+}
+
+// n / b for a divisor known in advance: inv = floor((2^64 - 1) / b), one high
+// product and at most two corrections (the estimate falls short by at most 2).
+__device__ __forceinline__ uint64_t div_by(uint64_t n, uint64_t b, uint64_t inv) {
+  uint64_t q = __umul64hi(n, inv);
+  uint64_t r = n - q * b;
+  if (r >= b) { ++q; r -= b; }
+  if (r >= b) ++q;
+  return q;
+}
+
+// What only a window's preparation uses of the launch's constants, one word per
+// lane of a register: held in scalar registers, they would make the chain spill
+// at every event; a window reads them back with one instruction a word.
+struct Consts {
+  uint32_t v;
+  __device__ __forceinline__ void put(uint32_t i, uint32_t x) { v = wl(v, i, x); }
+  __device__ __forceinline__ void put(uint32_t i, uint64_t x) {
+    put(i, (uint32_t)x);
+    put(i + 1, (uint32_t)(x >> 32));
+  }
+  template <class T>
+  __device__ __forceinline__ void put(uint32_t i, const T* p) { put(i, (uint64_t)p); }
+  __device__ __forceinline__ uint32_t u32(uint32_t i) const { return rl(v, i); }
+  __device__ __forceinline__ uint64_t u64(uint32_t i) const {
+    return ((uint64_t)rl(v, i + 1) << 32) | rl(v, i);
+  }
+  template <class T>
+  __device__ __forceinline__ T* ptr(uint32_t i) const {
+    typedef __attribute__((address_space(1))) T G;
+    return (T*)(G*)u64(i);
+  }
+  // The words may not be kept in scalar registers from one window to the next.
+  __device__ __forceinline__ void fresh() { asm volatile("" : "+v"(v)); }
+};
+enum : uint32_t {
+  kCMg = 0, kCGq = 2, kCLast = 4, kCNext = 6, kCLen = 8, kCKvb = 10, kCEvT = 12, kCEvNext = 14,
+  kCEvSid = 16, kCEvInfo = 18, kCEvLen = 20, kCEvTool = 22, kCEta = 24, kCLog = 26, kCDma = 28,
+  kCDmaInv = 30, kCTau = 32, kCTtl = 34, kCPz = 36, kCEnd = 38, kCLambda = 40, kCRecip, kCP, kCBg,
+  kCLogCap, kCIdBits, kCHasTool
+};
+
+// Queued records: the chain stops for a flush once kQueueFlush are waiting,
+// and one event adds at most its scan victim, a record per resident that
+// expires or is evicted, its own placement and two per resident that TIDE
+// promotes or swaps (a session TIDE moved up stays up for the pass).
+constexpr uint32_t kQueueFlush = 64;
+constexpr uint32_t queue_entries(uint32_t residents) { return kQueueFlush + 2u + 4u * residents; }
+
+// hazard_add_counts over one wavefront without a divergent branch: lanes from
+// 51 on rewrite the tables' unused 52nd entry.
+__device__ __forceinline__ void add_completion(const KeyCtx& K, uint32_t Tn, uint32_t lane) {
+  const uint32_t t = lane < kLut ? lane : kLut;
+  const uint32_t d = t < kLut ? K.hd[t] + (t + 1u == Tn ? 1u : 0u) : 0u;
+  const uint32_t n = t < kLut ? K.hn[t] + (t < Tn ? 1u : 0u) : 0u;
+  K.hd[t] = d;
+  K.hn[t] = n;
+  K.hf[t] = hazard_f32(d, n);
+  K.hq[t] = hazard_q(d, n, K.lambda);
+  wave_sync();
+}
+
+// One window's events as loaded, an event per lane.
+struct EvRegs {
+  uint64_t t, next;
+  uint32_t sid, info, len, tool;
+};
+// The table entries of a window's sessions.
+struct TabRegs {
+  uint64_t mg, gq, last;
+  uint32_t len, kvb;
+};
+
+// An event's word in the chain: its session (below 2^20) and flags.
+constexpr uint32_t kWNewBit = 25;
+constexpr uint32_t kWArrive = 1u << 24, kWNew = 1u << kWNewBit, kWOnset = 1u << 26, kWBig = 1u << 27;
+static_assert(UNISON_MAX_SESSIONS <= (1u << 20), "session ids take 20 bits");
+
+template <int SPL, uint32_t POL, uint32_t SMODE>
+struct LaneSim {
+  using PT = Pol<POL, SMODE>;
+  // fp32 scores are 32-bit keys; integer scores and times take 64 bits
+  using KT = typename std::conditional<PT::spear && !PT::fixed, uint32_t, uint64_t>::type;
+  static constexpr uint32_t kSram = 1u, kPref = 2u;  // slot flags
+  static_assert(kTierSram == 1 && kTierHbm == 2, "a tier's low bit is the SRAM flag");
+  // an order entry: session << 11 | slot << 2 | completed << 1 | in SRAM
+  static constexpr uint32_t kSidShift = 11, kDoneB = 2u;
+  static constexpr bool kGapEma = PT::spear || PT::belady;  // others read it for TIDE only
+
+  uint32_t lane;
+  // Residents in victim order (larger key first, ties to the smaller id): the
+  // key, and the entry complemented, so that an empty position is 0 in both
+  // and sorts last.
+  KT skey[SPL];
+  uint32_t snot[SPL];
+  // slots: every resident, also while it is served
+  uint32_t ssid[SPL], sfl[SPL];
+  uint64_t ssz[SPL];
+  // online tables: what a resident's key is recomputed from
+  uint32_t sturn[SPL];
+  uint64_t sema[SPL];
+
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      skey[j] = 0;
+      snot[j] = 0;
+      ssid[j] = kNone;
+      sfl[j] = 0;
+      ssz[j] = 0;
+      sturn[j] = 0;
+      sema[j] = 0;
+    }
+  }
+  template <class T>
+  __device__ __forceinline__ static T get(const T (&a)[SPL], uint32_t i) {
+    T v = rl(a[0], i & 63u);
+#pragma unroll
+    for (int j = 1; j < SPL; ++j) {
+      const T o = rl(a[j], i & 63u);
+      v = (i >> 6) == (uint32_t)j ? o : v;
+    }
+    return v;
+  }
+  template <class T>
+  __device__ __forceinline__ static void set(T (&a)[SPL], uint32_t i, T v) {
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      const T n = wl(a[j], i & 63u, v);
+      a[j] = SPL == 1 || (i >> 6) == (uint32_t)j ? n : a[j];
+    }
+  }
+  // Register j's lane l as an index, or `other` for no lane.
+  __device__ __forceinline__ static uint32_t at(uint32_t l, int j, uint32_t other) {
+    if constexpr (SPL == 1) return l;
+    else return l == kNone ? other : (uint32_t)j * 64u + l;
+  }
+  // The slot of resident sid, or kNone.
+  __device__ __forceinline__ uint32_t slot_of(uint32_t sid) const {
+    uint32_t s = kNone;
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j) s = at(first_set(ballot(ssid[j] == sid)), j, s);
+    return s;
+  }
+  // The position of a resident that is in the order.
+  __device__ __forceinline__ uint32_t pos_of(uint32_t sid) const {
+    const uint32_t top = (uint32_t)((int)~(sid << kSidShift) >> kSidShift);
+    uint32_t p = kNone;
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j)
+      p = at(first_set(ballot((uint32_t)((int)snot[j] >> kSidShift) == top)), j, p);
+    return p;
+  }
+  // The entry at position p (kNone: empty).
+  __device__ __forceinline__ uint32_t entry(uint32_t p) const { return ~get(snot, p); }
+  __device__ __forceinline__ uint32_t front() const { return ~rl(snot[0], 0u); }
+  __device__ __forceinline__ static uint32_t slot_in(uint32_t x) { return (x >> 2) & 511u; }
+  template <bool FRONT, class T>
+  __device__ __forceinline__ void close_gap(T (&a)[SPL], uint32_t pos) const {
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      T t = from_above(a[j]);
+      if constexpr (SPL > 1) {
+        if (j + 1 < SPL) t = wl(t, 63u, rl(a[j + 1 < SPL ? j + 1 : j], 0u));
+      }
+      a[j] = !FRONT && (uint32_t)j * 64u + lane < pos ? a[j] : t;
+    }
+  }
+  __device__ __forceinline__ void remove_at(uint32_t pos) {
+    close_gap<false>(skey, pos);
+    close_gap<false>(snot, pos);
+  }
+  __device__ __forceinline__ void pop_front() {
+    close_gap<true>(skey, 0u);
+    close_gap<true>(snot, 0u);
+  }
+  template <class T>
+  __device__ __forceinline__ static void open_gap(T (&a)[SPL], const bool (&before)[SPL]) {
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j) {
+      T t = from_below(a[j]);
+      if constexpr (SPL > 1) {
+        if (j > 0) t = wl(t, 0u, rl(a[j > 0 ? j - 1 : 0], 63u));
+      }
+      a[j] = before[j] ? a[j] : t;
+    }
+  }
+  __device__ __forceinline__ void insert(KT key, uint32_t entry_word) {
+    const uint32_t n = ~entry_word;
+    bool before[SPL];
+    uint32_t pos = 0;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      before[j] = (skey[j] > key) | ((skey[j] == key) & (snot[j] > n));
+      pos += pop64(ballot(before[j]));
+    }
+    open_gap(skey, before);
+    open_gap(snot, before);
+    set(skey, pos, key);
+    set(snot, pos, n);
+  }
+  // TIDE's candidates: the smallest key in HBM, ties to the smaller id
+  // (eq. (promote)), and the largest key in SRAM (eq. (demote)).  kNone: none.
+  __device__ __forceinline__ uint64_t hbm(int j) const { return ballot((snot[j] & 1u) != 0u); }
+  __device__ __forceinline__ uint32_t last_hbm() const {
+    uint64_t m[SPL];
+    uint32_t p = kNone;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      m[j] = hbm(j);
+      p = at(last_set(m[j]), j, p);
+    }
+    if (p == kNone) return kNone;
+    const KT k = get(skey, p);
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j) p = at(first_set(ballot(skey[j] == k) & m[j]), j, p);
+    return p;
+  }
+  __device__ __forceinline__ uint32_t first_sram() const {
+    uint32_t p = kNone;
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j)
+      p = at(first_set(ballot(snot[j] != 0u) & ~hbm(j)), j, p);
+    return p;
+  }
+  // The slot a new resident takes (residents never exceed 64 SPL).
+  __device__ __forceinline__ uint32_t free_slot() const {
+    uint32_t s = 0;
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j) s = at(first_set(ballot(ssid[j] == kNone)), j, s);
+    return s;
+  }
+
+  // The session of an order entry; kNone for the empty one.
+  __device__ __forceinline__ static uint32_t sid_of(uint32_t x) {
+    return (uint32_t)((int)x >> kSidShift);
+  }
+  // A key in the form the order compares.
+  __device__ __forceinline__ static KT key_from(const KeyCtx& K, bool done, uint32_t turn, float g,
+                                                uint64_t gq, uint64_t t, uint64_t next) {
+    const uint32_t m = make_meta(done ? kDoneP : kGap, kTierNone, turn);
+    return (KT)key_of<POL, SMODE>(K, m, hazard_of<POL, SMODE>(K, m), g, gq, t, next);
+  }
+  // After a change of the hazard table: every ordered resident's key, and the order.
+  __device__ __forceinline__ void rescore(const KeyCtx& K) {
+    if constexpr (PT::spear) {
+      KT fresh[SPL];
+#pragma unroll
+      for (int j = 0; j < SPL; ++j)
+        fresh[j] = key_from(K, false, sturn[j], __uint_as_float((uint32_t)sema[j]), sema[j], 0ull, 0ull);
+      // the keys from slot order to the present order, then each entry's rank
+      KT nk[SPL];
+      uint32_t nn[SPL], rank[SPL], n = 0;
+#pragma unroll
+      for (int j = 0; j < SPL; ++j) {
+        const uint32_t x = ~snot[j], s = slot_in(x);
+        KT v = 0;
+#pragma unroll
+        for (int i = 0; i < SPL; ++i) {
+          const KT o = (KT)__shfl((unsigned long long)fresh[i], (int)(s & 63u));
+          v = (s >> 6) == (uint32_t)i ? o : v;
+        }
+        const bool in = snot[j] != 0u;
+        n += pop64(ballot(in));
+        nk[j] = !in ? (KT)0 : (x & kDoneB) ? (KT)PT::inf_key : v;
+        nn[j] = snot[j];
+        rank[j] = 0;
+      }
+      for (uint32_t i = 0; i < n; ++i) {
+        const KT k = get(nk, i);
+        const uint32_t d = get(nn, i);
+#pragma unroll
+        for (int j = 0; j < SPL; ++j)
+          rank[j] += (k > nk[j]) | ((k == nk[j]) & (d > nn[j])) ? 1u : 0u;
+      }
+      for (uint32_t i = 0; i < n; ++i) {
+        const uint32_t r = get(rank, i);
+        set(skey, r, get(nk, i));
+        set(snot, r, get(nn, i));
+      }
+    }
+  }
+};
+
+// The wavefront's 64-bit sums, 64 words each in LDS.
+enum : uint32_t { kSTok, kSComp, kSExtra, kSMiss, kSHitS, kSPrevS, kSHitH, kSPrevH, kSEvals, kSResEvals,
+                  kSDigest, kSVictim, kSums };
+
+// The pool's scalars, and what a launch adds to a simulation's counters.
+struct Pool {
+  uint64_t used_s, used_h, dma_free, log_len;
+  uint32_t n_res, n_table;
+};
+struct Totals {
+  uint64_t hit_s, hit_h, miss_tok, prev_s, prev_h, dma_bytes, tok, comp, extra, evals, res_evals,
+      digest, victim_digest;
+  uint32_t hi, req, n_hs, n_hh, n_pf, n_byp, n_evict, n_exp, n_pro, n_swap, passes;
+};
+
+// Events [e_io, end) of one simulation.
+template <int SPL, uint32_t POL, uint32_t SMODE>
+__device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_params& P,
+                                            const KeyCtx& K, const TraceView& tr, size_t tb,
+                                            const uint32_t* kvb_of, uint2* queue, uint64_t* sums,
+                                            LaneSim<SPL, POL, SMODE>& T,
+                                            Pool& pool, Totals& W, const LogSink& L, uint64_t& e_io,
+                                            uint64_t end) {
+  using PT = Pol<POL, SMODE>;
+  using LS = LaneSim<SPL, POL, SMODE>;
+  using KT = typename LS::KT;
+  constexpr uint64_t kGolden = 0x9e3779b97f4a7c15ull;
+  const uint32_t lane = T.lane;
+  const uint64_t below = (1ull << lane) - 1ull;
+  Consts c{0u};
+  c.put(kCMg, a.t_mg + tb);
+  c.put(kCGq, a.t_gq + tb);
+  c.put(kCLast, a.t_last + tb);
+  c.put(kCNext, a.t_next + tb);
+  c.put(kCLen, a.t_len + tb);
+  c.put(kCKvb, kvb_of);
+  c.put(kCEvT, tr.t);
+  c.put(kCEvNext, tr.next);
+  c.put(kCEvSid, tr.sid);
+  c.put(kCEvInfo, tr.info);
+  c.put(kCEvLen, tr.len);
+  c.put(kCEvTool, tr.tool);
+  c.put(kCEta, K.eta);
+  c.put(kCLog, L.rec);
+  c.put(kCDma, uni64(P.dma_B_per_us));
+  // the DMA busy time divides by the bandwidth: one reciprocal per launch
+  c.put(kCDmaInv, uni64(~0ull / P.dma_B_per_us));
+  c.put(kCTau, uni64(P.tau_ns));
+  c.put(kCTtl, uni64(P.ttl_ns));
+  c.put(kCPz, uni64(K.p_z));
+  c.put(kCEnd, end);
+  c.put(kCLambda, uni32(K.lambda));
+  c.put(kCRecip, uni32(K.recip_bits));
+  c.put(kCP, uni32(__float_as_uint(K.P)));
+  c.put(kCBg, uni32(P.b_g));
+  c.put(kCLogCap, L.cap);
+  c.put(kCIdBits, tr.n_sess > 1u ? 32u - (uint32_t)__builtin_clz(tr.n_sess - 1u) : 0u);
+  c.put(kCHasTool, PT::eta && tr.tool != nullptr ? 1u : 0u);
+  const auto key_ctx = [&]() {
+    KeyCtx v = K;
+    v.lambda = c.u32(kCLambda);
+    v.p_z = c.u64(kCPz);
+    v.recip_bits = c.u32(kCRecip);
+    v.P = __uint_as_float(c.u32(kCP));
+    return v;
+  };
+  const bool tide = uni32(P.tide) != 0;
+  const uint32_t online = K.online_cap;
+  const uint32_t log_on = L.on ? 1u : 0u, log_victims = L.victims ? 1u : 0u;
+  const bool ema = LS::kGapEma || tide;
+  const uint64_t cap_s = uni64(P.cap_sram_B), cap_h = uni64(P.cap_hbm_B);
+  const uint64_t slots = uni64(P.n_slots);
+  const uint32_t n_slots = slots < 64u * SPL ? (uint32_t)slots : 64u * SPL;  // residents fit the slots
+
+  uint64_t used_s = pool.used_s, used_h = pool.used_h, dma_free = pool.dma_free;
+  uint32_t n_res = uni32(pool.n_res), n_table = uni32(pool.n_table);
+
+  uint64_t log_len = in_vgpr(pool.log_len);
+  uint64_t dma_bytes = 0;
+  uint32_t passes = 0, hi = 0;
+  // per lane, summed over the wavefront at the end; the 64-bit sums in LDS
+#pragma unroll
+  for (uint32_t i = 0; i < kSums; ++i) sums[i * 64u + lane] = 0ull;
+  const auto add = [&](uint32_t i, uint64_t v) { sums[i * 64u + lane] += v; };
+  uint32_t n_req = 0, n_hs = 0, n_hh = 0, n_pf = 0, n_evict = 0, n_exp = 0, n_byp = 0, n_pro = 0,
+           n_swap = 0;
+  uint32_t q_n = 0;  // queued decision records
+
+  const auto load_events = [&](uint64_t b) {
+    const uint64_t last = c.u64(kCEnd) - 1;
+    const uint64_t i = b + lane < last ? b + lane : last;
+    EvRegs v;
+    v.t = c.ptr<uint64_t>(kCEvT)[i];
+    v.sid = c.ptr<uint32_t>(kCEvSid)[i];
+    v.info = c.ptr<uint32_t>(kCEvInfo)[i];
+    v.len = c.ptr<uint32_t>(kCEvLen)[i];
+    v.next = PT::belady ? c.ptr<uint64_t>(kCEvNext)[i] : ~0ull;
+    v.tool = PT::eta && c.u32(kCHasTool) ? c.ptr<uint32_t>(kCEvTool)[i] : 0u;
+    return v;
+  };
+  const auto gather = [&](uint32_t sid) {
+    TabRegs v;
+    v.mg = c.ptr<uint64_t>(kCMg)[sid];
+    v.gq = PT::fixed ? c.ptr<uint64_t>(kCGq)[sid] : 0ull;
+    v.last = c.ptr<uint64_t>(kCLast)[sid];
+    v.len = c.ptr<uint32_t>(kCLen)[sid];
+    v.kvb = c.ptr<uint32_t>(kCKvb)[sid];
+    return v;
+  };
+
+  uint64_t base = e_io;
+  EvRegs cur = load_events(base);
+  TabRegs tab = gather(cur.sid);
+  EvRegs nxt = load_events(base + 64);
+
+  while (base < end) {
+    c.fresh();
+    const uint32_t cnt = end - base < 64 ? (uint32_t)(end - base) : 64u;
+    const uint64_t all = cnt < 64u ? (1ull << cnt) - 1ull : ~0ull;
+    const bool valid = lane < cnt;
+    const uint64_t now = cur.t;
+    const uint32_t sid = cur.sid, kind = cur.info >> 24, turn_ev = cur.info & 0xFFFFFFu;
+    const uint32_t ln = cur.len;
+
+    // ---- the window, an event per lane ----
+    // the lanes of each lane's own session: those that agree in every id bit
+    const uint32_t n_bits = c.u32(kCIdBits);
+    uint32_t same_lo = (uint32_t)all, same_hi = (uint32_t)(all >> 32);
+    for (uint32_t b = 0; b < n_bits; ++b) {
+      const uint32_t mine = 0u - ((sid >> b) & 1u);
+      const uint64_t set = ballot(mine != 0u);
+      same_lo &= ~((uint32_t)set ^ mine);
+      same_hi &= ~((uint32_t)(set >> 32) ^ mine);
+    }
+    const uint64_t same = ((uint64_t)same_hi << 32) | same_lo;
+    const uint64_t earlier = same & below;
+    const bool newest = valid && (same & ~below & ~(1ull << lane)) == 0ull;
+    const int prev = valid && earlier ? 63 - __builtin_clzll(earlier) : -1;
+    // the register file's entry before the event, then after it
+    float g_in = __uint_as_float((uint32_t)(tab.mg >> 32));
+    uint64_t gq_in = tab.gq, last_in = tab.last;
+    uint32_t len_in = tab.len, turn_in = meta_turn((uint32_t)tab.mg);
+    const bool arrive = kind == kArrive;
+    const bool fresh = arrive && turn_ev == 0u;
+    float g = 0.0f;
+    uint64_t gq = 0;
+    uint32_t len_out = 0, turn = 0;
+    uint64_t ready = ballot(prev < 0);
+    for (;;) {
+      const uint64_t gap = now - last_in;  // eq. (gap)
+      const bool upd = arrive && !fresh;
+      if (ema) g = upd ? ema_f32(g_in, gap) : g_in;
+      else g = g_in;
+      if constexpr (PT::fixed) gq = upd ? ema_int(gq_in, gap, c.u32(kCBg), c.u64(kCTau)) : gq_in;
+      if (fresh) {
+        g = 0.0f;
+        gq = 0;
+      }
+      len_out = arrive ? ln : len_in;
+      turn = arrive ? turn_ev : turn_in;
+      if (ready == ~0ull) break;
+      const int p = prev < 0 ? (int)lane : prev;
+      const float pg = __shfl(g, p);
+      const uint64_t pq = PT::fixed ? __shfl((unsigned long long)gq, p) : 0ull;
+      const uint64_t pt = __shfl((unsigned long long)now, p);
+      const uint32_t pl = __shfl(len_out, p), pn = __shfl(turn, p);
+      const bool take = prev >= 0 && ((ready >> p) & 1ull);
+      g_in = take ? pg : g_in;
+      gq_in = take ? pq : gq_in;
+      last_in = take ? pt : last_in;
+      len_in = take ? pl : len_in;
+      turn_in = take ? pn : turn_in;
+      ready |= ballot(take);
+    }
+    const uint32_t len_prev = fresh ? 0u : len_in;
+    uint64_t next = kind == kGapStart ? cur.next : ~0ull;
+    if constexpr (PT::eta) {
+      // the predicted return: gap onset + the expected wait of the gap's tool class
+      if (kind == kGapStart) next = sat_add(now, c.ptr<uint64_t>(kCEta)[cur.tool < kEtaClasses ? cur.tool : 0u]);
+    }
+    KT key = LS::key_from(key_ctx(), kind == kDone, turn, g, gq, now, next);
+    const uint64_t size = (uint64_t)ln * tab.kvb;
+    uint64_t budget = 0;
+    if (tide) {
+      // eq. (budget) / eq. (budgetq): Delta is the session's gap EMA in us
+      uint64_t delta_us;
+      if constexpr (PT::fixed) {
+        const uint64_t tau = c.u64(kCTau);
+        if (gq < (1ull << 32) && tau < (1ull << 32)) {
+          delta_us = (gq * tau) / 1000u;
+        } else {
+          const unsigned __int128 d = ((unsigned __int128)gq * tau) / 1000u;
+          delta_us = d > (unsigned __int128)~0ull ? ~0ull : (uint64_t)d;
+        }
+      } else {
+        delta_us = (uint64_t)g;
+      }
+      budget = sat_mul(delta_us, c.u64(kCDma));
+    }
+    // each session's newest entry back to the table (tiers follow at the end)
+    if (newest) {
+      const uint32_t ph = arrive ? kServing : kind == kGapStart ? kGap : kDoneP;
+      c.ptr<uint64_t>(kCMg)[sid] = (uint64_t)make_meta(ph, kTierNone, turn) | ((uint64_t)__float_as_uint(g) << 32);
+      if constexpr (PT::fixed) c.ptr<uint64_t>(kCGq)[sid] = gq;
+      c.ptr<uint32_t>(kCLen)[sid] = len_out;
+      c.ptr<uint64_t>(kCLast)[sid] = now;
+      if constexpr (PT::nextkey) {
+        if (!arrive) c.ptr<uint64_t>(kCNext)[sid] = next;
+      }
+    }
+    wave_sync();
+    const uint32_t kvb = tab.kvb;
+    // the next window's entries and the events after it, in flight meanwhile
+    cur = nxt;
+    tab = gather(cur.sid);
+    nxt = load_events(base + 128);
+
+    // the event's word: its session, and what the chain asks about it
+    const bool onset_l = kind == kGapStart;
+    const uint32_t word = sid | (arrive ? kWArrive : 0u) | (fresh ? kWNew : 0u) |
+                          (onset_l ? kWOnset : 0u) | (size > cap_s && size > cap_h ? kWBig : 0u);
+    uint64_t m_free = tide ? ballot(valid && onset_l && now >= dma_free) : 0ull;
+    uint64_t thr = 0;
+    if constexpr (PT::timeout) thr = ~idle_threshold(now, c.u64(kCTtl));  // a timer fired: key > thr
+    hi = valid && fresh && sid + 1u > hi ? sid + 1u : hi;
+    uint32_t o_code = 0, o_vic = 0;  // the event's outcome and scan victim, noted in its lane
+    uint32_t w_evals = 0, w_res = 0;
+
+    // Decision records queue in LDS as (event in window | op << 6 | b << 12, a)
+    // and are hashed, counted and logged 64 at a time outside the chain.
+    const auto emit = [&](uint32_t k, uint32_t op, uint32_t x, uint32_t y) {
+      queue[q_n] = make_uint2(k | (op << 6) | (y << 12), x);
+      ++q_n;
+    };
+    const auto flush = [&]() {
+      wave_sync();
+      for (uint32_t q0 = 0; q0 < q_n; q0 += 64u) {
+        const bool in = q0 + lane < q_n;
+        const uint2 r = queue[in ? q0 + lane : 0u];
+        const uint32_t op = in ? (r.x >> 6) & 7u : 0u;
+        const uint32_t ev = (uint32_t)base + (r.x & 63u);
+        const uint32_t y = op == kOpPlace || op == kOpSwap ? r.x >> 12 : kNone;
+        // placements and bypasses are hashed from the window, an event per lane
+        if (in && op != kOpVictim && op != kOpPlace && op != kOpBypass) add(kSDigest, rec_hash(ev, op, r.y, y));
+        n_evict += op == kOpEvict ? 1u : 0u;
+        n_exp += op == kOpExpire ? 1u : 0u;
+        n_pro += op == kOpPromote ? 1u : 0u;
+        n_swap += op == kOpSwap ? 1u : 0u;
+        if (L.on) {
+          if (in && log_len + lane < c.u32(kCLogCap))
+            c.ptr<unison_record>(kCLog)[log_len + lane] = unison_record{ev, op, r.y, y};
+          log_len += q_n - q0 < 64u ? q_n - q0 : 64u;
+        }
+      }
+      wave_sync();
+      q_n = 0;
+    };
+    // A resident leaves the pool: its bytes, its slot.
+    const auto leave = [&](uint32_t x) {
+      const uint32_t slot = LS::slot_in(x);
+      const uint64_t sz = LS::get(T.ssz, slot);
+      used_s -= x & LS::kSram ? sz : 0ull;
+      used_h -= x & LS::kSram ? 0ull : sz;
+      --n_res;
+      n_table -= (x >> 1) & 1u;  // a completed session leaves the table
+      LS::set(T.ssid, slot, kNone);
+    };
+
+    // ---- the chain, one event after the other (every branch is uniform) ----
+    for (uint32_t k = 0; k < cnt;) {
+      uint32_t stop = cnt;
+      for (; k < stop; ++k) {
+        const uint32_t wd = rl(word, k);
+        const uint32_t s = wd & (kWArrive - 1u);
+        if constexpr (PT::timeout) {
+          // TTL timers that fired since the previous event, smallest id first
+          const uint64_t th = rl(thr, k);
+          while (LS::get(T.skey, 0) > th) {
+            uint32_t c = kNone;
+#pragma unroll
+            for (int j = 0; j < SPL; ++j) c = T.skey[j] > th && ~T.snot[j] < c ? ~T.snot[j] : c;
+            c = uni32(wave_ext32<false>(c));
+            emit(k, kOpExpire, c >> LS::kSidShift, 0u);
+            leave(c);
+            T.remove_at(T.pos_of(c >> LS::kSidShift));
+            stop = q_n >= kQueueFlush ? k + 1u : stop;
+          }
+        }
+        const uint32_t slot = T.slot_of(s);
+        if (wd & kWArrive) {
+          n_table += (wd >> kWNewBit) & 1u;
+          w_evals += n_table;
+          w_res += n_res;
+          uint32_t code = 0;
+          if (slot != kNone) {
+            const uint32_t fl = LS::get(T.sfl, slot);
+            const uint64_t sz = LS::get(T.ssz, slot);
+            used_s -= fl & LS::kSram ? sz : 0ull;
+            used_h -= fl & LS::kSram ? 0ull : sz;
+            code = fl & LS::kSram ? fl & 3u : 4u;
+            --n_res;
+            LS::set(T.ssid, slot, kNone);
+            T.remove_at(T.pos_of(s));
+          }
+          uint32_t x = T.front();
+          o_vic = wl(o_vic, k, LS::sid_of(x));
+          if (log_victims) emit(k, kOpVictim, LS::sid_of(x), 0u);
+          // Alg. 1 capacity branch: evict the argmax victim until the session fits
+          uint32_t place = 0;  // the tier, 0: bypassed
+          const uint64_t sz = rl(size, k);
+          const uint32_t want_h = code >> 2;
+          if (!(wd & kWBig)) {
+            for (;;) {
+              const uint32_t room = (n_res - n_slots) >> 31;  // n_res < n_slots
+              const uint32_t fit_s = room & le64(used_s + sz, cap_s);
+              const uint32_t fit_h = room & le64(used_h + sz, cap_h);
+              // SRAM first, for an HBM resident's request HBM first
+              place = fit_s + 2u * (fit_h & ((fit_s ^ 1u) | want_h));
+              place = place == 3u ? kTierHbm : place;
+              if ((place != 0u) | (x == kNone)) break;
+              emit(k, kOpEvict, x >> LS::kSidShift, 0u);
+              leave(x);
+              T.pop_front();
+              x = T.front();
+              stop = q_n >= kQueueFlush ? k + 1u : stop;
+            }
+          }
+          o_code = wl(o_code, k, code | (place << 4));
+          if (log_on) {
+            emit(k, place ? kOpPlace : kOpBypass, s, place);
+            stop = q_n >= kQueueFlush ? k + 1u : stop;
+          }
+          if (place) {
+            used_s += place & 1u ? sz : 0ull;
+            used_h += place & 1u ? 0ull : sz;
+            ++n_res;
+            const uint32_t f = T.free_slot();
+            LS::set(T.ssid, f, s);
+            LS::set(T.ssz, f, sz);
+            LS::set(T.sfl, f, place & 1u);
+          }
+        } else {
+          const bool onset = (wd & kWOnset) != 0u;
+          if (slot != kNone) {
+            const uint32_t fl = LS::get(T.sfl, slot);
+            if (online) {
+              LS::set(T.sturn, slot, rl(turn, k));
+              LS::set(T.sema, slot, PT::fixed ? rl(gq, k) : (uint64_t)rl(__float_as_uint(g), k));
+            }
+            T.insert(rl(key, k), (s << LS::kSidShift) | (slot << 2) | (onset ? 0u : LS::kDoneB) |
+                                     (fl & LS::kSram));
+          }
+          // an online hazard table counts the completed session before the scan
+          if (!onset && online && uni32(K.hn[0]) < K.online_cap) {
+            add_completion(K, rl(turn, k) + 1u, lane);
+            T.rescore(key_ctx());
+            key = LS::key_from(key_ctx(), kind == kDone, turn, g, gq, now, next);
+          }
+          w_evals += n_table;
+          w_res += n_res;
+          const uint32_t v0 = LS::sid_of(T.front());
+          o_vic = wl(o_vic, k, v0);
+          if (log_victims) {
+            emit(k, kOpVictim, v0, 0u);
+            stop = q_n >= kQueueFlush ? k + 1u : stop;
+          }
+          n_table -= !onset && slot == kNone ? 1u : 0u;
+          if ((m_free >> k) & 1ull) {
+            uint64_t left = rl(budget, k), moved = 0;
+            ++passes;
+            bool more = true;
+            while (more) {
+              more = false;
+              const uint32_t p = T.last_hbm();
+              if (p != kNone) {
+                const KT pk = LS::get(T.skey, p);
+                const uint32_t px = T.entry(p);
+                const uint32_t ps = LS::slot_in(px);
+                const uint64_t sp = LS::get(T.ssz, ps);
+                // past the budget or the SRAM, neither a promotion nor a swap is legal
+                uint32_t may = le64(sp, left) & le64(sp, cap_s);
+                if constexpr (PT::has_inf) may &= pk != (KT)PT::inf_key ? 1u : 0u;
+                if (may) {
+                  uint32_t d = kNone, dx = 0, ds = 0;
+                  uint64_t sd = 0;
+                  more = le64(used_s + sp, cap_s) != 0u;
+                  if (!more) {
+                    d = T.first_sram();
+                    if (d != kNone) {
+                      dx = T.entry(d);
+                      ds = LS::slot_in(dx);
+                      sd = LS::get(T.ssz, ds);
+                      more = ((pk < LS::get(T.skey, d) ? 1u : 0u) & le64(sd, left - sp) &
+                              le64(used_s - sd + sp, cap_s) & le64(used_h - sp + sd, cap_h)) != 0u;
+                    }
+                  }
+                  if (more) {
+                    used_s = used_s - sd + sp;
+                    used_h = used_h - sp + sd;
+                    LS::set(T.snot, p, ~(px | 1u));
+                    LS::set(T.sfl, ps, LS::get(T.sfl, ps) | LS::kSram | LS::kPref);
+                    if (d != kNone) {
+                      LS::set(T.snot, d, ~(dx & ~1u));
+                      LS::set(T.sfl, ds, LS::get(T.sfl, ds) & ~LS::kSram);
+                    }
+                    left -= sp + sd;
+                    moved += sp + sd;
+                    emit(k, d == kNone ? kOpPromote : kOpSwap, px >> LS::kSidShift,
+                         d == kNone ? 0u : dx >> LS::kSidShift);
+                    stop = q_n >= kQueueFlush ? k + 1u : stop;
+                  }
+                }
+              }
+            }
+            if (moved) {
+              // DMA busy for ceil(moved * 1000 / B) ns
+              const uint64_t b = c.u64(kCDma);
+              const uint64_t busy = moved < (1ull << 53) && b < (1ull << 53)
+                                        ? div_by(moved * 1000u + b - 1u, b, c.u64(kCDmaInv))
+                                        : dma_ns(moved, b);
+              dma_free = sat_add(rl(now, k), busy);
+              m_free = ballot(valid && onset_l && now >= dma_free);
+              dma_bytes += moved;
+            }
+          }
+        }
+      }
+      flush();
+    }
+
+    // ---- the window's accounting, an event per lane: eq. (hr-amat), eq. (prered) ----
+    add(kSEvals, lane == 0 ? w_evals : 0u);
+    add(kSResEvals, lane == 0 ? w_res : 0u);
+    const bool h_s = valid && (o_code & 1u), h_h = valid && (o_code & 4u);
+    n_hs += h_s ? 1u : 0u;
+    n_hh += h_h ? 1u : 0u;
+    n_pf += h_s && (o_code & LS::kPref) ? 1u : 0u;
+    if (valid && arrive) {
+      const uint32_t tier = o_code >> 4;  // where the session was placed
+      add(kSDigest, rec_hash((uint32_t)(base + lane), tier ? kOpPlace : kOpBypass, sid,
+                             tier ? tier : kNone));
+      n_byp += tier ? 0u : 1u;
+      ++n_req;
+      const uint64_t old = (uint64_t)len_prev * kvb;
+      const bool h = h_s || h_h;
+      add(kSTok, ln);
+      add(kSComp, h ? ln - len_prev : ln);
+      if (h) {
+        add(h_s ? kSHitS : kSHitH, size);
+        add(h_s ? kSPrevS : kSPrevH, old);
+      } else {
+        add(kSExtra, len_prev);
+        add(kSMiss, ln);
+      }
+    }
+    // odd weight per event: a different victim at any one event changes the sum
+    if (valid) add(kSVictim, ((uint64_t)o_vic + 1u) * ((2ull * (base + lane) + 1ull) * kGolden));
+    base += cnt;
+  }
+
+  e_io = base;
+  pool = Pool{used_s, used_h, dma_free, log_len, n_res, n_table};
+  const auto sum = [&](uint32_t i) { return wave_sum64(sums[i * 64u + lane]); };
+  const auto sum32 = [](uint32_t v) { return (uint32_t)wave_sum64(v); };
+  W.hi = wave_ext32<true>(hi);
+  W.hit_s = sum(kSHitS);
+  W.hit_h = sum(kSHitH);
+  W.miss_tok = sum(kSMiss);
+  W.prev_s = sum(kSPrevS);
+  W.prev_h = sum(kSPrevH);
+  W.req = sum32(n_req);
+  W.n_hs = sum32(n_hs);
+  W.n_hh = sum32(n_hh);
+  W.n_pf = sum32(n_pf);
+  W.n_byp = sum32(n_byp);
+  W.n_evict = sum32(n_evict);
+  W.n_exp = sum32(n_exp);
+  W.n_pro = sum32(n_pro);
+  W.n_swap = sum32(n_swap);
+  W.passes = passes;
+  W.dma_bytes = dma_bytes;
+  W.tok = sum(kSTok);
+  W.comp = sum(kSComp);
+  W.extra = sum(kSExtra);
+  W.evals = sum(kSEvals);
+  W.res_evals = sum(kSResEvals);
+  W.digest = sum(kSDigest);
+  W.victim_digest = sum(kSVictim);
+}
+
+template <int SPL, uint32_t POL, uint32_t SMODE>
+__device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const KeyCtx& K0,
+                                         uint2* queue, uint64_t* sums) {
+  using LS = LaneSim<SPL, POL, SMODE>;
+  using KT = typename LS::KT;
+  using PT = Pol<POL, SMODE>;
+  // each instance computes its own addresses: shared ones would be hoisted
+  // above the switch over policies and stay live in every instance
+  asm volatile("" : "+s"(sim));
+  const unison_sim_params& P = a.params[sim];
+  const uint32_t lane = threadIdx.x;
+  const uint64_t eb = a.ev_off[P.trace], ee = a.ev_off[P.trace + 1];
+  const uint64_t sb = a.sess_off[P.trace];
+  const uint32_t n_sess = (uint32_t)(a.sess_off[P.trace + 1] - sb);
+  const TraceView tr{a.ev_t + eb, a.ev_sid + eb, a.ev_info + eb, a.ev_len + eb, a.ev_next + eb,
+                     a.ev_tool ? a.ev_tool + eb : nullptr, ee - eb, n_sess};
+  const size_t tb = (size_t)sim * a.max_sessions;
+  const bool cont = (a.flags & UNISON_RUN_CONTINUE) != 0;
+  KeyCtx K = K0;
+  K.P = P.penalty_us;
+  K.lambda = (1u << P.b_h) - 1u;
+  K.p_z = P.p_z;
+  K.pack44 = false;  // keys compare as they are
+  K.online_cap = uni32(P.hazard_online ? P.online_sessions : 0u);
+  K.eta = a.eta + (size_t)P.trace * kEtaClasses;
+  K.recip_bits = P.recip_bits;
+
+  uint64_t e = 0;
+  bool ok = true;
+  LS T;
+  T.lane = lane;
+  T.init();
+  if (cont) {
+    e = uni64(a.state[sim].next_event);
+    ok = uni64(a.counters[sim].error) == 0ull;
+  } else {
+    for (uint32_t i = lane; i < n_sess; i += 64) {
+      a.t_mg[tb + i] = 0;
+      a.t_gq[tb + i] = 0;
+      a.t_len[tb + i] = 0;
+      a.t_last[tb + i] = 0;
+      a.t_next[tb + i] = ~0ull;
+    }
+  }
+  __syncthreads();
+  // residents never exceed min(N_sess, sessions): the launcher picks a kernel that holds them
+  const uint64_t max_res = P.n_slots < n_sess ? P.n_slots : n_sess;
+  bool fits = !P.dual_sync && max_res <= 64u * SPL;
+  ok = ok && fits;
+
+  // a resumed table's residents take slots, in session order
+  if (cont && ok) {
+    uint32_t n = 0;
+    for (uint32_t b = 0; b < n_sess && ok; b += 64) {
+      const uint32_t i = b + lane;
+      const bool in = i < n_sess;
+      const uint64_t x = in ? a.t_mg[tb + i] : 0ull;
+      const uint32_t m = (uint32_t)x;
+      const uint64_t q = in ? a.t_gq[tb + i] : 0ull;
+      const uint64_t last = in ? a.t_last[tb + i] : 0ull, next = in ? a.t_next[tb + i] : ~0ull;
+      const uint64_t sz = in ? (uint64_t)a.t_len[tb + i] * a.sess_kvb[sb + i] : 0ull;
+      const float g = __uint_as_float((uint32_t)(x >> 32));
+      const bool done = meta_phase(m) == kDoneP;
+      const KT key = LS::key_from(K, done, meta_turn(m), g, q, last, next);
+      // while the launch runs only the slots know the tiers: a resident that
+      // leaves without an event of its own must not keep one in the table
+      if (in && meta_tier(m) != kTierNone)
+        *reinterpret_cast<uint32_t*>(a.t_mg + tb + i) = with_tier(m, kTierNone) & ~kPrefetched;
+      for (uint64_t bits = ballot(in && meta_tier(m) != kTierNone); bits; bits &= bits - 1u) {
+        if (n >= 64u * SPL) {
+          ok = fits = false;
+          break;
+        }
+        const uint32_t l = (uint32_t)__builtin_ctzll(bits);
+        const uint32_t mm = rl(m, l), s = b + l;
+        const uint32_t fl = (meta_tier(mm) == kTierSram ? LS::kSram : 0u) |
+                            ((mm & kPrefetched) ? LS::kPref : 0u);
+        LS::set(T.ssid, n, s);
+        LS::set(T.sfl, n, fl);
+        LS::set(T.ssz, n, rl(sz, l));
+        LS::set(T.sturn, n, meta_turn(mm));
+        LS::set(T.sema, n, PT::fixed ? rl(q, l) : (uint64_t)rl((uint32_t)(x >> 32), l));
+        if (meta_phase(mm) != kServing)
+          T.insert(rl(key, l), (s << LS::kSidShift) | (n << 2) |
+                                   (meta_phase(mm) == kDoneP ? LS::kDoneB : 0u) | (fl & LS::kSram));
+        ++n;
+      }
+    }
+  }
+  const bool log_on = (a.flags & UNISON_RUN_LOG) && a.log_cap;
+  const LogSink L{log_on, log_on ? a.log + (size_t)sim * a.log_cap : nullptr, a.log_cap, lane == 0,
+                  log_on && (a.flags & UNISON_RUN_LOG_VICTIM) != 0};
+  const uint64_t e0 = e;
+  uint64_t bad = 0;
+  Totals W{};
+  Pool pool{};
+  if (cont) {
+    const SimState& st = a.state[sim];
+    pool = Pool{uni64(st.used_s), uni64(st.used_h), uni64(st.dma_free_at), uni64(st.log_len),
+                uni32(st.n_res), uni32(st.n_table)};
+  }
+  if (ok) {
+    const uint64_t bad_at = a.first_bad[P.trace];
+    uint64_t end = (e >= tr.n_ev || tr.n_ev - e < a.max_events) ? tr.n_ev : e + a.max_events;
+    if (bad_at < end) {
+      end = bad_at;
+      bad = bad_at + 1;
+    }
+    if (e < end)
+      lane_events<SPL, POL, SMODE>(a, P, K, tr, tb, a.sess_kvb + sb, queue, sums, T, pool, W, L, e, end);
+    __syncthreads();
+    // the residents' tiers into the table
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < SPL; ++j)
+      if (T.ssid[j] != kNone) {
+        uint32_t* w = reinterpret_cast<uint32_t*>(a.t_mg + tb + T.ssid[j]);
+        *w = with_tier(*w, (T.sfl[j] & LS::kSram) ? kTierSram : kTierHbm) |
+             ((T.sfl[j] & LS::kPref) ? kPrefetched : 0u);
+      }
+  }
+  store_hazard(a, P, sim, K, lane, 64);
+  if (lane == 0) {
+    Scalars S{};
+    Cnt C = cnt_from(unison_counters{});
+    if (cont) {
+      load_scalars(a.state[sim], S);
+      C = cnt_from(a.counters[sim]);
+    }
+    if (!fits) C.error = ~0ull;
+    if (bad) C.error = bad;
+    S.used_s = pool.used_s;
+    S.used_h = pool.used_h;
+    S.dma_free_at = pool.dma_free;
+    S.log_len = pool.log_len;
+    S.n_res = pool.n_res;
+    S.n_table = pool.n_table;
+    if (S.hi > n_sess) S.hi = n_sess;
+    S.hi = W.hi > S.hi ? W.hi : S.hi;
+    S.hit_s_bytes += W.hit_s;
+    S.hit_h_bytes += W.hit_h;
+    S.miss_tok += W.miss_tok;
+    S.prev_s_bytes += W.prev_s;
+    S.prev_h_bytes += W.prev_h;
+    C.requests += W.req;
+    C.hit_sram += W.n_hs;
+    C.hit_hbm += W.n_hh;
+    C.miss += W.req - W.n_hs - W.n_hh;
+    C.prefetch_hits += W.n_pf;
+    C.bypass += W.n_byp;
+    C.evict += W.n_evict;
+    C.expire += W.n_exp;
+    C.promote += W.n_pro;
+    C.swap += W.n_swap;
+    C.tide_passes += W.passes;
+    C.dma_bytes += W.dma_bytes;
+    C.tokens_total += W.tok;
+    C.tokens_computed += W.comp;
+    C.extra_prefill += W.extra;
+    C.score_evals += W.evals;
+    C.resident_evals += W.res_evals;
+    C.digest += W.digest;
+    C.victim_digest += W.victim_digest;
+    C.events += (uint32_t)(e - e0);
+    finish_costs(S, P, C);
+    store_scalars(a.state[sim], S, e);
+    a.counters[sim] = cnt_to(C);
+  }
+}
+
+template <int SPL>
+__global__ __launch_bounds__(64, SPL == 1 ? 4 : SPL == 2 ? 2 : 1) void sim_lane_kernel(SimArgs a) {
+  __shared__ float s_hf[52];
+  __shared__ uint32_t s_hq[52];
+  __shared__ uint32_t s_hd[52];
+  __shared__ uint32_t s_hn[52];
+  __shared__ uint2 s_queue[queue_entries(64u * SPL)];
+  __shared__ uint64_t s_sums[kSums * 64u];
+  const uint32_t sim = blockIdx.x;
+  const unison_sim_params& P = a.params[sim];
+  const uint32_t lambda = (1u << P.b_h) - 1u;
+  const KeyCtx K{s_hf, s_hq, s_hd, s_hn, P.penalty_us, lambda, P.p_z, a.time44 != 0,
+                 P.hazard_online ? P.online_sessions : 0u, a.eta + (size_t)P.trace * kEtaClasses,
+                 P.recip_bits};
+  load_hazard(a, P, sim, K, threadIdx.x, 64);
+  __syncthreads();
+  switch (sim_policy(a, P)) {
+    case kSpear:
+      if (P.score_mode) lane_run<SPL, kSpear, 1>(a, sim, K, s_queue, s_sums);
+      else lane_run<SPL, kSpear, 0>(a, sim, K, s_queue, s_sums);
+      break;
+    case kLru: lane_run<SPL, kLru, 0>(a, sim, K, s_queue, s_sums); break;
+    case kTimeout: lane_run<SPL, kTimeout, 0>(a, sim, K, s_queue, s_sums); break;
+    case kBelady: lane_run<SPL, kBelady, 0>(a, sim, K, s_queue, s_sums); break;
+    default: lane_run<SPL, kEta, 0>(a, sim, K, s_queue, s_sums); break;
+  }
+}
+
+template <int SPL>
+void launch_width(const SimArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((sim_lane_kernel<SPL>), dim3(a.n_sims), dim3(64), 0, stream, a);
+}
+
+}  // namespace
+
+// max_res: the most residents any simulation can hold, at most 512.
+hipError_t launch_lanes(const SimArgs& a, uint64_t max_res, hipStream_t stream) {
+  if (max_res <= 64) launch_width<1>(a, stream);
+  else if (max_res <= 128) launch_width<2>(a, stream);
+  else if (max_res <= 256) launch_width<4>(a, stream);
+  else if (max_res <= 512) launch_width<8>(a, stream);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace unison

@@ -9,7 +9,8 @@
 //
 // The event loop of a simulation is sequential; parallelism comes from
 // running many simulations at once and from the scan inside each event.
-// Two table layouts share one event engine:
+// One event engine runs over these table layouts (lane.hip has an engine of its
+// own, with the residents sorted across a wavefront's lanes):
 //   RegTable<G, EPL>  a group of G lanes (4 to 64) per simulation; each lane
 //                     owns EPL sessions (sid = j*G + lane) and keeps their
 //                     register-file entries in VGPRs.  Keys are computed per
@@ -27,314 +28,13 @@
 // so control flow is uniform within a group.
 #include <hip/hip_runtime.h>
 
-#include "unison_device.h"
+#include "sim_device.h"
 
 #pragma clang fp contract(off)
 
 namespace unison {
 
-// ------------------------------------------------------- cross-lane moves
-
-// Every pattern used here reads a lane of the same row, so no lane needs a
-// fallback value (mov_dpp leaves the destination's old value unspecified).
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
-}
-
-// Partner value for butterfly step M.  Before step M every aligned block of
-// M lanes holds one value; the partner lane lies in the sibling block.
-template <int M>
-__device__ __forceinline__ uint32_t xchg(uint32_t v) {
-  if constexpr (M == 1) return dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-  else if constexpr (M == 2) return dpp<0x4E>(v);  // quad_perm [2,3,0,1]
-  else if constexpr (M == 4) return dpp<0x141>(v);  // row_half_mirror
-  else if constexpr (M == 8) return dpp<0x140>(v);  // row_mirror
-  else if constexpr (M == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);  // xor 16
-  else return (uint32_t)__shfl_xor((int)v, 32);
-}
-
-struct Cand {
-  uint64_t key;
-  uint32_t sid;
-};
-
-__device__ __forceinline__ bool max_better(uint64_t ka, uint32_t sa, uint64_t kb, uint32_t sb) {
-  return ka > kb || (ka == kb && sa < sb);
-}
-__device__ __forceinline__ bool min_better(uint64_t ka, uint32_t sa, uint64_t kb, uint32_t sb) {
-  return ka < kb || (ka == kb && sa < sb);
-}
-__device__ __forceinline__ Cand cand_none_max() { return Cand{0ull, kNone}; }
-__device__ __forceinline__ Cand cand_none_min() { return Cand{~0ull, kNone}; }
-
-// Max (MAX) or min of a 32-bit value over each aligned group of W lanes;
-// every lane of the group ends with it.
-template <int W, int M, bool MAX>
-__device__ __forceinline__ uint32_t group_ext32(uint32_t v) {
-  if constexpr (M < W) {
-    const uint32_t o = xchg<M>(v);
-    return group_ext32<W, M * 2, MAX>(MAX ? (o > v ? o : v) : (o < v ? o : v));
-  } else {
-    return v;
-  }
-}
-
-// Max (MAX) or min of a packed 64-bit value over each aligned group of W
-// lanes, as two 32-bit words, most significant first: the group's best high
-// word, then the best low word among the lanes that hold it (the others enter
-// the empty value).  Each word's step is one max or min with a lane permute,
-// which the compiler folds into one DPP instruction, where a 64-bit step
-// needs two permutes, a compare and two selects.
-template <int W, bool MAX>
-__device__ __forceinline__ uint64_t reduce_words(uint64_t c) {
-  const uint32_t hi = (uint32_t)(c >> 32);
-  const uint32_t h = group_ext32<W, 1, MAX>(hi);
-  const uint32_t lo = hi == h ? (uint32_t)c : (MAX ? 0u : ~0u);
-  return ((uint64_t)h << 32) | group_ext32<W, 1, MAX>(lo);
-}
-
-template <int W, int M>
-__device__ __forceinline__ uint32_t reduce_min32(uint32_t c) {
-  if constexpr (M < W) {
-    const uint32_t o = xchg<M>(c);
-    return reduce_min32<W, M * 2>(o < c ? o : c);
-  } else {
-    return c;
-  }
-}
-
-// Every lane of an aligned group of W lanes ends with the winner (ties to
-// the smaller session id): the key's two words, most significant first, then
-// the smallest id among the lanes still tied, each over the lanes that hold
-// the best word so far (the others enter the empty value).
-template <int W, bool MAX>
-__device__ __forceinline__ Cand reduce_group(Cand c) {
-  const uint32_t empty = MAX ? 0u : ~0u;
-  const uint32_t khi = (uint32_t)(c.key >> 32), klo = (uint32_t)c.key;
-  const uint32_t h = group_ext32<W, 1, MAX>(khi);
-  const bool tied = khi == h;
-  const uint32_t l = group_ext32<W, 1, MAX>(tied ? klo : empty);
-  const uint32_t s = group_ext32<W, 1, false>(tied && klo == l ? c.sid : ~0u);
-  return Cand{((uint64_t)h << 32) | l, s};
-}
-
-// Whole-wavefront max (MAX) or min of a 32-bit value, uniform: a DPP
-// butterfly inside each row of 16 lanes, then the four row results compared
-// in scalar registers (no cross-row permute through the LDS crossbar).
-template <bool MAX>
-__device__ __forceinline__ uint32_t ext32(uint32_t a, uint32_t b) {
-  return MAX ? (a > b ? a : b) : (a < b ? a : b);
-}
-template <bool MAX>
-__device__ __forceinline__ uint32_t wave_ext32(uint32_t v) {
-  v = ext32<MAX>(v, xchg<1>(v));
-  v = ext32<MAX>(v, xchg<2>(v));
-  v = ext32<MAX>(v, xchg<4>(v));
-  v = ext32<MAX>(v, xchg<8>(v));
-  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
-  const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
-  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
-  const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
-  return ext32<MAX>(ext32<MAX>(r0, r1), ext32<MAX>(r2, r3));
-}
-// One phase of a lexicographic wavefront reduction over N words per lane:
-// the best word M among the active ones; with NARROW, a word stays active
-// only where it equals M, so the next phase breaks the ties.
-template <bool MAX, bool NARROW, int N>
-__device__ __forceinline__ uint32_t lex_phase(const uint32_t (&w)[N], bool (&act)[N]) {
-  uint32_t v = MAX ? 0u : ~0u;
-#pragma unroll
-  for (int k = 0; k < N; ++k) v = act[k] ? ext32<MAX>(v, w[k]) : v;
-  const uint32_t m = wave_ext32<MAX>(v);
-  if constexpr (NARROW) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) act[k] = act[k] && w[k] == m;
-  }
-  return m;
-}
-
-// Sum mod 2^64 over the wavefront; every lane ends with it.
-__device__ __forceinline__ uint64_t wave_sum64_step(uint64_t v, uint32_t lo, uint32_t hi) {
-  return v + (((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
-  v = wave_sum64_step(v, xchg<1>((uint32_t)v), xchg<1>((uint32_t)(v >> 32)));
-  v = wave_sum64_step(v, xchg<2>((uint32_t)v), xchg<2>((uint32_t)(v >> 32)));
-  v = wave_sum64_step(v, xchg<4>((uint32_t)v), xchg<4>((uint32_t)(v >> 32)));
-  v = wave_sum64_step(v, xchg<8>((uint32_t)v), xchg<8>((uint32_t)(v >> 32)));
-  v = wave_sum64_step(v, xchg<16>((uint32_t)v), xchg<16>((uint32_t)(v >> 32)));
-  v = wave_sum64_step(v, xchg<32>((uint32_t)v), xchg<32>((uint32_t)(v >> 32)));
-  return v;
-}
-
-// Pins a value to a vector register.  A workgroup-per-simulation kernel keeps
-// its long-lived per-simulation state (pool usage, counters) there: held in
-// scalar registers it would exceed them and spill on every event.
-__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-__device__ __forceinline__ uint64_t in_vgpr(uint64_t v) {
-  return ((uint64_t)in_vgpr((uint32_t)(v >> 32)) << 32) | in_vgpr((uint32_t)v);
-}
-__device__ __forceinline__ double in_vgpr(double v) {
-  return __longlong_as_double((long long)in_vgpr((uint64_t)__double_as_longlong(v)));
-}
-
-__device__ __forceinline__ uint32_t uni32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-  return ((uint64_t)uni32((uint32_t)(v >> 32)) << 32) | uni32((uint32_t)v);
-}
-// A condition every lane of the wavefront evaluates alike (UNI), as a scalar
-// branch condition: values pinned to vector registers would otherwise make
-// the compiler treat the branch as divergent (exec masking, merges of every
-// live value at the join).
-template <bool UNI>
-__device__ __forceinline__ bool uc(bool c) {
-  if constexpr (UNI) return __builtin_amdgcn_ballot_w64(c) != 0ull;
-  else return c;
-}
-
-// ------------------------------------------------------------ keys
-
-template <uint32_t POL, uint32_t SMODE>
-struct Pol {
-  static constexpr bool spear = POL == kSpear;
-  static constexpr bool fixed = spear && SMODE == 1;
-  static constexpr bool belady = POL == kBelady;
-  static constexpr bool eta = POL == kEta;
-  // the key is the session's next arrival: true (Belady) or predicted (ETA)
-  static constexpr bool nextkey = belady || eta;
-  static constexpr bool timeout = POL == kTimeout;
-  static constexpr bool recency = POL == kLru || POL == kTimeout;
-  static constexpr bool has_inf = spear || nextkey;
-  static constexpr uint64_t inf_key = (spear && !fixed) ? 0x7F800000ull : ~0ull;
-};
-
-// The simulation's hazard table lives in LDS: its counts d(t), n(t) of
-// eq. (hazard) and both derived forms, h as fp32 and h_q (eq. (hq)).  An
-// online table (online_cap > 0) grows by one session at each of the first
-// online_cap completions.
-struct KeyCtx {
-  float* hf;            // LDS [52]
-  uint32_t* hq;         // LDS [52]
-  uint32_t* hd;         // LDS [52]
-  uint32_t* hn;         // LDS [52]
-  float P;
-  uint32_t lambda;
-  uint64_t p_z;
-  bool pack44;          // times fit 44 bits and ids 20 bits: recency / Belady keys pack
-  uint32_t online_cap;  // completions an online table still may count; 0: fixed table
-  const uint64_t* eta;  // the trace's ETA table: expected wait per tool class, ns (global)
-  uint32_t recip_bits;  // eq. (t1) by a reciprocal of this many fraction bits; 0: exact
-};
-
-// Adds a completed session of Tn turns to the counts (n(t) += 1 for t < Tn,
-// d(Tn - 1) += 1) and rebuilds the entries it changed; t is split over
-// `width` cooperating lanes starting at `lane`.
-__device__ __forceinline__ void hazard_add_counts(const KeyCtx& K, uint32_t Tn, uint32_t lane,
-                                                  uint32_t width) {
-  for (uint32_t t = lane; t < kLut; t += width) {
-    const uint32_t dn = t < Tn ? 1u : 0u;
-    const uint32_t dd = t + 1u == Tn ? 1u : 0u;
-    if (dn | dd) {
-      const uint32_t d = K.hd[t] + dd;
-      const uint32_t n = K.hn[t] + dn;
-      K.hd[t] = d;
-      K.hn[t] = n;
-      K.hf[t] = hazard_f32(d, n);
-      K.hq[t] = hazard_q(d, n, K.lambda);
-    }
-  }
-}
-
-// The hazard entry eq. (hazard) / eq. (hq) of a session at turn index t
-// (clamped to 50): fp32 bits of h for the fp32 score, h_q for the integer one.
-template <uint32_t POL, uint32_t SMODE>
-__device__ __forceinline__ uint32_t hazard_of(const KeyCtx& K, uint32_t meta) {
-  using PT = Pol<POL, SMODE>;
-  if constexpr (PT::spear) {
-    uint32_t t = meta_turn(meta);
-    t = t < 50u ? t : 50u;
-    return PT::fixed ? K.hq[t] : __float_as_uint(K.hf[t]);
-  } else {
-    return 0u;
-  }
-}
-
-// "Larger key = evict first".  SPEAR: the score (eq. (esp) or eq. (scoreq))
-// from the entry's hazard value hz (hazard_of); completed sessions take
-// S_max.  LRU / timeout: older last event first.  Belady: later next arrival
-// first.
-template <uint32_t POL, uint32_t SMODE>
-__device__ __forceinline__ uint64_t key_of(const KeyCtx& K, uint32_t meta, uint32_t hz, float g,
-                                           uint64_t gq, uint64_t last, uint64_t next) {
-  using PT = Pol<POL, SMODE>;
-  if constexpr (PT::spear) {
-    const bool done = meta_phase(meta) == kDoneP;
-    if constexpr (PT::fixed) {
-      const uint64_t s = spear_fixed(hz, gq, K.lambda, K.p_z, K.recip_bits);
-      return done ? ~0ull : s;
-    } else {
-      const float s = spear_f32(__uint_as_float(hz), g, K.P);
-      return done ? 0x7F800000ull : (uint64_t)__float_as_uint(s);
-    }
-  } else if constexpr (PT::nextkey) {
-    return next;
-  } else {
-    return ~0ull - last;
-  }
-}
-
-// A session's timer has fired (now - last > ttl) exactly when last lies below
-// this threshold: last never exceeds now, and nothing fires while now <= ttl.
-__device__ __forceinline__ uint64_t idle_threshold(uint64_t now, uint64_t ttl) {
-  return now > ttl ? now - ttl : 0ull;
-}
-
-struct Entry {
-  uint32_t meta;
-  float g;
-  uint64_t gq;
-  uint32_t len;
-  uint32_t kvb;
-  uint64_t last;
-  uint64_t next;
-};
-
-struct TraceView {
-  const uint64_t* t;
-  const uint32_t* sid;
-  const uint32_t* info;
-  const uint32_t* len;
-  const uint64_t* next;
-  const uint32_t* tool;  // or null: every gap is tool class 0
-  uint64_t n_ev;
-  uint32_t n_sess;
-};
-
-struct Ev {
-  uint64_t t;
-  uint32_t sid, info, len, tool;
-  uint64_t next;
-};
-
-// The event record; the next arrival only where the key reads it (Belady),
-// the tool class only where it predicts one (ETA).
-template <bool NEXT, bool TOOL>
-__device__ __forceinline__ Ev load_ev(const TraceView& tr, uint64_t e) {
-  Ev v;
-  v.t = tr.t[e];
-  v.sid = tr.sid[e];
-  v.info = tr.info[e];
-  v.len = tr.len[e];
-  v.next = NEXT ? tr.next[e] : ~0ull;
-  v.tool = (TOOL && tr.tool) ? tr.tool[e] : 0u;
-  return v;
-}
+hipError_t launch_lanes(const SimArgs& a, uint64_t max_res, hipStream_t stream);
 
 // Event records one event ahead: the next record's loads are in flight while
 // the current event is processed.
@@ -349,62 +49,6 @@ struct AheadReader {
     const Ev c = cur;
     cur = load_ev<NEXT, TOOL>(tr, e + 1 < end ? e + 1 : e);
     return c;
-  }
-};
-
-// Event records 64 at a time for a lone wavefront: lane l holds event base + l
-// of the current window and of the next, whose loads are issued a whole
-// window ahead; an event's fields are read out of its lane.
-template <bool NEXT, bool TOOL>
-struct WindowReader {
-  const TraceView& tr;
-  uint64_t end, base;
-  uint32_t lane;
-  uint64_t ct, cn, nt, nn;
-  uint32_t csid, cinfo, clen, ctool, nsid, ninfo, nlen, ntool;
-  __device__ __forceinline__ void load(uint64_t b, uint64_t& t, uint32_t& sid, uint32_t& info,
-                                       uint32_t& len, uint64_t& nx, uint32_t& tool) const {
-    const uint64_t e = b + lane;
-    const bool ok = e < end;
-    const uint64_t i = ok ? e : (end ? end - 1 : 0);
-    t = tr.t[i];
-    sid = tr.sid[i];
-    info = tr.info[i];
-    len = tr.len[i];
-    nx = NEXT ? tr.next[i] : ~0ull;
-    tool = (TOOL && tr.tool) ? tr.tool[i] : 0u;
-  }
-  __device__ __forceinline__ WindowReader(const TraceView& t, uint64_t e, uint64_t end_, void*)
-      : tr(t), end(end_), base(e), lane(threadIdx.x & 63u) {
-    load(base, ct, csid, cinfo, clen, cn, ctool);
-    load(base + 64, nt, nsid, ninfo, nlen, nn, ntool);
-  }
-  __device__ __forceinline__ static uint64_t lane64(uint64_t v, int k) {
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), k) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, k);
-  }
-  // Session id of event e, the event after the one take() returned last (at
-  // the end of the trace, the last event's: the window repeats it).
-  __device__ __forceinline__ uint32_t peek_sid(uint64_t e) const {
-    const uint64_t k = e - base;
-    return k < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)csid, (int)k)
-                  : (uint32_t)__builtin_amdgcn_readlane((int)nsid, (int)(k - 64));
-  }
-  __device__ __forceinline__ Ev take(uint64_t e) {
-    if (e - base >= 64) {
-      ct = nt; csid = nsid; cinfo = ninfo; clen = nlen; cn = nn; ctool = ntool;
-      base += 64;
-      load(base + 64, nt, nsid, ninfo, nlen, nn, ntool);
-    }
-    const int k = (int)(e - base);
-    Ev v;
-    v.t = lane64(ct, k);
-    v.sid = (uint32_t)__builtin_amdgcn_readlane((int)csid, k);
-    v.info = (uint32_t)__builtin_amdgcn_readlane((int)cinfo, k);
-    v.len = (uint32_t)__builtin_amdgcn_readlane((int)clen, k);
-    v.next = NEXT ? lane64(cn, k) : ~0ull;
-    v.tool = TOOL ? (uint32_t)__builtin_amdgcn_readlane((int)ctool, k) : 0u;
-    return v;
   }
 };
 
@@ -1335,352 +979,6 @@ struct LaneQueue {
 
 };
 
-// Residents in registers, table in LDS, one wavefront per simulation.  Every
-// session's entry stays in LDS (as in the LDS-resident MemTable), and each
-// resident also occupies a VGPR slot of the wavefront -- its session id, meta,
-// size and key -- kept current wherever the engine writes an entry.  Residents
-// never exceed N_sess (eq. (cap)), so SPL slots per lane hold them all while
-// N_sess <= 64 SPL: every scan and TIDE selection is then a reduction over the
-// slots alone, with no table memory touched, and an event reads only its own
-// session's entry.  The single wavefront's LDS accesses are in program order,
-// so no barrier is needed anywhere.
-template <int SPL, uint32_t POL, uint32_t SMODE>
-struct SlotTable : LaneQueue {
-  using PT = Pol<POL, SMODE>;
-  static constexpr bool kViews = false;
-  static constexpr bool kFuseGap = true;
-  static constexpr bool kDeferD = false;
-  // Digest terms are queued one per lane and hashed 64 at a time.
-  static constexpr bool kLaneDigest = true;
-  static constexpr bool kPrefetch = false;
-  __device__ __forceinline__ void* window() const { return nullptr; }
-  struct Pf {};
-  __device__ __forceinline__ Pf prefetch_issue(uint32_t) { return Pf{}; }
-  __device__ __forceinline__ void prefetch_land(const Pf&) {}
-  template <bool N, bool T>
-  using Reader = WindowReader<N, T>;  // events come 64 to a window, one per lane
-  uint64_t* mg;
-  uint64_t* gq;
-  uint32_t* len;
-  uint32_t* kvb;
-  uint64_t* last;
-  uint64_t* next;
-  KeyCtx kc;
-  uint32_t ssid[SPL];   // kNone: free
-  uint32_t smeta[SPL];
-  uint64_t skey[SPL];
-  uint64_t ssize[SPL];
-  // the entry of the latest write(): its key, KV bytes per token and length
-  uint32_t w_sid;
-  uint64_t w_key;
-  uint32_t w_kvb, w_len;
-
-  __device__ __forceinline__ uint64_t key_from(uint32_t m, float g, uint64_t q, uint64_t l,
-                                               uint64_t n) const {
-    return key_of<POL, SMODE>(kc, m, hazard_of<POL, SMODE>(kc, m), g, q, l, n);
-  }
-  // the key of entry i from its fields in LDS (per lane)
-  __device__ __forceinline__ uint64_t key_at(uint32_t i) const {
-    const uint64_t x = mg[i];
-    return key_from((uint32_t)x, __uint_as_float((uint32_t)(x >> 32)), PT::fixed ? gq[i] : 0ull,
-                    PT::recency ? last[i] : 0ull, PT::nextkey ? next[i] : ~0ull);
-  }
-
-  template <class T>
-  __device__ __forceinline__ static T pick(const T (&a)[SPL], uint32_t j) {
-    T v = a[0];
-#pragma unroll
-    for (int k = 1; k < SPL; ++k) v = j == (uint32_t)k ? a[k] : v;
-    return v;
-  }
-  // The slot (j, lane l) holding sid; false if sid is not resident.
-  __device__ __forceinline__ bool find(uint32_t sid, uint32_t& j, uint32_t& l) const {
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) {
-      const uint64_t b = __builtin_amdgcn_ballot_w64(ssid[k] == sid);
-      if (b) {
-        j = (uint32_t)k;
-        l = (uint32_t)__builtin_ctzll(b);
-        return true;
-      }
-    }
-    return false;
-  }
-  __device__ __forceinline__ void put(uint32_t j, uint32_t l, uint32_t sid, uint32_t m,
-                                      uint64_t key, uint64_t size) {
-    const bool mine = lane == l;
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) {
-      const bool w = mine && j == (uint32_t)k;
-      ssid[k] = w ? sid : ssid[k];
-      smeta[k] = w ? m : smeta[k];
-      skey[k] = w ? key : skey[k];
-      ssize[k] = w ? size : ssize[k];
-    }
-  }
-  __device__ __forceinline__ void set_slot_meta(uint32_t j, uint32_t l, uint32_t m) {
-    const bool mine = lane == l;
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) smeta[k] = (mine && j == (uint32_t)k) ? m : smeta[k];
-  }
-  __device__ __forceinline__ void set_slot_key(uint32_t j, uint32_t l, uint32_t m, uint64_t key) {
-    const bool mine = lane == l;
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) {
-      const bool w = mine && j == (uint32_t)k;
-      smeta[k] = w ? m : smeta[k];
-      skey[k] = w ? key : skey[k];
-    }
-  }
-  // A resident enters the first free slot.
-  __device__ __forceinline__ void insert(uint32_t sid, uint32_t m, uint64_t key, uint64_t size) {
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) {
-      const uint64_t b = __builtin_amdgcn_ballot_w64(ssid[k] == kNone);
-      if (b) {
-        put((uint32_t)k, (uint32_t)__builtin_ctzll(b), sid, m, key, size);
-        return;
-      }
-    }
-  }
-  // Meta word m of entry sid: LDS, and the resident set it implies.
-  __device__ __forceinline__ void meta_to(uint32_t sid, uint32_t m) {
-    if (lane == 0) reinterpret_cast<uint32_t*>(mg + sid)[0] = m;
-    uint32_t j, l;
-    const bool res = find(sid, j, l);
-    const bool now = meta_tier(m) != kTierNone;
-    if (res && !now) {
-      put(j, l, kNone, 0u, 0ull, 0ull);
-    } else if (res) {
-      set_slot_meta(j, l, m);
-    } else if (now) {
-      uint64_t key, size;
-      if (sid == w_sid) {
-        key = w_key;
-        size = (uint64_t)w_len * w_kvb;
-      } else {
-        key = uni64(key_at(sid));
-        size = (uint64_t)uni32(len[sid]) * uni32(kvb[sid]);
-      }
-      insert(sid, m, key, size);
-    }
-  }
-
-  __device__ __forceinline__ void event_begin() {}
-  __device__ __forceinline__ void grow(uint32_t) {}
-
-  __device__ __forceinline__ Entry read(uint32_t sid) const {
-    Entry e;
-    const uint64_t x = uni64(mg[sid]);
-    e.meta = (uint32_t)x;
-    e.g = __uint_as_float((uint32_t)(x >> 32));
-    e.gq = PT::fixed ? uni64(gq[sid]) : 0ull;
-    e.len = uni32(len[sid]);
-    e.kvb = uni32(kvb[sid]);
-    e.last = uni64(last[sid]);
-    e.next = PT::nextkey ? uni64(next[sid]) : ~0ull;
-    return e;
-  }
-  __device__ __forceinline__ void read_size(uint32_t sid, uint64_t& size, uint32_t& m) const {
-    uint32_t j, l;
-    if (find(sid, j, l)) {
-      const uint64_t sz = pick(ssize, j);
-      size = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(sz >> 32), (int)l) << 32) |
-             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sz, (int)l);
-      m = (uint32_t)__builtin_amdgcn_readlane((int)pick(smeta, j), (int)l);
-    } else {
-      m = uni32((uint32_t)mg[sid]);
-      size = (uint64_t)uni32(len[sid]) * uni32(kvb[sid]);
-    }
-  }
-  __device__ __forceinline__ void read_end(uint32_t sid, Entry& e) const {
-    const uint64_t x = uni64(mg[sid]);
-    e.meta = (uint32_t)x;
-    e.g = __uint_as_float((uint32_t)(x >> 32));
-    e.gq = PT::fixed ? uni64(gq[sid]) : 0ull;
-  }
-  __device__ __forceinline__ void write_end(uint32_t sid, const Entry& e, uint64_t t, uint64_t nx) {
-    if (lane == 0) {
-      reinterpret_cast<uint32_t*>(mg + sid)[0] = e.meta;
-      last[sid] = t;
-      if constexpr (PT::nextkey) next[sid] = nx;
-    }
-    w_sid = kNone;
-    uint32_t j, l;
-    if (find(sid, j, l)) set_slot_key(j, l, e.meta, key_from(e.meta, e.g, e.gq, t, nx));
-  }
-  __device__ __forceinline__ void write(uint32_t sid, const Entry& e) {
-    if (lane == 0) {
-      mg[sid] = (uint64_t)e.meta | ((uint64_t)__float_as_uint(e.g) << 32);
-      if constexpr (PT::fixed) gq[sid] = e.gq;
-      len[sid] = e.len;
-      last[sid] = e.last;
-      if constexpr (PT::nextkey) next[sid] = e.next;
-    }
-    w_sid = sid;
-    w_key = key_from(e.meta, e.g, e.gq, e.last, e.next);
-    w_kvb = e.kvb;
-    w_len = e.len;
-    uint32_t j, l;
-    if (find(sid, j, l)) set_slot_key(j, l, e.meta, w_key);
-  }
-  __device__ __forceinline__ void set_meta(uint32_t sid, uint32_t m) { meta_to(sid, m); }
-  __device__ __forceinline__ void set_len_meta(uint32_t sid, uint32_t l, uint32_t m) {
-    if (lane == 0) len[sid] = l;
-    if (sid == w_sid) w_len = l;
-    meta_to(sid, m);
-  }
-  __device__ __forceinline__ void set_turn(uint32_t, uint32_t, const KeyCtx&) {}
-  __device__ __forceinline__ void scan(const KeyCtx&, uint32_t) {}
-
-  // Candidates reduce as one 64-bit word where the key allows: an fp32 score
-  // above the id (complemented for argmax, so ties go to the smaller id), or a
-  // time below 2^44 above a 20-bit id; other keys reduce as (key, id) pairs.
-  // 0 and 2^64 - 1 stay free as the empty values (ids stay far below 2^20 - 1:
-  // the table is LDS-resident).
-  static constexpr uint64_t kCap44 = (1ull << 44) - 1;
-  __device__ __forceinline__ int pack_mode() const {
-    if constexpr (PT::spear && !PT::fixed) return 1;
-    if constexpr (PT::recency || PT::belady) return kc.pack44 ? 2 : 0;
-    return 0;
-  }
-  template <bool MAX>
-  __device__ __forceinline__ static uint64_t pack(int mode, uint64_t key, uint32_t sid) {
-    if (mode == 1) return (key << 32) | (MAX ? 0xFFFFFFFFu - sid : sid);
-    uint64_t k44;
-    if constexpr (PT::belady) k44 = key < kCap44 ? key : kCap44;
-    else k44 = key & kCap44;  // recency: key = 2^64 - 1 - last, last below 2^44 - 1
-    return (k44 << 20) | (MAX ? 0xFFFFFu - sid : sid);
-  }
-  template <bool MAX>
-  __device__ __forceinline__ static Cand unpack(int mode, uint64_t c) {
-    const bool none = MAX ? c == 0ull : c == ~0ull;
-    if (mode == 1) {
-      const uint32_t lo = (uint32_t)c;
-      return Cand{c >> 32, none ? kNone : (MAX ? 0xFFFFFFFFu - lo : lo)};
-    }
-    const uint32_t lo = (uint32_t)c & 0xFFFFFu;
-    const uint64_t k44 = c >> 20;
-    uint64_t key;
-    if constexpr (PT::belady) key = k44 == kCap44 ? ~0ull : k44;
-    else key = k44 | ~kCap44;
-    return Cand{key, none ? kNone : (MAX ? 0xFFFFFu - lo : lo)};
-  }
-  __device__ __forceinline__ bool eligible(int k, uint32_t tier) const {
-    const uint32_t m = smeta[k];
-    return ssid[k] != kNone && meta_phase(m) != kServing && (tier == 0 || meta_tier(m) == tier);
-  }
-
-  // Up to three reductions over the slots side by side: argmax over tier ta
-  // (A), argmin over tier tb (B), argmax over tier tc (C).  Each compares its
-  // candidates as a string of 32-bit words, most significant first -- the
-  // packed key's two halves, or a wide key's two halves and then the id -- one
-  // wavefront max / min per word.  The id enters complemented for argmax, so
-  // both directions break ties towards the smaller id, and an id word never
-  // equals the empty value: no candidate leaves it at 0 (argmax) or at
-  // 2^32 - 1 (argmin).
-  template <bool A, bool B, bool C>
-  __device__ __forceinline__ void reduce3(uint32_t ta, uint32_t tb, uint32_t tc, Cand& ra, Cand& rb,
-                                          Cand& rc) const {
-    const int mode = pack_mode();
-    bool aa[SPL], ab[SPL], ac[SPL];
-    uint32_t hi[SPL], lox[SPL], lon[SPL], idx[SPL], idn[SPL];
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) {
-      aa[k] = A && eligible(k, ta);
-      ab[k] = B && eligible(k, tb);
-      ac[k] = C && eligible(k, tc);
-      const uint64_t key = skey[k];
-      const uint32_t sid = ssid[k];
-      idx[k] = ~sid;
-      idn[k] = sid;
-      if (mode == 1) {
-        hi[k] = (uint32_t)key;
-        lox[k] = ~sid;
-        lon[k] = sid;
-      } else if (mode == 2) {
-        uint64_t k44;
-        if constexpr (PT::belady) k44 = key < kCap44 ? key : kCap44;
-        else k44 = key & kCap44;  // recency: key = 2^64 - 1 - last, last below 2^44 - 1
-        hi[k] = (uint32_t)(k44 >> 12);
-        const uint32_t base = (uint32_t)k44 << 20;
-        lox[k] = base | (0xFFFFFu - sid);
-        lon[k] = base | sid;
-      } else {
-        hi[k] = (uint32_t)(key >> 32);
-        lox[k] = (uint32_t)key;
-        lon[k] = (uint32_t)key;
-      }
-    }
-    uint32_t a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0, c0 = 0, c1 = 0, c2 = 0;
-    if (A) a0 = lex_phase<true, true>(hi, aa);
-    if (B) b0 = lex_phase<false, true>(hi, ab);
-    if (C) c0 = lex_phase<true, true>(hi, ac);
-    if (mode) {
-      if (A) a1 = lex_phase<true, false>(lox, aa);
-      if (B) b1 = lex_phase<false, false>(lon, ab);
-      if (C) c1 = lex_phase<true, false>(lox, ac);
-      if (A) ra = unpack<true>(mode, ((uint64_t)a0 << 32) | a1);
-      if (B) rb = unpack<false>(mode, ((uint64_t)b0 << 32) | b1);
-      if (C) rc = unpack<true>(mode, ((uint64_t)c0 << 32) | c1);
-      return;
-    }
-    if (A) a1 = lex_phase<true, true>(lox, aa);
-    if (B) b1 = lex_phase<false, true>(lon, ab);
-    if (C) c1 = lex_phase<true, true>(lox, ac);
-    if (A) a2 = lex_phase<true, false>(idx, aa);
-    if (B) b2 = lex_phase<false, false>(idn, ab);
-    if (C) c2 = lex_phase<true, false>(idx, ac);
-    if (A) ra = Cand{((uint64_t)a0 << 32) | a1, a2 == 0u ? kNone : ~a2};
-    if (B) rb = Cand{((uint64_t)b0 << 32) | b1, b2};
-    if (C) rc = Cand{((uint64_t)c0 << 32) | c1, c2 == 0u ? kNone : ~c2};
-  }
-
-  template <bool MAX>
-  __device__ __forceinline__ Cand select(uint32_t tier, const KeyCtx&) const {
-    Cand r, unused;
-    if constexpr (MAX) reduce3<true, false, false>(tier, 0, 0, r, unused, unused);
-    else reduce3<false, true, false>(0, tier, 0, unused, r, unused);
-    return r;
-  }
-  __device__ __forceinline__ Cand argmax_first(const KeyCtx& K) const { return select<true>(0, K); }
-  __device__ __forceinline__ void select_pd(const KeyCtx&, Cand& p, Cand& d) const {
-    Cand unused;
-    reduce3<false, true, true>(0, kTierHbm, kTierSram, unused, p, d);
-  }
-  __device__ __forceinline__ void scan3(const KeyCtx&, Cand& v, Cand& p, Cand& d) const {
-    reduce3<true, true, true>(0, kTierHbm, kTierSram, v, p, d);
-  }
-
-  // Online hazard table: add the completed session, then rescore every resident.
-  __device__ __forceinline__ bool hazard_open(const KeyCtx& K) const {
-    return uni32(K.hn[0]) < K.online_cap;
-  }
-  __device__ __forceinline__ void hazard_add(const KeyCtx& K, uint32_t Tn) {
-    hazard_add_counts(K, Tn, lane, 64);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int k = 0; k < SPL; ++k)
-      if (ssid[k] != kNone) skey[k] = key_at(ssid[k]);
-    w_sid = kNone;
-  }
-
-  // Smallest evictable resident idle for longer than ttl (timeout: key = 2^64 - 1 - last).
-  __device__ __forceinline__ uint32_t first_idle(uint64_t now, uint64_t ttl) const {
-    const uint64_t thr = idle_threshold(now, ttl);
-    uint32_t c = kNone;
-#pragma unroll
-    for (int k = 0; k < SPL; ++k) {
-      const bool ok = ssid[k] != kNone && meta_phase(smeta[k]) != kServing && (~0ull - skey[k]) < thr;
-      c = ok && ssid[k] < c ? ssid[k] : c;
-    }
-    if (__builtin_amdgcn_ballot_w64(c != kNone) == 0) return kNone;
-    return uni32(reduce_min32<64, 1>(c));
-  }
-};
-
 // One wavefront per simulation for tables too large for LDS.  The session
 // table stays in the workspace; the residents (at most 64 * rows of them,
 // bounded by N_sess, eq. (cap)) sit in LDS slots: slot s holds (key, session
@@ -2292,144 +1590,6 @@ struct WideTable : LaneQueue {
 
 // ------------------------------------------------------------- the engine
 
-struct Scalars {
-  uint64_t used_s, used_h, dma_free_at, prev_t, log_len;
-  uint32_t n_res, n_table, hi;
-  uint64_t hit_s_bytes, hit_h_bytes, miss_tok, prev_s_bytes, prev_h_bytes;
-};
-
-// Counters as kept during a run: event-bounded counts in 32 bits.
-struct Cnt {
-  uint32_t requests, hit_sram, hit_hbm, miss, bypass, evict, expire, promote, swap, tide_passes,
-      events, prefetch_hits, vict_diff, prom_diff;
-  uint64_t dma_bytes, tokens_total, tokens_computed, extra_prefill, score_evals, resident_evals,
-      digest, victim_digest, error;
-  double amat, ttft;
-};
-
-__device__ __forceinline__ Cnt cnt_from(const unison_counters& c) {
-  Cnt k;
-  k.requests = (uint32_t)c.requests;
-  k.hit_sram = (uint32_t)c.hit_sram;
-  k.hit_hbm = (uint32_t)c.hit_hbm;
-  k.miss = (uint32_t)c.miss;
-  k.bypass = (uint32_t)c.bypass;
-  k.evict = (uint32_t)c.evict;
-  k.expire = (uint32_t)c.expire;
-  k.promote = (uint32_t)c.promote;
-  k.swap = (uint32_t)c.swap;
-  k.tide_passes = (uint32_t)c.tide_passes;
-  k.events = (uint32_t)c.events;
-  k.prefetch_hits = (uint32_t)c.prefetch_hits;
-  k.vict_diff = (uint32_t)c.vict_diff;
-  k.prom_diff = (uint32_t)c.prom_diff;
-  k.dma_bytes = c.dma_bytes;
-  k.tokens_total = c.tokens_total;
-  k.tokens_computed = c.tokens_computed;
-  k.extra_prefill = c.extra_prefill_tok;
-  k.score_evals = c.score_evals;
-  k.resident_evals = c.resident_evals;
-  k.digest = c.digest;
-  k.victim_digest = c.victim_digest;
-  k.error = c.error;
-  k.amat = c.amat_sum_ns;
-  k.ttft = c.ttft_sum_ns;
-  return k;
-}
-
-__device__ __forceinline__ unison_counters cnt_to(const Cnt& k) {
-  unison_counters c;
-  c.requests = k.requests;
-  c.hit_sram = k.hit_sram;
-  c.hit_hbm = k.hit_hbm;
-  c.miss = k.miss;
-  c.bypass = k.bypass;
-  c.evict = k.evict;
-  c.expire = k.expire;
-  c.promote = k.promote;
-  c.swap = k.swap;
-  c.dma_bytes = k.dma_bytes;
-  c.tide_passes = k.tide_passes;
-  c.tokens_total = k.tokens_total;
-  c.tokens_computed = k.tokens_computed;
-  c.extra_prefill_tok = k.extra_prefill;
-  c.score_evals = k.score_evals;
-  c.resident_evals = k.resident_evals;
-  c.digest = k.digest;
-  c.victim_digest = k.victim_digest;
-  c.events = k.events;
-  c.error = k.error;
-  c.prefetch_hits = k.prefetch_hits;
-  c.vict_diff = k.vict_diff;
-  c.prom_diff = k.prom_diff;
-  c.amat_sum_ns = k.amat;
-  c.ttft_sum_ns = k.ttft;
-  return c;
-}
-
-__device__ __forceinline__ void pin_vgpr(Scalars& S) {
-  S.used_s = in_vgpr(S.used_s);
-  S.used_h = in_vgpr(S.used_h);
-  S.dma_free_at = in_vgpr(S.dma_free_at);
-  S.prev_t = in_vgpr(S.prev_t);
-  S.log_len = in_vgpr(S.log_len);
-  S.n_res = in_vgpr(S.n_res);
-  S.n_table = in_vgpr(S.n_table);
-  S.hi = in_vgpr(S.hi);
-  S.hit_s_bytes = in_vgpr(S.hit_s_bytes);
-  S.hit_h_bytes = in_vgpr(S.hit_h_bytes);
-  S.miss_tok = in_vgpr(S.miss_tok);
-  S.prev_s_bytes = in_vgpr(S.prev_s_bytes);
-  S.prev_h_bytes = in_vgpr(S.prev_h_bytes);
-}
-
-__device__ __forceinline__ void pin_vgpr(unison_sim_params& p) {
-  p.tide = in_vgpr(p.tide);
-  p.cap_sram_B = in_vgpr(p.cap_sram_B);
-  p.cap_hbm_B = in_vgpr(p.cap_hbm_B);
-  p.n_slots = in_vgpr(p.n_slots);
-  p.dma_B_per_us = in_vgpr(p.dma_B_per_us);
-  p.ttl_ns = in_vgpr(p.ttl_ns);
-  p.b_g = in_vgpr(p.b_g);
-  p.tau_ns = in_vgpr(p.tau_ns);
-}
-
-__device__ __forceinline__ void pin_vgpr(Cnt& k) {
-  k.requests = in_vgpr(k.requests);
-  k.hit_sram = in_vgpr(k.hit_sram);
-  k.hit_hbm = in_vgpr(k.hit_hbm);
-  k.miss = in_vgpr(k.miss);
-  k.bypass = in_vgpr(k.bypass);
-  k.evict = in_vgpr(k.evict);
-  k.expire = in_vgpr(k.expire);
-  k.promote = in_vgpr(k.promote);
-  k.swap = in_vgpr(k.swap);
-  k.tide_passes = in_vgpr(k.tide_passes);
-  k.events = in_vgpr(k.events);
-  k.prefetch_hits = in_vgpr(k.prefetch_hits);
-  k.vict_diff = in_vgpr(k.vict_diff);
-  k.prom_diff = in_vgpr(k.prom_diff);
-  k.dma_bytes = in_vgpr(k.dma_bytes);
-  k.tokens_total = in_vgpr(k.tokens_total);
-  k.tokens_computed = in_vgpr(k.tokens_computed);
-  k.extra_prefill = in_vgpr(k.extra_prefill);
-  k.score_evals = in_vgpr(k.score_evals);
-  k.resident_evals = in_vgpr(k.resident_evals);
-  k.digest = in_vgpr(k.digest);
-  k.victim_digest = in_vgpr(k.victim_digest);
-  k.error = in_vgpr(k.error);
-  k.amat = in_vgpr(k.amat);
-  k.ttft = in_vgpr(k.ttft);
-}
-
-struct LogSink {
-  bool on;             // logging requested (a launch-wide, uniform flag)
-  unison_record* rec;  // this simulation's records
-  uint32_t cap;
-  bool lead;           // the one lane that stores records
-  bool victims;        // also record each event's scan result
-};
-
 template <class Tab>
 __device__ __forceinline__ void emit(Tab& T, Cnt& C, Scalars& S, const LogSink& L, uint32_t ev,
                                      uint32_t op, uint32_t a, uint32_t b) {
@@ -2792,88 +1952,6 @@ __device__ __forceinline__ void run_events(Tab& T, const unison_sim_params& P, c
   if (stops) C.error = bad_at + 1;
 }
 
-// The simulation's hazard table into LDS: the counts of its fixed table, or
-// of its online table so far (none on a fresh run), and h in both forms.
-__device__ __forceinline__ void load_hazard(const SimArgs& a, const unison_sim_params& P,
-                                            uint32_t sim, const KeyCtx& K, uint32_t lane,
-                                            uint32_t width) {
-  const bool online = P.hazard_online != 0;
-  const bool fresh = online && !(a.flags & UNISON_RUN_CONTINUE);
-  const uint32_t* kd = online ? a.hcount + (size_t)sim * 2 * kLut : a.lut_d + (size_t)P.lut * kLut;
-  const uint32_t* kn = online ? kd + kLut : a.lut_n + (size_t)P.lut * kLut;
-  for (uint32_t t = lane; t < kLut; t += width) {
-    const uint32_t d = fresh ? 0u : kd[t];
-    const uint32_t n = fresh ? 0u : kn[t];
-    K.hd[t] = d;
-    K.hn[t] = n;
-    K.hf[t] = hazard_f32(d, n);
-    K.hq[t] = hazard_q(d, n, K.lambda);
-  }
-}
-
-// An online table's counts at the end of the launch, for a later CONTINUE
-// and for unison_read_hazard (a fixed table never changes: nothing to store).
-__device__ __forceinline__ void store_hazard(const SimArgs& a, const unison_sim_params& P,
-                                             uint32_t sim, const KeyCtx& K, uint32_t lane,
-                                             uint32_t width) {
-  if (!P.hazard_online) return;
-  uint32_t* out = a.hcount + (size_t)sim * 2 * kLut;
-  for (uint32_t t = lane; t < kLut; t += width) {
-    out[t] = K.hd[t];
-    out[kLut + t] = K.hn[t];
-  }
-}
-
-__device__ __forceinline__ void load_scalars(const SimState& st, Scalars& S) {
-  S.used_s = st.used_s;
-  S.used_h = st.used_h;
-  S.dma_free_at = st.dma_free_at;
-  S.prev_t = st.prev_t;
-  S.log_len = st.log_len;
-  S.n_res = st.n_res;
-  S.n_table = st.n_table;
-  S.hi = st.hi;
-  S.hit_s_bytes = st.hit_s_bytes;
-  S.hit_h_bytes = st.hit_h_bytes;
-  S.miss_tok = st.miss_tok;
-  S.prev_s_bytes = st.prev_s_bytes;
-  S.prev_h_bytes = st.prev_h_bytes;
-}
-
-__device__ __forceinline__ void store_scalars(SimState& st, const Scalars& S, uint64_t next_event) {
-  st.next_event = next_event;
-  st.used_s = S.used_s;
-  st.used_h = S.used_h;
-  st.dma_free_at = S.dma_free_at;
-  st.prev_t = S.prev_t;
-  st.log_len = S.log_len;
-  st.n_res = S.n_res;
-  st.n_table = S.n_table;
-  st.hi = S.hi;
-  st.hit_s_bytes = S.hit_s_bytes;
-  st.hit_h_bytes = S.hit_h_bytes;
-  st.miss_tok = S.miss_tok;
-  st.prev_s_bytes = S.prev_s_bytes;
-  st.prev_h_bytes = S.prev_h_bytes;
-}
-
-// eq. (hr-amat) sums from the exact integer totals, rounded once: the same
-// quantities the per-request f64 sums approximate.
-__device__ __forceinline__ void finish_costs(const Scalars& S, const unison_sim_params& P, Cnt& C) {
-  const double a = (double)S.hit_s_bytes * P.t_s_ns_per_B;
-  const double b = (double)S.hit_h_bytes * P.t_h_ns_per_B;
-  const double c = (double)S.miss_tok * P.t_p_ns_per_tok;
-  C.amat = (a + b) + c;
-  const double d = (double)S.prev_s_bytes * P.t_s_ns_per_B;
-  const double f = (double)S.prev_h_bytes * P.t_h_ns_per_B;
-  const double h = (double)C.tokens_computed * P.t_p_ns_per_tok;
-  C.ttft = (d + f) + h;
-}
-
-__device__ __forceinline__ uint32_t sim_policy(const SimArgs& a, const unison_sim_params& P) {
-  return a.policy_override == UNISON_POLICY_PARAMS ? P.policy : a.policy_override;
-}
-
 // ------------------------------------------------- register-table kernels
 
 template <int G, int EPL, uint32_t POL, uint32_t SMODE>
@@ -3163,144 +2241,6 @@ __global__ __launch_bounds__(BLOCK) void sim_block_kernel(SimArgs a) {
   }
 }
 
-// ------------------------------------------------- slot-table kernel
-
-// One wavefront per simulation: the table in LDS, the residents in SPL VGPR
-// slots per lane (SlotTable), events 64 to a window.
-template <int SPL, uint32_t POL, uint32_t SMODE>
-__device__ __forceinline__ void slot_run(const SimArgs& a, uint32_t sim, const unison_sim_params& P,
-                                         const KeyCtx& K, uint64_t* s_tab) {
-  const uint32_t lane = threadIdx.x;
-  const uint64_t eb = a.ev_off[P.trace], ee = a.ev_off[P.trace + 1];
-  const uint64_t sb = a.sess_off[P.trace];
-  const uint32_t n_sess = (uint32_t)(a.sess_off[P.trace + 1] - sb);
-  const TraceView tr{a.ev_t + eb, a.ev_sid + eb, a.ev_info + eb, a.ev_len + eb, a.ev_next + eb,
-                     a.ev_tool ? a.ev_tool + eb : nullptr, ee - eb, n_sess};
-  const size_t tb = (size_t)sim * a.max_sessions;
-  const bool cont = (a.flags & UNISON_RUN_CONTINUE) != 0;
-
-  SlotTable<SPL, POL, SMODE> T;
-  const uint32_t n = n_sess;
-  T.mg = s_tab;
-  T.last = s_tab + n;
-  T.gq = s_tab + 2 * (size_t)n;
-  T.next = s_tab + 3 * (size_t)n;
-  uint32_t* s32 = reinterpret_cast<uint32_t*>(s_tab + 4 * (size_t)n);
-  T.len = s32;
-  T.kvb = s32 + n;
-  T.lane = lane;
-  T.kc = K;
-  T.w_sid = kNone;
-  T.w_key = 0;
-  T.w_kvb = 0;
-  T.w_len = 0;
-  T.queue_init();
-#pragma unroll
-  for (int k = 0; k < SPL; ++k) {
-    T.ssid[k] = kNone;
-    T.smeta[k] = 0;
-    T.skey[k] = 0;
-    T.ssize[k] = 0;
-  }
-  for (uint32_t i = lane; i < n; i += 64) {
-    T.mg[i] = cont ? a.t_mg[tb + i] : 0ull;
-    T.last[i] = cont ? a.t_last[tb + i] : 0ull;
-    T.gq[i] = cont ? a.t_gq[tb + i] : 0ull;
-    T.next[i] = cont ? a.t_next[tb + i] : ~0ull;
-    T.len[i] = cont ? a.t_len[tb + i] : 0u;
-    T.kvb[i] = a.sess_kvb[sb + i];
-  }
-  __syncthreads();
-  // a resumed table's residents take slots
-  if (cont) {
-    for (uint32_t base = 0; base < n; base += 64) {
-      const uint32_t i = base + lane;
-      const uint32_t ic = i < n ? i : 0u;  // lanes past the table read entry 0
-      const bool res = i < n && meta_tier((uint32_t)T.mg[ic]) != kTierNone;
-      const uint64_t key = T.key_at(ic);
-      const uint64_t size = (uint64_t)T.len[ic] * T.kvb[ic];
-      const uint32_t m = (uint32_t)T.mg[ic];
-      for (uint64_t bits = __builtin_amdgcn_ballot_w64(res); bits; bits &= bits - 1u) {
-        const int l = __builtin_ctzll(bits);
-        T.insert(base + (uint32_t)l, (uint32_t)__builtin_amdgcn_readlane((int)m, l),
-                 WindowReader<false, false>::lane64(key, l), WindowReader<false, false>::lane64(size, l));
-      }
-    }
-  }
-
-  Scalars S;
-  Cnt C;
-  uint64_t next_event = 0;
-  if (cont) {
-    load_scalars(a.state[sim], S);
-    C = cnt_from(a.counters[sim]);
-    next_event = a.state[sim].next_event;
-  } else {
-    S = Scalars{};
-    C = cnt_from(unison_counters{});
-  }
-  if (S.hi > n_sess) S.hi = n_sess;
-  // residents never exceed min(N_sess, sessions): the launcher picks a kernel that holds them
-  const uint64_t max_res = P.n_slots < n_sess ? P.n_slots : n_sess;
-  if (P.dual_sync || max_res > 64u * SPL) C.error = ~0ull;
-  pin_vgpr(S);
-  pin_vgpr(C);
-  const bool log_on = (a.flags & UNISON_RUN_LOG) && a.log_cap;
-  const LogSink L{log_on, log_on ? a.log + (size_t)sim * a.log_cap : nullptr, a.log_cap, lane == 0,
-                  log_on && (a.flags & UNISON_RUN_LOG_VICTIM) != 0};
-  if (C.error == 0) {
-    unison_sim_params Pv = P;
-    pin_vgpr(Pv);
-    run_events<POL, SMODE, true>(T, Pv, K, tr, S, C, L, next_event, a.max_events,
-                                 a.first_bad[P.trace]);
-    uint64_t dg, vd;
-    T.drain(dg, vd);
-    C.digest += dg;
-    C.victim_digest += vd;
-  }
-  __syncthreads();
-  for (uint32_t i = lane; i < n; i += 64) {
-    a.t_mg[tb + i] = T.mg[i];
-    a.t_last[tb + i] = T.last[i];
-    a.t_gq[tb + i] = T.gq[i];
-    a.t_next[tb + i] = T.next[i];
-    a.t_len[tb + i] = T.len[i];
-  }
-  store_hazard(a, P, sim, K, lane, 64);
-  if (lane == 0) {
-    finish_costs(S, P, C);
-    store_scalars(a.state[sim], S, next_event);
-    a.counters[sim] = cnt_to(C);
-  }
-}
-
-template <int SPL>
-__global__ __launch_bounds__(64) void sim_slot_kernel(SimArgs a) {
-  __shared__ float s_hf[52];
-  __shared__ uint32_t s_hq[52];
-  __shared__ uint32_t s_hd[52];
-  __shared__ uint32_t s_hn[52];
-  extern __shared__ uint64_t s_tab[];
-  const uint32_t sim = blockIdx.x;
-  const unison_sim_params P = a.params[sim];
-  const uint32_t lambda = (1u << P.b_h) - 1u;
-  const KeyCtx K{s_hf, s_hq, s_hd, s_hn, P.penalty_us, lambda, P.p_z, a.time44 != 0,
-                 P.hazard_online ? P.online_sessions : 0u, a.eta + (size_t)P.trace * kEtaClasses,
-                 P.recip_bits};
-  load_hazard(a, P, sim, K, threadIdx.x, 64);
-  __syncthreads();
-  switch (sim_policy(a, P)) {
-    case kSpear:
-      if (P.score_mode) slot_run<SPL, kSpear, 1>(a, sim, P, K, s_tab);
-      else slot_run<SPL, kSpear, 0>(a, sim, P, K, s_tab);
-      break;
-    case kLru: slot_run<SPL, kLru, 0>(a, sim, P, K, s_tab); break;
-    case kTimeout: slot_run<SPL, kTimeout, 0>(a, sim, P, K, s_tab); break;
-    case kBelady: slot_run<SPL, kBelady, 0>(a, sim, P, K, s_tab); break;
-    default: slot_run<SPL, kEta, 0>(a, sim, P, K, s_tab); break;
-  }
-}
-
 // ------------------------------------------------- wide-table kernel
 
 // One wavefront per simulation: the table in the workspace, the residents in
@@ -3564,8 +2504,8 @@ constexpr int kBlock = 256;
 constexpr int kLdsVariant = 9;
 constexpr int kLdsWaveVariant = 12;  // the table in LDS, one wavefront per simulation
 constexpr int kDualVariant = 11;  // streamed, 512 threads, with the dual design's copies
-constexpr int kSlotVariant = 13;  // the table in LDS, residents in VGPR slots, one wavefront
-constexpr uint64_t kSlotMaxResidents = 512;  // 8 slots per lane
+constexpr int kLaneVariant = kLaneKernel;  // residents sorted across one wavefront's lanes (lane.hip)
+constexpr uint64_t kLaneMaxResidents = 512;  // 8 per lane
 constexpr int kWideVariant = 14;  // the table in the workspace, residents in LDS slots, one wavefront
 constexpr uint64_t kWideMaxResidents = 4096;  // 96 KiB of slots
 constexpr uint32_t kLdsBytesPerSession = 4 * 8 + 2 * 4;  // mg, last, gq, next; len, kvb
@@ -3596,8 +2536,7 @@ static uint32_t block_of(int v) { return v == 10 || v == kDualVariant ? 512u : (
 uint32_t sim_variant_capacity(int v) {
   if (v < 0 || v >= kNumVariants) return 0;
   const uint32_t lim = lds_limit();
-  if (v == kSlotVariant) return lim / kLdsBytesPerSession;  // the table alone
-  if (v == kWideVariant) return UNISON_MAX_SESSIONS;  // the table stays in the workspace
+  if (v == kLaneVariant || v == kWideVariant) return UNISON_MAX_SESSIONS;  // the table stays in the workspace
   if (v == kLdsVariant || v == kLdsWaveVariant) {
     // the table and its residency bits
     uint32_t n = lim / kLdsBytesPerSession;
@@ -3621,16 +2560,19 @@ uint32_t sim_variant_lanes(int v) {
   return (uint32_t)kVariants[v].g;
 }
 
-// Measured on 4,096-simulation batches: register tables win up to 256
-// sessions (32 x 8 takes half the LDS table's time there), the LDS table up
-// to its capacity (one wavefront per simulation, which needs no workgroup
-// barriers: C2 163 vs 169 ms with 256 threads), then the 512-thread streamed
-// table.
+// By the largest trace and the largest resident count of the batch (a batch
+// of small tables with few simulations then moves to the lane kernel, see
+// kLaneSims).  Measured, each kernel against the next: the lane kernel takes a
+// third to a half of the register tables' time from 17 sessions on (4,096
+// simulations of 64 and 200 sessions 0.64 and 2.1 ms against 1.35 and 13.9;
+// 16,384 of 40 sessions 2.0 against 3.1) and, with up to 512 residents, 0.2
+// to 0.67 of the LDS table's (the paper-scale trace at 64 and 512 slots 32
+// and 112 ms against 161 and 167).  Above that the LDS table up to its
+// capacity (one wavefront per simulation), then the wide-table kernel, then
+// the 512-thread streamed table.
 int sim_auto_variant(uint32_t max_sess, uint64_t max_slots) {
   if (max_sess <= 16) return 5;
-  if (max_sess <= 64) return 7;
-  if (max_sess <= 256) return 8;
-  if (max_sess <= sim_variant_capacity(kSlotVariant) && max_slots <= 256) return kSlotVariant;
+  if (max_slots <= kLaneMaxResidents) return kLaneVariant;
   if (max_sess <= sim_variant_capacity(kLdsWaveVariant)) return kLdsWaveVariant;
   if (max_slots <= kWideMaxResidents) return kWideVariant;
   return 10;
@@ -3638,7 +2580,7 @@ int sim_auto_variant(uint32_t max_sess, uint64_t max_slots) {
 
 // Largest N_sess a variant holds (UNISON_MAX_SESSIONS: no limit of its own).
 uint64_t sim_variant_max_slots(int v) {
-  if (v == kSlotVariant) return kSlotMaxResidents;
+  if (v == kLaneVariant) return kLaneMaxResidents;
   if (v == kWideVariant) return kWideMaxResidents;
   return UNISON_MAX_SESSIONS;
 }
@@ -3672,24 +2614,12 @@ static void launch_regs(const SimArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL((sim_regs_kernel<G, EPL>), dim3(blocks), dim3(256), 0, stream, a);
 }
 
-template <int SPL>
-static void launch_slots(const SimArgs& a, uint32_t max_sess_in_batch, hipStream_t stream) {
-  const uint32_t n = max_sess_in_batch ? max_sess_in_batch : 1;
-  hipLaunchKernelGGL((sim_slot_kernel<SPL>), dim3(a.n_sims), dim3(64), (size_t)n * kLdsBytesPerSession,
-                     stream, a);
-}
-
 hipError_t launch_sim(const SimArgs& a, uint32_t max_sess_in_batch, uint64_t max_slots,
                       hipStream_t stream, int force_variant, int force_cache_slots) {
   const int v = force_variant >= 0 ? force_variant : sim_auto_variant(max_sess_in_batch, max_slots);
   switch (v) {
-    case kSlotVariant:
-      if (max_slots <= 64) launch_slots<1>(a, max_sess_in_batch, stream);
-      else if (max_slots <= 128) launch_slots<2>(a, max_sess_in_batch, stream);
-      else if (max_slots <= 256) launch_slots<4>(a, max_sess_in_batch, stream);
-      else if (max_slots <= kSlotMaxResidents) launch_slots<8>(a, max_sess_in_batch, stream);
-      else return hipErrorInvalidValue;
-      break;
+    case kLaneVariant:
+      return launch_lanes(a, max_slots, stream);
     case kWideVariant: {
       if (max_slots > kWideMaxResidents) return hipErrorInvalidValue;
       const uint32_t cap = (uint32_t)((max_slots ? max_slots : 1) + 63) / 64u * 64u;

@@ -234,6 +234,17 @@ struct SimArgs {
   uint32_t n_slots;        // lane groups the register-table grid covers
 };
 
+// The kernel that sorts the residents across one wavefront's lanes, and up to
+// how many simulations it also takes batches of tables of 16 sessions or fewer
+// from the register tables.  Up to 4,096 wavefronts (four per SIMD) are
+// resident together and their chains hide each other's latency: 16-session
+// traces under four policies take 97, 118 and 167 us at 512, 2,048 and 4,096
+// simulations against 210, 218 and 215 in register tables; past that a second
+// round of wavefronts starts (8,192: 308 us), while the register tables, eight
+// simulations to a wavefront, still fit one (220 us).
+constexpr int kLaneKernel = 13;
+constexpr uint32_t kLaneSims = 4096;
+
 // Most lane groups of a wavefront (the 4-lane register table's 16).
 constexpr uint32_t kMaxGroupsPerWave = 16;
 
