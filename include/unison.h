@@ -292,8 +292,9 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params);
  * under the parameter row and policy it ran with (state a policy never
  * reads, such as the gap EMA of LRU or timeout without TIDE, is not kept).
  * policy_override is a UNISON_POLICY_* value applied to all simulations, or
- * UNISON_POLICY_PARAMS.  A batch with a dual-design row runs on the copies'
- * kernel (variant 11).  While no simulation can hold more than 512 residents
+ * UNISON_POLICY_PARAMS.  A batch with a dual-design row runs on variant 13
+ * while no simulation can hold more than 512 residents and no dual row has
+ * hazard_online set, else on the copies' streamed kernel (variant 11).  While no simulation can hold more than 512 residents
  * (min(N_sess, sessions)) a batch runs on one wavefront per simulation with
  * the residents sorted across its lanes (variant 13), except that tables of at
  * most 16 sessions take eight simulations to a wavefront above 4,096
@@ -378,8 +379,8 @@ int unison_read_hazard(unison_ctx* ctx, uint32_t sim, uint32_t* d_out, uint32_t*
  * 8: 32 x 8 (6 is retired); one workgroup per simulation with the table 3:
  * streamed from the workspace by 256 threads, 10: by 512 threads, 9: held in
  * LDS (256 threads), 12: held in LDS by one wavefront, 11: streamed by 512
- * threads with the dual design's copies -- the only variant for a batch with
- * a dual-design row; one wavefront per simulation with 13: the table in the
+ * threads with the dual design's copies -- the only one that may be pinned for a
+ * batch with a dual-design row; one wavefront per simulation with 13: the table in the
  * workspace and the residents sorted across the lanes, 1 to 8 per lane (at most
  * 512 residents), 14: the table in the workspace and the residents in LDS slots
  * (at most 4,096 residents)).  A variant too small for the traces or their

@@ -179,6 +179,7 @@ struct unison_ctx {
   bool traces_loaded = false, params_set = false, ran = false;
   bool time44 = false;  // every trace time is below 2^44 - 1 ns
   bool dual = false;    // some row uses the dual register-file design
+  bool dual_lanes = false;  // and none of those rebuilds its hazard table online
   uint32_t max_sess_batch = 0;
   uint64_t max_slots_batch = 0;  // largest N_sess of the parameter rows
   int force_variant = -1;
@@ -472,7 +473,11 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
   }
   ctx->h_params.assign(params, params + ctx->dims.n_sims);
   ctx->dual = false;
-  for (uint32_t i = 0; i < ctx->dims.n_sims; ++i) ctx->dual = ctx->dual || params[i].dual_sync != 0;
+  ctx->dual_lanes = true;
+  for (uint32_t i = 0; i < ctx->dims.n_sims; ++i) {
+    ctx->dual = ctx->dual || params[i].dual_sync != 0;
+    if (params[i].dual_sync && params[i].hazard_online) ctx->dual_lanes = false;
+  }
   int rc = ctx->hip(hipMemcpyAsync(ctx->at<unison_sim_params>(ctx->L.params), ctx->h_params.data(),
                                    sizeof(unison_sim_params) * ctx->dims.n_sims,
                                    hipMemcpyHostToDevice, ctx->stream),
@@ -590,11 +595,18 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
   a.flags = flags;
   a.policy_override = policy_override;
   a.time44 = ctx->time44 ? 1u : 0u;
+  a.dual = ctx->dual ? 1u : 0u;
   int v = ctx->force_variant;
-  // the dual design's copies live in the workspace: its streamed-table kernel runs it
+  // The dual design's copies live in the workspace: the lane kernel keeps them
+  // while its residents fit and no dual row's table grows online (its copies'
+  // keys would have to be recomputed from fields it does not hold), else the
+  // streamed-table kernel does.  24 simulations of the dual study: 12.5 ms
+  // against 94.
   if (ctx->dual) {
-    if (v < 0) v = 11;
-    if (v != 11)
+    if (v < 0 && !(ctx->dual_lanes && std::min<uint64_t>(ctx->max_slots_batch, ctx->max_sess_batch) <=
+                                          sim_variant_max_slots(kLaneKernel)))
+      v = 11;
+    if (v >= 0 && v != 11)
       return ctx->fail(UNISON_E_INVALID, "dual register files run on variant 11, not %d", v);
   }
   if (v >= 0 && (sim_variant_capacity(v) == 0 || sim_variant_capacity(v) < ctx->max_sess_batch))
@@ -607,7 +619,7 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
                      (unsigned long long)sim_variant_max_slots(v), (unsigned long long)max_res);
   if (v < 0) {
     v = sim_auto_variant(ctx->max_sess_batch, max_res);
-    if (sim_variant_lanes(v) && a.n_sims <= kLaneSims) v = kLaneKernel;
+    if (ctx->dual || (sim_variant_lanes(v) && a.n_sims <= kLaneSims)) v = kLaneKernel;
     if (sim_variant_capacity(v) < ctx->max_sess_batch)
       return ctx->fail(UNISON_E_CAPACITY, "%u sessions exceed every kernel variant (largest %u)",
                        ctx->max_sess_batch, sim_variant_capacity(v));

@@ -144,7 +144,7 @@ enum : uint32_t {
   kCMg = 0, kCGq = 2, kCLast = 4, kCNext = 6, kCLen = 8, kCKvb = 10, kCEvT = 12, kCEvNext = 14,
   kCEvSid = 16, kCEvInfo = 18, kCEvLen = 20, kCEvTool = 22, kCEta = 24, kCLog = 26, kCDma = 28,
   kCDmaInv = 30, kCTau = 32, kCTtl = 34, kCPz = 36, kCEnd = 38, kCLambda = 40, kCRecip, kCP, kCBg,
-  kCLogCap, kCIdBits, kCHasTool
+  kCLogCap, kCIdBits, kCHasTool, kCDual, kCView = 48, kCStride = 50, kCSync = 52, kCReq = 54
 };
 
 // Queued records: the chain stops for a flush once kQueueFlush are waiting,
@@ -177,48 +177,23 @@ struct TabRegs {
   uint64_t mg, gq, last;
   uint32_t len, kvb;
 };
+// The dual design's copies of them, the index of the session's latest event
+// and the live table's next arrival.
+struct CopyRegs {
+  uint64_t gq, last, next, seen, live_next;
+  float g;
+  uint32_t turn;
+  bool done;
+};
 
 // An event's word in the chain: its session (below 2^20) and flags.
 constexpr uint32_t kWNewBit = 25;
 constexpr uint32_t kWArrive = 1u << 24, kWNew = 1u << kWNewBit, kWOnset = 1u << 26, kWBig = 1u << 27;
 static_assert(UNISON_MAX_SESSIONS <= (1u << 20), "session ids take 20 bits");
 
-template <int SPL, uint32_t POL, uint32_t SMODE>
-struct LaneSim {
-  using PT = Pol<POL, SMODE>;
-  // fp32 scores are 32-bit keys; integer scores and times take 64 bits
-  using KT = typename std::conditional<PT::spear && !PT::fixed, uint32_t, uint64_t>::type;
-  static constexpr uint32_t kSram = 1u, kPref = 2u;  // slot flags
-  static_assert(kTierSram == 1 && kTierHbm == 2, "a tier's low bit is the SRAM flag");
-  // an order entry: session << 11 | slot << 2 | completed << 1 | in SRAM
-  static constexpr uint32_t kSidShift = 11, kDoneB = 2u;
-  static constexpr bool kGapEma = PT::spear || PT::belady;  // others read it for TIDE only
-
-  uint32_t lane;
-  // Residents in victim order (larger key first, ties to the smaller id): the
-  // key, and the entry complemented, so that an empty position is 0 in both
-  // and sorts last.
-  KT skey[SPL];
-  uint32_t snot[SPL];
-  // slots: every resident, also while it is served
-  uint32_t ssid[SPL], sfl[SPL];
-  uint64_t ssz[SPL];
-  // online tables: what a resident's key is recomputed from
-  uint32_t sturn[SPL];
-  uint64_t sema[SPL];
-
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int j = 0; j < SPL; ++j) {
-      skey[j] = 0;
-      snot[j] = 0;
-      ssid[j] = kNone;
-      sfl[j] = 0;
-      ssz[j] = 0;
-      sturn[j] = 0;
-      sema[j] = 0;
-    }
-  }
+// Values spread over a wavefront: index i sits in lane i % 64 of register i / 64.
+template <int SPL>
+struct Spread {
   template <class T>
   __device__ __forceinline__ static T get(const T (&a)[SPL], uint32_t i) {
     T v = rl(a[0], i & 63u);
@@ -242,12 +217,31 @@ struct LaneSim {
     if constexpr (SPL == 1) return l;
     else return l == kNone ? other : (uint32_t)j * 64u + l;
   }
-  // The slot of resident sid, or kNone.
-  __device__ __forceinline__ uint32_t slot_of(uint32_t sid) const {
-    uint32_t s = kNone;
+};
+
+// An order entry: session << 11 | slot << 2 | completed << 1 | in SRAM.
+constexpr uint32_t kSidShift = 11, kDoneB = 2u, kSram = 1u;
+static_assert(kTierSram == 1 && kTierHbm == 2, "a tier's low bit is the SRAM flag");
+
+// Evictable residents in victim order (larger key first, ties to the smaller
+// id): the key, and the entry complemented, so that an empty position is 0 in
+// both and sorts last.
+template <int SPL, class KT>
+struct Order : Spread<SPL> {
+  using Spread<SPL>::get;
+  using Spread<SPL>::set;
+  using Spread<SPL>::at;
+  uint32_t lane;
+  KT skey[SPL];
+  uint32_t snot[SPL];
+
+  __device__ __forceinline__ void init(uint32_t l) {
+    lane = l;
 #pragma unroll
-    for (int j = SPL - 1; j >= 0; --j) s = at(first_set(ballot(ssid[j] == sid)), j, s);
-    return s;
+    for (int j = 0; j < SPL; ++j) {
+      skey[j] = 0;
+      snot[j] = 0;
+    }
   }
   // The position of a resident that is in the order.
   __device__ __forceinline__ uint32_t pos_of(uint32_t sid) const {
@@ -330,6 +324,87 @@ struct LaneSim {
       p = at(first_set(ballot(snot[j] != 0u) & ~hbm(j)), j, p);
     return p;
   }
+  // The session of an order entry; kNone for the empty one.
+  __device__ __forceinline__ static uint32_t sid_of(uint32_t x) {
+    return (uint32_t)((int)x >> kSidShift);
+  }
+};
+
+// DUAL: the dual register-file design, eq. (rf), eq. (stale): both engines
+// decide from copies of the key fields that are refreshed together, so one
+// order by the copies' keys serves both; the live order beside it tells which
+// decisions the unified file would have taken differently.
+template <int SPL, uint32_t POL, uint32_t SMODE, bool DUAL>
+struct LaneSim : Spread<SPL> {
+  using Spread<SPL>::get;
+  using Spread<SPL>::set;
+  using Spread<SPL>::at;
+  using PT = Pol<POL, SMODE>;
+  // fp32 scores are 32-bit keys; integer scores and times take 64 bits
+  using KT = typename std::conditional<PT::spear && !PT::fixed, uint32_t, uint64_t>::type;
+  static constexpr uint32_t kPref = 2u;         // slot flags: kSram and this
+  static constexpr bool kGapEma = PT::spear || PT::belady;  // others read it for TIDE only
+
+  uint32_t lane;
+  Order<SPL, KT> live;
+  Order<SPL, KT> copy;   // DUAL only
+  // slots: every resident, also while it is served
+  uint32_t ssid[SPL], sfl[SPL];
+  uint64_t ssz[SPL];
+  // online tables: what a resident's key is recomputed from
+  uint32_t sturn[SPL];
+  uint64_t sema[SPL];
+
+  __device__ __forceinline__ void init() {
+    live.init(lane);
+    copy.init(lane);
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      ssid[j] = kNone;
+      sfl[j] = 0;
+      ssz[j] = 0;
+      sturn[j] = 0;
+      sema[j] = 0;
+    }
+  }
+  // The order the engines decide by.
+  __device__ __forceinline__ Order<SPL, KT>& order() {
+    if constexpr (DUAL) return copy;
+    else return live;
+  }
+  __device__ __forceinline__ void insert(KT key, KT copy_key, uint32_t x) {
+    live.insert(key, x);
+    if constexpr (DUAL) copy.insert(copy_key, x);
+  }
+  __device__ __forceinline__ void remove(uint32_t sid) {
+    live.remove_at(live.pos_of(sid));
+    if constexpr (DUAL) copy.remove_at(copy.pos_of(sid));
+  }
+  // The front of the deciding order, session sid, leaves.
+  __device__ __forceinline__ void pop_front(uint32_t sid) {
+    order().pop_front();
+    if constexpr (DUAL) live.remove_at(live.pos_of(sid));
+  }
+  // The entry at position p of the deciding order changes from x to y.
+  __device__ __forceinline__ void change(uint32_t p, uint32_t x, uint32_t y) {
+    set(order().snot, p, ~y);
+    if constexpr (DUAL) set(live.snot, live.pos_of(x >> kSidShift), ~y);
+  }
+  // The copies are refreshed.
+  __device__ __forceinline__ void sync() {
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      copy.skey[j] = live.skey[j];
+      copy.snot[j] = live.snot[j];
+    }
+  }
+  // The slot of resident sid, or kNone.
+  __device__ __forceinline__ uint32_t slot_of(uint32_t sid) const {
+    uint32_t s = kNone;
+#pragma unroll
+    for (int j = SPL - 1; j >= 0; --j) s = at(first_set(ballot(ssid[j] == sid)), j, s);
+    return s;
+  }
   // The slot a new resident takes (residents never exceed 64 SPL).
   __device__ __forceinline__ uint32_t free_slot() const {
     uint32_t s = 0;
@@ -338,10 +413,6 @@ struct LaneSim {
     return s;
   }
 
-  // The session of an order entry; kNone for the empty one.
-  __device__ __forceinline__ static uint32_t sid_of(uint32_t x) {
-    return (uint32_t)((int)x >> kSidShift);
-  }
   // A key in the form the order compares.
   __device__ __forceinline__ static KT key_from(const KeyCtx& K, bool done, uint32_t turn, float g,
                                                 uint64_t gq, uint64_t t, uint64_t next) {
@@ -360,17 +431,17 @@ struct LaneSim {
       uint32_t nn[SPL], rank[SPL], n = 0;
 #pragma unroll
       for (int j = 0; j < SPL; ++j) {
-        const uint32_t x = ~snot[j], s = slot_in(x);
+        const uint32_t x = ~live.snot[j], s = live.slot_in(x);
         KT v = 0;
 #pragma unroll
         for (int i = 0; i < SPL; ++i) {
           const KT o = (KT)__shfl((unsigned long long)fresh[i], (int)(s & 63u));
           v = (s >> 6) == (uint32_t)i ? o : v;
         }
-        const bool in = snot[j] != 0u;
+        const bool in = live.snot[j] != 0u;
         n += pop64(ballot(in));
         nk[j] = !in ? (KT)0 : (x & kDoneB) ? (KT)PT::inf_key : v;
-        nn[j] = snot[j];
+        nn[j] = live.snot[j];
         rank[j] = 0;
       }
       for (uint32_t i = 0; i < n; ++i) {
@@ -382,8 +453,8 @@ struct LaneSim {
       }
       for (uint32_t i = 0; i < n; ++i) {
         const uint32_t r = get(rank, i);
-        set(skey, r, get(nk, i));
-        set(snot, r, get(nn, i));
+        set(live.skey, r, get(nk, i));
+        set(live.snot, r, get(nn, i));
       }
     }
   }
@@ -395,26 +466,28 @@ enum : uint32_t { kSTok, kSComp, kSExtra, kSMiss, kSHitS, kSPrevS, kSHitH, kSPre
 
 // The pool's scalars, and what a launch adds to a simulation's counters.
 struct Pool {
-  uint64_t used_s, used_h, dma_free, log_len;
+  uint64_t used_s, used_h, dma_free, log_len, requests, last_sync;
   uint32_t n_res, n_table;
 };
 struct Totals {
   uint64_t hit_s, hit_h, miss_tok, prev_s, prev_h, dma_bytes, tok, comp, extra, evals, res_evals,
       digest, victim_digest;
-  uint32_t hi, req, n_hs, n_hh, n_pf, n_byp, n_evict, n_exp, n_pro, n_swap, passes;
+  uint32_t hi, req, n_hs, n_hh, n_pf, n_byp, n_evict, n_exp, n_pro, n_swap, passes, vict_diff,
+      prom_diff;
 };
 
 // Events [e_io, end) of one simulation.
-template <int SPL, uint32_t POL, uint32_t SMODE>
+template <int SPL, uint32_t POL, uint32_t SMODE, bool DUAL>
 __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_params& P,
                                             const KeyCtx& K, const TraceView& tr, size_t tb,
-                                            const uint32_t* kvb_of, uint2* queue, uint64_t* sums,
-                                            LaneSim<SPL, POL, SMODE>& T,
+                                            const uint32_t* kvb_of, uint64_t* view, uint2* queue, uint64_t* sums,
+                                            LaneSim<SPL, POL, SMODE, DUAL>& T,
                                             Pool& pool, Totals& W, const LogSink& L, uint64_t& e_io,
                                             uint64_t end) {
   using PT = Pol<POL, SMODE>;
-  using LS = LaneSim<SPL, POL, SMODE>;
+  using LS = LaneSim<SPL, POL, SMODE, DUAL>;
   using KT = typename LS::KT;
+  using O = Order<SPL, KT>;
   constexpr uint64_t kGolden = 0x9e3779b97f4a7c15ull;
   const uint32_t lane = T.lane;
   const uint64_t below = (1ull << lane) - 1ull;
@@ -447,6 +520,13 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
   c.put(kCLogCap, L.cap);
   c.put(kCIdBits, tr.n_sess > 1u ? 32u - (uint32_t)__builtin_clz(tr.n_sess - 1u) : 0u);
   c.put(kCHasTool, PT::eta && tr.tool != nullptr ? 1u : 0u);
+  if constexpr (DUAL) {
+    c.put(kCDual, uni32(P.dual_sync));
+    c.put(kCView, view);
+    c.put(kCStride, (uint64_t)a.max_sessions);
+    c.put(kCSync, (uint64_t)0);           // 1 + the index of the latest refresh
+    c.put(kCReq, pool.requests);    // requests so far
+  }
   const auto key_ctx = [&]() {
     KeyCtx v = K;
     v.lambda = c.u32(kCLambda);
@@ -456,7 +536,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
     return v;
   };
   const bool tide = uni32(P.tide) != 0;
-  const uint32_t online = K.online_cap;
+  const uint32_t online = DUAL ? 0u : K.online_cap;
   const uint32_t log_on = L.on ? 1u : 0u, log_victims = L.victims ? 1u : 0u;
   const bool ema = LS::kGapEma || tide;
   const uint64_t cap_s = uni64(P.cap_sram_B), cap_h = uni64(P.cap_hbm_B);
@@ -468,7 +548,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
 
   uint64_t log_len = in_vgpr(pool.log_len);
   uint64_t dma_bytes = 0;
-  uint32_t passes = 0, hi = 0;
+  uint32_t passes = 0, hi = 0, vict_diff = 0, prom_diff = 0;
   // per lane, summed over the wavefront at the end; the 64-bit sums in LDS
 #pragma unroll
   for (uint32_t i = 0; i < kSums; ++i) sums[i * 64u + lane] = 0ull;
@@ -499,9 +579,28 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
     return v;
   };
 
+  const auto gather_copy = [&](uint32_t sid) {
+    CopyRegs v{};
+    if constexpr (DUAL) {
+      const uint64_t* v0 = c.ptr<uint64_t>(kCView);
+      const uint64_t st = c.u64(kCStride);
+      const uint64_t x = v0[sid];
+      v.g = __uint_as_float((uint32_t)(x >> 32));
+      v.turn = meta_turn((uint32_t)x);
+      v.done = meta_phase((uint32_t)x) == kDoneP;
+      v.gq = PT::fixed ? v0[st + sid] : 0ull;
+      v.last = v0[2 * st + sid];
+      v.next = PT::nextkey ? v0[3 * st + sid] : ~0ull;
+      v.seen = v0[4 * st + sid];
+      v.live_next = PT::nextkey ? c.ptr<uint64_t>(kCNext)[sid] : ~0ull;
+    }
+    return v;
+  };
+
   uint64_t base = e_io;
   EvRegs cur = load_events(base);
   TabRegs tab = gather(cur.sid);
+  CopyRegs cp = gather_copy(cur.sid);
   EvRegs nxt = load_events(base + 64);
 
   while (base < end) {
@@ -570,6 +669,78 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
       if (kind == kGapStart) next = sat_add(now, c.ptr<uint64_t>(kCEta)[cur.tool < kEtaClasses ? cur.tool : 0u]);
     }
     KT key = LS::key_from(key_ctx(), kind == kDone, turn, g, gq, now, next);
+    // The copies' entry before the event.  It is the live entry after the
+    // session's previous event if a refresh fell at or after that event, else
+    // what the copies held before it.
+    KT copy_key = 0;
+    uint64_t m_sync = 0;
+    uint64_t next_out = next;  // the live entry's next arrival after the event
+    if constexpr (DUAL) {
+      const uint32_t mode = c.u32(kCDual);
+      const uint64_t m_arr = ballot(valid && arrive);
+      const uint32_t nth = (uint32_t)c.u64(kCReq) + pop64(m_arr & (below | (1ull << lane)));
+      m_sync = ballot(valid && (mode == UNISON_DUAL_EVERY   ? kind != kDone
+                                : mode == UNISON_DUAL_EIGHT ? arrive && nth % 8u == 0u
+                                                            : kind == kGapStart));
+      const uint64_t sync_before = m_sync & below;
+      // event indices + 1; 0: no refresh yet
+      const uint64_t last_sync = c.u64(kCSync);
+      const CopyRegs v = cp;
+      float vg = v.g;
+      uint64_t vq = v.gq, vlast = v.last, vnext = v.next;
+      uint32_t vturn = v.turn;
+      bool vdone = v.done;
+      if (arrive) next_out = v.live_next;  // an arrival keeps the one before it
+      uint64_t go = ballot(prev < 0);
+      const bool late = prev < 0 ? sync_before != 0ull || last_sync > v.seen
+                                 : (sync_before >> (prev < 0 ? 0 : prev)) != 0ull;
+      if (prev < 0 && late) {
+        vg = __uint_as_float((uint32_t)(tab.mg >> 32));
+        vq = tab.gq;
+        vlast = tab.last;
+        vnext = v.live_next;
+        vturn = meta_turn((uint32_t)tab.mg);
+        vdone = false;  // a completed session has no later event
+      }
+      while (go != ~0ull) {
+        const int p = prev < 0 ? (int)lane : prev;
+        const bool take = prev >= 0 && ((go >> p) & 1ull) && !((go >> lane) & 1ull);
+        // after the previous event ...
+        const float ag = __shfl(g, p);
+        const uint64_t aq = PT::fixed ? __shfl((unsigned long long)gq, p) : 0ull;
+        const uint64_t al = __shfl((unsigned long long)now, p), an = __shfl((unsigned long long)next_out, p);
+        const uint32_t at = __shfl(turn, p);
+        // ... and what the copies held before it
+        const float bg = __shfl(vg, p);
+        const uint64_t bq = PT::fixed ? __shfl((unsigned long long)vq, p) : 0ull;
+        const uint64_t bl = __shfl((unsigned long long)vlast, p), bn = __shfl((unsigned long long)vnext, p);
+        const uint32_t bt = __shfl(vturn, p);
+        const bool bd = __shfl((int)vdone, p) != 0;
+        if (take) {
+          vg = late ? ag : bg;
+          vq = late ? aq : bq;
+          vlast = late ? al : bl;
+          vnext = late ? an : bn;
+          vturn = late ? at : bt;
+          vdone = late ? false : bd;
+          if (arrive) next_out = an;
+        }
+        go |= ballot(take);
+      }
+      copy_key = LS::key_from(key_ctx(), vdone, vturn, vg, vq, vlast, vnext);
+      if (newest) {
+        c.ptr<uint64_t>(kCView)[sid] = (uint64_t)make_meta(vdone ? kDoneP : kGap, kTierNone, vturn) |
+                                       ((uint64_t)__float_as_uint(vg) << 32);
+        uint64_t* const v1 = c.ptr<uint64_t>(kCView) + c.u64(kCStride);
+        v1[sid] = vq;
+        v1[c.u64(kCStride) + sid] = vlast;
+        v1[2 * c.u64(kCStride) + sid] = vnext;
+        // the event's index, where the second copy will be
+        v1[3 * c.u64(kCStride) + sid] = base + lane;
+      }
+      if (m_sync) c.put(kCSync, (uint64_t)(base + 64u - (uint32_t)__builtin_clzll(m_sync)));
+      c.put(kCReq, (uint64_t)(c.u64(kCReq) + pop64(m_arr)));
+    }
     const uint64_t size = (uint64_t)ln * tab.kvb;
     uint64_t budget = 0;
     if (tide) {
@@ -596,7 +767,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
       c.ptr<uint32_t>(kCLen)[sid] = len_out;
       c.ptr<uint64_t>(kCLast)[sid] = now;
       if constexpr (PT::nextkey) {
-        if (!arrive) c.ptr<uint64_t>(kCNext)[sid] = next;
+        if (DUAL || !arrive) c.ptr<uint64_t>(kCNext)[sid] = next_out;
       }
     }
     wave_sync();
@@ -604,6 +775,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
     // the next window's entries and the events after it, in flight meanwhile
     cur = nxt;
     tab = gather(cur.sid);
+    cp = gather_copy(cur.sid);
     nxt = load_events(base + 128);
 
     // the event's word: its session, and what the chain asks about it
@@ -648,10 +820,10 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
     };
     // A resident leaves the pool: its bytes, its slot.
     const auto leave = [&](uint32_t x) {
-      const uint32_t slot = LS::slot_in(x);
+      const uint32_t slot = O::slot_in(x);
       const uint64_t sz = LS::get(T.ssz, slot);
-      used_s -= x & LS::kSram ? sz : 0ull;
-      used_h -= x & LS::kSram ? 0ull : sz;
+      used_s -= x & kSram ? sz : 0ull;
+      used_h -= x & kSram ? 0ull : sz;
       --n_res;
       n_table -= (x >> 1) & 1u;  // a completed session leaves the table
       LS::set(T.ssid, slot, kNone);
@@ -666,14 +838,14 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
         if constexpr (PT::timeout) {
           // TTL timers that fired since the previous event, smallest id first
           const uint64_t th = rl(thr, k);
-          while (LS::get(T.skey, 0) > th) {
+          while (LS::get(T.live.skey, 0) > th) {
             uint32_t c = kNone;
 #pragma unroll
-            for (int j = 0; j < SPL; ++j) c = T.skey[j] > th && ~T.snot[j] < c ? ~T.snot[j] : c;
+            for (int j = 0; j < SPL; ++j) c = T.live.skey[j] > th && ~T.live.snot[j] < c ? ~T.live.snot[j] : c;
             c = uni32(wave_ext32<false>(c));
-            emit(k, kOpExpire, c >> LS::kSidShift, 0u);
+            emit(k, kOpExpire, c >> kSidShift, 0u);
             leave(c);
-            T.remove_at(T.pos_of(c >> LS::kSidShift));
+            T.remove(c >> kSidShift);
             stop = q_n >= kQueueFlush ? k + 1u : stop;
           }
         }
@@ -686,16 +858,16 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
           if (slot != kNone) {
             const uint32_t fl = LS::get(T.sfl, slot);
             const uint64_t sz = LS::get(T.ssz, slot);
-            used_s -= fl & LS::kSram ? sz : 0ull;
-            used_h -= fl & LS::kSram ? 0ull : sz;
-            code = fl & LS::kSram ? fl & 3u : 4u;
+            used_s -= fl & kSram ? sz : 0ull;
+            used_h -= fl & kSram ? 0ull : sz;
+            code = fl & kSram ? fl & 3u : 4u;
             --n_res;
             LS::set(T.ssid, slot, kNone);
-            T.remove_at(T.pos_of(s));
+            T.remove(s);
           }
-          uint32_t x = T.front();
-          o_vic = wl(o_vic, k, LS::sid_of(x));
-          if (log_victims) emit(k, kOpVictim, LS::sid_of(x), 0u);
+          uint32_t x = T.order().front();
+          o_vic = wl(o_vic, k, O::sid_of(x));
+          if (log_victims) emit(k, kOpVictim, O::sid_of(x), 0u);
           // Alg. 1 capacity branch: evict the argmax victim until the session fits
           uint32_t place = 0;  // the tier, 0: bypassed
           const uint64_t sz = rl(size, k);
@@ -709,10 +881,12 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
               place = fit_s + 2u * (fit_h & ((fit_s ^ 1u) | want_h));
               place = place == 3u ? kTierHbm : place;
               if ((place != 0u) | (x == kNone)) break;
-              emit(k, kOpEvict, x >> LS::kSidShift, 0u);
+              emit(k, kOpEvict, x >> kSidShift, 0u);
               leave(x);
-              T.pop_front();
-              x = T.front();
+              // eq. (stale): would the live file agree?
+              if constexpr (DUAL) vict_diff += T.live.front() >> kSidShift != x >> kSidShift ? 1u : 0u;
+              T.pop_front(x >> kSidShift);
+              x = T.order().front();
               stop = q_n >= kQueueFlush ? k + 1u : stop;
             }
           }
@@ -738,8 +912,8 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
               LS::set(T.sturn, slot, rl(turn, k));
               LS::set(T.sema, slot, PT::fixed ? rl(gq, k) : (uint64_t)rl(__float_as_uint(g), k));
             }
-            T.insert(rl(key, k), (s << LS::kSidShift) | (slot << 2) | (onset ? 0u : LS::kDoneB) |
-                                     (fl & LS::kSram));
+            T.insert(rl(key, k), DUAL ? rl(copy_key, k) : (KT)0, (s << kSidShift) | (slot << 2) | (onset ? 0u : kDoneB) |
+                                     (fl & kSram));
           }
           // an online hazard table counts the completed session before the scan
           if (!onset && online && uni32(K.hn[0]) < K.online_cap) {
@@ -749,7 +923,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
           }
           w_evals += n_table;
           w_res += n_res;
-          const uint32_t v0 = LS::sid_of(T.front());
+          const uint32_t v0 = O::sid_of(T.order().front());
           o_vic = wl(o_vic, k, v0);
           if (log_victims) {
             emit(k, kOpVictim, v0, 0u);
@@ -762,11 +936,11 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
             bool more = true;
             while (more) {
               more = false;
-              const uint32_t p = T.last_hbm();
+              const uint32_t p = T.order().last_hbm();
               if (p != kNone) {
-                const KT pk = LS::get(T.skey, p);
-                const uint32_t px = T.entry(p);
-                const uint32_t ps = LS::slot_in(px);
+                const KT pk = LS::get(T.order().skey, p);
+                const uint32_t px = T.order().entry(p);
+                const uint32_t ps = O::slot_in(px);
                 const uint64_t sp = LS::get(T.ssz, ps);
                 // past the budget or the SRAM, neither a promotion nor a swap is legal
                 uint32_t may = le64(sp, left) & le64(sp, cap_s);
@@ -776,28 +950,32 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
                   uint64_t sd = 0;
                   more = le64(used_s + sp, cap_s) != 0u;
                   if (!more) {
-                    d = T.first_sram();
+                    d = T.order().first_sram();
                     if (d != kNone) {
-                      dx = T.entry(d);
-                      ds = LS::slot_in(dx);
+                      dx = T.order().entry(d);
+                      ds = O::slot_in(dx);
                       sd = LS::get(T.ssz, ds);
-                      more = ((pk < LS::get(T.skey, d) ? 1u : 0u) & le64(sd, left - sp) &
+                      more = ((pk < LS::get(T.order().skey, d) ? 1u : 0u) & le64(sd, left - sp) &
                               le64(used_s - sd + sp, cap_s) & le64(used_h - sp + sd, cap_h)) != 0u;
                     }
                   }
                   if (more) {
+                    if constexpr (DUAL) {
+                      const uint32_t lp = T.live.last_hbm();
+                      prom_diff += T.live.entry(lp) >> kSidShift != px >> kSidShift ? 1u : 0u;
+                    }
                     used_s = used_s - sd + sp;
                     used_h = used_h - sp + sd;
-                    LS::set(T.snot, p, ~(px | 1u));
-                    LS::set(T.sfl, ps, LS::get(T.sfl, ps) | LS::kSram | LS::kPref);
+                    T.change(p, px, px | kSram);
+                    LS::set(T.sfl, ps, LS::get(T.sfl, ps) | kSram | LS::kPref);
                     if (d != kNone) {
-                      LS::set(T.snot, d, ~(dx & ~1u));
-                      LS::set(T.sfl, ds, LS::get(T.sfl, ds) & ~LS::kSram);
+                      T.change(d, dx, dx & ~kSram);
+                      LS::set(T.sfl, ds, LS::get(T.sfl, ds) & ~kSram);
                     }
                     left -= sp + sd;
                     moved += sp + sd;
-                    emit(k, d == kNone ? kOpPromote : kOpSwap, px >> LS::kSidShift,
-                         d == kNone ? 0u : dx >> LS::kSidShift);
+                    emit(k, d == kNone ? kOpPromote : kOpSwap, px >> kSidShift,
+                         d == kNone ? 0u : dx >> kSidShift);
                     stop = q_n >= kQueueFlush ? k + 1u : stop;
                   }
                 }
@@ -814,6 +992,9 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
               dma_bytes += moved;
             }
           }
+        }
+        if constexpr (DUAL) {
+          if ((m_sync >> k) & 1ull) T.sync();
         }
       }
       flush();
@@ -850,7 +1031,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
   }
 
   e_io = base;
-  pool = Pool{used_s, used_h, dma_free, log_len, n_res, n_table};
+  pool = Pool{used_s, used_h, dma_free, log_len, 0ull, DUAL ? c.u64(kCSync) : 0ull, n_res, n_table};
   const auto sum = [&](uint32_t i) { return wave_sum64(sums[i * 64u + lane]); };
   const auto sum32 = [](uint32_t v) { return (uint32_t)wave_sum64(v); };
   W.hi = wave_ext32<true>(hi);
@@ -869,6 +1050,8 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
   W.n_pro = sum32(n_pro);
   W.n_swap = sum32(n_swap);
   W.passes = passes;
+  W.vict_diff = vict_diff;
+  W.prom_diff = prom_diff;
   W.dma_bytes = dma_bytes;
   W.tok = sum(kSTok);
   W.comp = sum(kSComp);
@@ -879,10 +1062,10 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
   W.victim_digest = sum(kSVictim);
 }
 
-template <int SPL, uint32_t POL, uint32_t SMODE>
+template <int SPL, uint32_t POL, uint32_t SMODE, bool DUAL>
 __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const KeyCtx& K0,
                                          uint2* queue, uint64_t* sums) {
-  using LS = LaneSim<SPL, POL, SMODE>;
+  using LS = LaneSim<SPL, POL, SMODE, DUAL>;
   using KT = typename LS::KT;
   using PT = Pol<POL, SMODE>;
   // each instance computes its own addresses: shared ones would be hoisted
@@ -926,7 +1109,9 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
   __syncthreads();
   // residents never exceed min(N_sess, sessions): the launcher picks a kernel that holds them
   const uint64_t max_res = P.n_slots < n_sess ? P.n_slots : n_sess;
-  bool fits = !P.dual_sync && max_res <= 64u * SPL;
+  const bool dual_ok = DUAL ? a.views && !P.hazard_online : !P.dual_sync;
+  bool fits = dual_ok && max_res <= 64u * SPL;
+  uint64_t* const view = DUAL ? a.views + (size_t)sim * 8 * a.max_sessions : nullptr;
   ok = ok && fits;
 
   // a resumed table's residents take slots, in session order
@@ -943,6 +1128,14 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
       const float g = __uint_as_float((uint32_t)(x >> 32));
       const bool done = meta_phase(m) == kDoneP;
       const KT key = LS::key_from(K, done, meta_turn(m), g, q, last, next);
+      KT copy_key = 0;
+      if constexpr (DUAL) {
+        const size_t st = a.max_sessions;
+        const uint64_t vx = in ? view[i] : 0ull;
+        copy_key = LS::key_from(K, meta_phase((uint32_t)vx) == kDoneP, meta_turn((uint32_t)vx),
+                                __uint_as_float((uint32_t)(vx >> 32)), in ? view[st + i] : 0ull,
+                                in ? view[2 * st + i] : 0ull, in ? view[3 * st + i] : ~0ull);
+      }
       // while the launch runs only the slots know the tiers: a resident that
       // leaves without an event of its own must not keep one in the table
       if (in && meta_tier(m) != kTierNone)
@@ -954,7 +1147,7 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
         }
         const uint32_t l = (uint32_t)__builtin_ctzll(bits);
         const uint32_t mm = rl(m, l), s = b + l;
-        const uint32_t fl = (meta_tier(mm) == kTierSram ? LS::kSram : 0u) |
+        const uint32_t fl = (meta_tier(mm) == kTierSram ? kSram : 0u) |
                             ((mm & kPrefetched) ? LS::kPref : 0u);
         LS::set(T.ssid, n, s);
         LS::set(T.sfl, n, fl);
@@ -962,8 +1155,8 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
         LS::set(T.sturn, n, meta_turn(mm));
         LS::set(T.sema, n, PT::fixed ? rl(q, l) : (uint64_t)rl((uint32_t)(x >> 32), l));
         if (meta_phase(mm) != kServing)
-          T.insert(rl(key, l), (s << LS::kSidShift) | (n << 2) |
-                                   (meta_phase(mm) == kDoneP ? LS::kDoneB : 0u) | (fl & LS::kSram));
+          T.insert(rl(key, l), DUAL ? rl(copy_key, l) : (KT)0, (s << kSidShift) | (n << 2) |
+                                   (meta_phase(mm) == kDoneP ? kDoneB : 0u) | (fl & kSram));
         ++n;
       }
     }
@@ -972,13 +1165,32 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
   const LogSink L{log_on, log_on ? a.log + (size_t)sim * a.log_cap : nullptr, a.log_cap, lane == 0,
                   log_on && (a.flags & UNISON_RUN_LOG_VICTIM) != 0};
   const uint64_t e0 = e;
+  if constexpr (DUAL) {
+    // While the launch runs, the first copy holds each session's entry as the
+    // copies did before its latest event, and the second copy's first field
+    // that event's index: none since this launch began (a resumed launch's
+    // copies are as the last one left them).
+    if (ok) {
+      const size_t st = a.max_sessions;
+      for (uint32_t i = lane; i < n_sess; i += 64) {
+        if (!cont) {
+          view[i] = 0;
+          view[st + i] = 0;
+          view[2 * st + i] = 0;
+          view[3 * st + i] = ~0ull;
+        }
+        view[4 * st + i] = e0;
+      }
+      __syncthreads();
+    }
+  }
   uint64_t bad = 0;
   Totals W{};
   Pool pool{};
   if (cont) {
     const SimState& st = a.state[sim];
     pool = Pool{uni64(st.used_s), uni64(st.used_h), uni64(st.dma_free_at), uni64(st.log_len),
-                uni32(st.n_res), uni32(st.n_table)};
+                uni64(a.counters[sim].requests), 0ull, uni32(st.n_res), uni32(st.n_table)};
   }
   if (ok) {
     const uint64_t bad_at = a.first_bad[P.trace];
@@ -988,15 +1200,30 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
       bad = bad_at + 1;
     }
     if (e < end)
-      lane_events<SPL, POL, SMODE>(a, P, K, tr, tb, a.sess_kvb + sb, queue, sums, T, pool, W, L, e, end);
+      lane_events<SPL, POL, SMODE, DUAL>(a, P, K, tr, tb, a.sess_kvb + sb, view, queue, sums, T, pool, W, L, e, end);
     __syncthreads();
+    if constexpr (DUAL) {
+      // both copies as the latest refresh left them
+      const size_t st = a.max_sessions;
+      for (uint32_t i = lane; i < n_sess; i += 64) {
+        const bool late = pool.last_sync > view[4 * st + i];
+        const uint64_t x = late ? a.t_mg[tb + i] : view[i];
+        const uint64_t q = late ? a.t_gq[tb + i] : view[st + i];
+        const uint64_t l = late ? a.t_last[tb + i] : view[2 * st + i];
+        const uint64_t n = late ? a.t_next[tb + i] : view[3 * st + i];
+        view[i] = view[4 * st + i] = x;
+        view[st + i] = view[5 * st + i] = q;
+        view[2 * st + i] = view[6 * st + i] = l;
+        view[3 * st + i] = view[7 * st + i] = n;
+      }
+    }
     // the residents' tiers into the table
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < SPL; ++j)
       if (T.ssid[j] != kNone) {
         uint32_t* w = reinterpret_cast<uint32_t*>(a.t_mg + tb + T.ssid[j]);
-        *w = with_tier(*w, (T.sfl[j] & LS::kSram) ? kTierSram : kTierHbm) |
+        *w = with_tier(*w, (T.sfl[j] & kSram) ? kTierSram : kTierHbm) |
              ((T.sfl[j] & LS::kPref) ? kPrefetched : 0u);
       }
   }
@@ -1034,6 +1261,8 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
     C.promote += W.n_pro;
     C.swap += W.n_swap;
     C.tide_passes += W.passes;
+    C.vict_diff += W.vict_diff;
+    C.prom_diff += W.prom_diff;
     C.dma_bytes += W.dma_bytes;
     C.tokens_total += W.tok;
     C.tokens_computed += W.comp;
@@ -1049,8 +1278,22 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
   }
 }
 
-template <int SPL>
-__global__ __launch_bounds__(64, SPL == 1 ? 4 : SPL == 2 ? 2 : 1) void sim_lane_kernel(SimArgs a) {
+template <int SPL, uint32_t POL, uint32_t SMODE, bool DUAL>
+__device__ __forceinline__ void lane_row(const SimArgs& a, uint32_t sim, const KeyCtx& K,
+                                         uint2* queue, uint64_t* sums) {
+  if constexpr (DUAL) {
+    if (uni32(a.params[sim].dual_sync)) {
+      lane_run<SPL, POL, SMODE, true>(a, sim, K, queue, sums);
+      return;
+    }
+  }
+  lane_run<SPL, POL, SMODE, false>(a, sim, K, queue, sums);
+}
+
+// DUAL: a batch with rows of the dual design (the others run as ever).
+template <int SPL, bool DUAL>
+__global__ __launch_bounds__(64, SPL == 1 && !DUAL ? 4 : SPL <= 2 ? 2 : 1)
+void sim_lane_kernel(SimArgs a) {
   __shared__ float s_hf[52];
   __shared__ uint32_t s_hq[52];
   __shared__ uint32_t s_hd[52];
@@ -1059,39 +1302,42 @@ __global__ __launch_bounds__(64, SPL == 1 ? 4 : SPL == 2 ? 2 : 1) void sim_lane_
   __shared__ uint64_t s_sums[kSums * 64u];
   const uint32_t sim = blockIdx.x;
   const unison_sim_params& P = a.params[sim];
-  const uint32_t lambda = (1u << P.b_h) - 1u;
-  const KeyCtx K{s_hf, s_hq, s_hd, s_hn, P.penalty_us, lambda, P.p_z, a.time44 != 0,
-                 P.hazard_online ? P.online_sessions : 0u, a.eta + (size_t)P.trace * kEtaClasses,
-                 P.recip_bits};
+  KeyCtx K{};
+  K.hf = s_hf;
+  K.hq = s_hq;
+  K.hd = s_hd;
+  K.hn = s_hn;
+  K.lambda = (1u << P.b_h) - 1u;
   load_hazard(a, P, sim, K, threadIdx.x, 64);
   __syncthreads();
   switch (sim_policy(a, P)) {
     case kSpear:
-      if (P.score_mode) lane_run<SPL, kSpear, 1>(a, sim, K, s_queue, s_sums);
-      else lane_run<SPL, kSpear, 0>(a, sim, K, s_queue, s_sums);
+      if (P.score_mode) lane_row<SPL, kSpear, 1, DUAL>(a, sim, K, s_queue, s_sums);
+      else lane_row<SPL, kSpear, 0, DUAL>(a, sim, K, s_queue, s_sums);
       break;
-    case kLru: lane_run<SPL, kLru, 0>(a, sim, K, s_queue, s_sums); break;
-    case kTimeout: lane_run<SPL, kTimeout, 0>(a, sim, K, s_queue, s_sums); break;
-    case kBelady: lane_run<SPL, kBelady, 0>(a, sim, K, s_queue, s_sums); break;
-    default: lane_run<SPL, kEta, 0>(a, sim, K, s_queue, s_sums); break;
+    case kLru: lane_row<SPL, kLru, 0, DUAL>(a, sim, K, s_queue, s_sums); break;
+    case kTimeout: lane_row<SPL, kTimeout, 0, DUAL>(a, sim, K, s_queue, s_sums); break;
+    case kBelady: lane_row<SPL, kBelady, 0, DUAL>(a, sim, K, s_queue, s_sums); break;
+    default: lane_row<SPL, kEta, 0, DUAL>(a, sim, K, s_queue, s_sums); break;
   }
 }
 
-template <int SPL>
-void launch_width(const SimArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((sim_lane_kernel<SPL>), dim3(a.n_sims), dim3(64), 0, stream, a);
+template <bool DUAL>
+hipError_t launch_width(const SimArgs& a, uint64_t max_res, hipStream_t stream) {
+  const dim3 grid(a.n_sims), block(64);
+  if (max_res <= 64) hipLaunchKernelGGL((sim_lane_kernel<1, DUAL>), grid, block, 0, stream, a);
+  else if (max_res <= 128) hipLaunchKernelGGL((sim_lane_kernel<2, DUAL>), grid, block, 0, stream, a);
+  else if (max_res <= 256) hipLaunchKernelGGL((sim_lane_kernel<4, DUAL>), grid, block, 0, stream, a);
+  else if (max_res <= 512) hipLaunchKernelGGL((sim_lane_kernel<8, DUAL>), grid, block, 0, stream, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 }  // namespace
 
 // max_res: the most residents any simulation can hold, at most 512.
 hipError_t launch_lanes(const SimArgs& a, uint64_t max_res, hipStream_t stream) {
-  if (max_res <= 64) launch_width<1>(a, stream);
-  else if (max_res <= 128) launch_width<2>(a, stream);
-  else if (max_res <= 256) launch_width<4>(a, stream);
-  else if (max_res <= 512) launch_width<8>(a, stream);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  return a.dual ? launch_width<true>(a, max_res, stream) : launch_width<false>(a, max_res, stream);
 }
 
 }  // namespace unison

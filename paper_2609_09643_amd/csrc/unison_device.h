@@ -232,6 +232,7 @@ struct SimArgs {
   const uint32_t* slot_sim;  // register tables: lane group -> simulation (0xFFFFFFFF: empty), or
                              // null for group g = simulation g
   uint32_t n_slots;        // lane groups the register-table grid covers
+  uint32_t dual;           // some row uses the dual register-file design
 };
 
 // The kernel that sorts the residents across one wavefront's lanes, and up to

@@ -74,6 +74,47 @@ def test_resident_counts_around_each_width(n_slots):
     compare_counters(s.counters(), want, label="slots %d split" % n_slots)
 
 
+def dual_workload(n_slots, n_sessions):
+    w = workload(n_sessions=n_sessions, n_slots=n_slots, seed=n_slots + 1)
+    rows = []
+    for r in w.params:
+        if r["hazard_online"]:
+            continue
+        for sync in (synth.DUAL_NONE, synth.DUAL_EVERY, synth.DUAL_EIGHT, synth.DUAL_GAP):
+            q = r.copy()
+            q["dual_sync"] = sync
+            rows.append(q)
+    w.params = np.array(rows, dtype=synth.SIM_PARAMS_DTYPE)
+    return w
+
+
+@pytest.mark.parametrize("n_slots,step", [(12, 1), (40, 64), (40, 77), (100, 90), (200, 1000)])
+def test_dual_copies_across_launches(n_slots, step):
+    """The dual design's copies through launches cut anywhere, every second
+    one on the streamed-table kernel, which reads and refreshes the copies in
+    the workspace."""
+    from paper_2609_09643_amd.unison import lib
+    w = dual_workload(n_slots, 20 if step == 1 else 60 if n_slots < 100 else 300)
+    n = w.traces[0].n_events
+    for swap in (False, True):
+        s = Sim(w, log_cap=1 << 13)
+        for i, e in enumerate(range(0, n, step)):
+            if swap:
+                assert lib().unison_debug_force_variant(s.ctx, 11 if i % 2 else -1) == 0
+            s.run(flags=(1 if e else 0) | 2, max_events=step)
+        compare_counters(s.counters(), oracle_counters(w), label="dual %d/%d swap %d" % (n_slots, step, swap))
+        for i in range(0, w.n_sims, 5):
+            assert same_log(s.log(i), oracle_log(w, i)), "dual sim %d log" % i
+
+
+def test_dual_rows_with_online_tables():
+    w = dual_workload(40, 60)
+    w.params["hazard_online"] = np.arange(w.n_sims) % 3 == 0
+    s = Sim(w)
+    s.run()
+    compare_counters(s.counters(), oracle_counters(w), label="dual online")
+
+
 def test_session_ids_up_to_the_largest():
     top = (1 << 20) - 1
     sids = [top - 3 * k for k in range(60)] + list(range(0, 900, 30))
