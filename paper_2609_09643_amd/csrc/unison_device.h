@@ -150,19 +150,34 @@ __device__ __forceinline__ float spear_f32(float h, float g, float P) {
   return a + c;
 }
 
+// eq. (survq): sigma_q of a hazard h_q.
+__device__ __forceinline__ uint32_t sigma_q(uint32_t hq, uint32_t lambda) {
+  const uint32_t eps_q = (lambda + 50u) / 100u;  // floor(Lambda/100 + 1/2)
+  const uint32_t sigma = lambda - hq;
+  return sigma < eps_q ? eps_q : sigma;
+}
+// The reciprocal r = floor(2^W / sigma_q + 1/2), the entry a table of depth
+// Lambda would hold.
+__device__ __forceinline__ uint64_t recip_q(uint32_t sigma, uint32_t recip_bits) {
+  return ((2ull << recip_bits) + sigma) / (2ull * sigma);
+}
+// eq. (t2).
+__device__ __forceinline__ uint64_t term2_q(uint32_t sigma, uint32_t lambda, uint64_t p_z) {
+  const uint64_t m = lambda - sigma;
+  if (p_z < (1ull << 47)) return (m * p_z) / lambda;
+  return (uint64_t)(((unsigned __int128)m * p_z) / lambda);
+}
+
 // eq. (survq), eq. (t1), eq. (t2), eq. (scoreq) for a live session, b_s = 64.
-// recip_bits = W > 0: eq. (t1) multiplies by the reciprocal r = floor(2^W /
-// sigma_q + 1/2) -- the entry a table of depth Lambda would hold, computed
-// here -- and shifts right by W.
+// recip_bits = W > 0: eq. (t1) multiplies by the reciprocal and shifts right
+// by W.
 __device__ __forceinline__ uint64_t spear_fixed(uint32_t hq, uint64_t gq, uint32_t lambda,
                                                 uint64_t p_z, uint32_t recip_bits) {
-  uint32_t eps_q = (lambda + 50u) / 100u;  // floor(Lambda/100 + 1/2)
-  uint32_t sigma = lambda - hq;
-  if (sigma < eps_q) sigma = eps_q;
-  uint64_t t1, t2;
+  const uint32_t sigma = sigma_q(hq, lambda);
+  uint64_t t1;
   if (recip_bits) {
-    const uint64_t r = ((2ull << recip_bits) + sigma) / (2ull * sigma);
-    const unsigned __int128 q = ((unsigned __int128)gq * lambda * r) >> recip_bits;
+    const unsigned __int128 q =
+        ((unsigned __int128)gq * lambda * recip_q(sigma, recip_bits)) >> recip_bits;
     t1 = q > (unsigned __int128)~0ull ? ~0ull : (uint64_t)q;
   } else if (gq < (1ull << 47)) {
     t1 = (gq * lambda) / sigma;
@@ -170,13 +185,7 @@ __device__ __forceinline__ uint64_t spear_fixed(uint32_t hq, uint64_t gq, uint32
     unsigned __int128 q = ((unsigned __int128)gq * lambda) / sigma;
     t1 = q > (unsigned __int128)~0ull ? ~0ull : (uint64_t)q;  // saturates like the sum
   }
-  uint64_t m = lambda - sigma;
-  if (p_z < (1ull << 47)) {
-    t2 = (m * p_z) / lambda;
-  } else {
-    t2 = (uint64_t)(((unsigned __int128)m * p_z) / lambda);
-  }
-  return sat_add(t1, t2);
+  return sat_add(t1, term2_q(sigma, lambda, p_z));
 }
 
 // Device copy of the workspace regions one kernel launch needs.
