@@ -2,11 +2,10 @@
 // Kendall tau-b statistics of the ranking-fidelity study (Sec. IV-C, Sec. VI-F).
 //
 // The replay and the scorers are elementwise (per-turn terms in LDS, divisions
-// in f64 where that is exact, 16-byte loads where the arrays allow).  The Kendall kernels give each snapshot one
-// workgroup, which gathers its (x, y) pairs once.  Small snapshots are
-// classified pair by pair (each thread owns rows i and walks j > i with all
-// lanes of a wave reading the same LDS word, a broadcast); from 256 entries
-// on, a bitonic sort (its passes in groups of three in registers) and a
+// in f64 where that is exact, 16-byte loads where the arrays allow).  The Kendall
+// kernels gather a snapshot's (x, y) pairs once.  Small snapshots are
+// classified pair by pair, one wavefront each; above 256 entries, on a workgroup
+// each, a bitonic sort (its passes in groups of three in registers) and a
 // counting merge sort (runs of 8 inside each thread, merge path above) find
 // the same counts in O(n log^2 n).
 #include <hip/hip_runtime.h>
@@ -211,7 +210,11 @@ __global__ __launch_bounds__(256) void score_fixed_kernel(uint32_t n, const uint
 
 constexpr int kKendallBlock = 256;
 constexpr uint32_t kKendallMax = 4096;  // sort-based path: 18 B of LDS per entry, 72 KiB
-constexpr uint32_t kKendallSortFrom = 256;  // snapshots this large or larger are sorted
+// Snapshots up to this size are counted pair by pair, larger ones sorted.
+// 10,000 snapshots of 256 entries: 138 us by pairs, 248 sorted (512 in the wide
+// form); pairs grow with the square, and from 384 on the packed sort is ahead
+// (284 us).
+constexpr uint32_t kKendallPairsTo = 256;
 
 __device__ __forceinline__ bool fbetter(float a, uint32_t ia, float b, uint32_t ib) {
   return a > b || (a == b && ia < ib);
@@ -220,41 +223,62 @@ __device__ __forceinline__ bool ubetter(uint64_t a, uint32_t ia, uint64_t b, uin
   return a > b || (a == b && ia < ib);
 }
 
-__global__ __launch_bounds__(kKendallBlock) void kendall_kernel(uint32_t n_per, uint64_t n_x,
-                                                                const float* x, const uint64_t* y,
-                                                                const uint32_t* idx,
-                                                                uint64_t* counts, uint8_t* top1) {
-  extern __shared__ uint64_t s_dyn[];
-  uint64_t* s_y = s_dyn;                                   // [n_per]
-  float* s_x = reinterpret_cast<float*>(s_dyn + n_per);    // [n_per]
-  __shared__ uint64_t s_cnt[4][kKendallBlock / 64];
-  __shared__ float s_bx[kKendallBlock / 64];
-  __shared__ uint32_t s_bxi[kKendallBlock / 64], s_byi[kKendallBlock / 64];
-  __shared__ uint64_t s_by[kKendallBlock / 64];
-  __shared__ uint32_t s_bad;
-  const uint32_t snap = blockIdx.x;
-  const uint32_t tid = threadIdx.x;
-  const size_t base = (size_t)snap * n_per;
-
-  // gather the snapshot into LDS and find both argmaxes
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
+// A wavefront per snapshot of at most 64 R entries (entry i in lane i % 64 of
+// register i / 64).  Step d compares every entry i with entry (i + d) mod n, so
+// n / 2 steps meet each pair once and no lane idles; the snapshot lies twice in
+// LDS, so that a step reads consecutive words.
+// Bound by VALU issue (four compares and four adds per pair and lane).  10,000
+// snapshots of 64 entries: 60 us with a 256-thread workgroup per snapshot (three
+// of its wavefronts idle, every row walking all j > i), 20 now; of 255: 207 and
+// 137.
+template <int R>
+__global__ __launch_bounds__(kKendallBlock) void kendall_pairs_kernel(
+    uint32_t n_snap, uint32_t n, uint64_t n_x, const float* x, const uint64_t* y,
+    const uint32_t* idx, uint64_t* counts, uint8_t* top1) {
+  constexpr uint32_t kSpan = 96u * R;  // 64 R entries and the first 32 R again
+  __shared__ uint64_t s_y[kKendallBlock / 64][kSpan];
+  __shared__ float s_x[kKendallBlock / 64][kSpan];
+  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  const uint32_t want = blockIdx.x * (kKendallBlock / 64) + w;
+  const uint32_t snap = want < n_snap ? want : n_snap - 1u;  // the last block's spare wavefronts
+  const size_t base = (size_t)snap * n;
+  float xa[R];
+  uint64_t ya[R];
+  bool bad = false;
+  // the gather; both argmaxes, ties to the earlier entry
   float bx = 0.0f;
   uint32_t bxi = kNone, byi = kNone;
   uint64_t by = 0;
-  for (uint32_t i = tid; i < n_per; i += kKendallBlock) {
-    size_t e = idx ? (size_t)idx[base + i] : base + i;
-    if (e >= n_x) {  // an index outside x / y: flag the snapshot, read entry 0
-      s_bad = 1;
-      e = 0;
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = r * 64u + lane;
+    xa[r] = 0.0f;
+    ya[r] = 0;
+    if (i < n) {
+      size_t e = idx ? (size_t)idx[base + i] : base + i;
+      if (e >= n_x) {  // an index outside x / y: flag the snapshot, read entry 0
+        bad = true;
+        e = 0;
+      }
+      xa[r] = x[e];
+      ya[r] = y[e];
     }
-    const float xv = x[e];
-    const uint64_t yv = y[e];
-    s_x[i] = xv;
-    s_y[i] = yv;
-    if (bxi == kNone || fbetter(xv, i, bx, bxi)) { bx = xv; bxi = i; }
-    if (byi == kNone || ubetter(yv, i, by, byi)) { by = yv; byi = i; }
   }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = r * 64u + lane;
+    if (i < n) {
+      s_x[w][i] = xa[r];
+      s_y[w][i] = ya[r];
+      if (i < n / 2u) {
+        s_x[w][n + i] = xa[r];
+        s_y[w][n + i] = ya[r];
+      }
+      if (bxi == kNone || fbetter(xa[r], i, bx, bxi)) { bx = xa[r]; bxi = i; }
+      if (byi == kNone || ubetter(ya[r], i, by, byi)) { by = ya[r]; byi = i; }
+    }
+  }
+  bad = __builtin_amdgcn_ballot_w64(bad) != 0ull;
 #pragma unroll
   for (int m = 1; m < 64; m <<= 1) {
     const float ox = __shfl_xor(bx, m);
@@ -264,70 +288,51 @@ __global__ __launch_bounds__(kKendallBlock) void kendall_kernel(uint32_t n_per, 
     if (oxi != kNone && (bxi == kNone || fbetter(ox, oxi, bx, bxi))) { bx = ox; bxi = oxi; }
     if (oyi != kNone && (byi == kNone || ubetter(oy, oyi, by, byi))) { by = oy; byi = oyi; }
   }
-  if ((tid & 63u) == 0) {
-    s_bx[tid >> 6] = bx;
-    s_bxi[tid >> 6] = bxi;
-    s_by[tid >> 6] = by;
-    s_byi[tid >> 6] = byi;
-  }
   __syncthreads();
 
-  // pair classification: discordant, tied in x only, tied in y only, both
+  // pair classification: discordant, tied in x, tied in y, both
   uint32_t nd = 0, ntx = 0, nty = 0, nb = 0;
-  const uint32_t wave0 = tid & ~63u;
-  for (uint32_t r = 0; r * kKendallBlock < n_per; ++r) {
-    const uint32_t i = r * kKendallBlock + tid;
-    const uint32_t first = r * kKendallBlock + wave0;  // smallest row of this wave
-    if (first >= n_per) break;
-    const bool row = i < n_per;
-    const float xa = s_x[row ? i : 0];
-    const uint64_t ya = s_y[row ? i : 0];
-    for (uint32_t j = first + 1; j < n_per; ++j) {
-      const float xb = s_x[j];
-      const uint64_t yb = s_y[j];
-      const bool on = row && j > i;
-      const bool tx = xa == xb;
-      const bool ty = ya == yb;
-      const bool gx = xa > xb;
-      const bool gy = ya > yb;
-      nb += (on && tx && ty) ? 1u : 0u;
-      ntx += (on && tx && !ty) ? 1u : 0u;
-      nty += (on && !tx && ty) ? 1u : 0u;
-      nd += (on && !tx && !ty && gx != gy) ? 1u : 0u;
-    }
-  }
-  uint64_t v[4] = {nd, ntx, nty, nb};
+  // The first `to` entries against those d further on.  A NaN in x is neither
+  // tied nor greater, so a pair with one is compared from its earlier entry (NAN_X).
+  const auto step = [&](auto nan_x, uint32_t d, uint32_t to) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) v[c] += __shfl_xor(v[c], m);
-    if ((tid & 63u) == 0) s_cnt[c][tid >> 6] = v[c];
-  }
-  __syncthreads();
-  if (tid == 0) {
-    uint64_t tot[4] = {0, 0, 0, 0};
-    for (int w = 0; w < kKendallBlock / 64; ++w)
-      for (int c = 0; c < 4; ++c) tot[c] += s_cnt[c][w];
-    const uint64_t pairs = (uint64_t)n_per * (n_per - 1) / 2;
-    counts[(size_t)snap * 5 + 0] = pairs - tot[0] - tot[1] - tot[2] - tot[3];
-    counts[(size_t)snap * 5 + 1] = tot[0];
-    counts[(size_t)snap * 5 + 2] = tot[1];
-    counts[(size_t)snap * 5 + 3] = tot[2];
-    counts[(size_t)snap * 5 + 4] = tot[3];
-    float fx = s_bx[0];
-    uint32_t fxi = s_bxi[0], fyi = s_byi[0];
-    uint64_t fy = s_by[0];
-    for (int w = 1; w < kKendallBlock / 64; ++w) {
-      if (s_bxi[w] != kNone && (fxi == kNone || fbetter(s_bx[w], s_bxi[w], fx, fxi))) {
-        fx = s_bx[w];
-        fxi = s_bxi[w];
-      }
-      if (s_byi[w] != kNone && (fyi == kNone || ubetter(s_by[w], s_byi[w], fy, fyi))) {
-        fy = s_by[w];
-        fyi = s_byi[w];
-      }
+    for (uint32_t r = 0; r < R; ++r) {
+      const uint32_t i = r * 64u + lane;
+      const float xb = s_x[w][i + d];
+      const uint64_t yb = s_y[w][i + d];
+      const bool on = i < to, ex = xa[r] == xb, ey = ya[r] == yb, gy = ya[r] > yb;
+      bool gx = xa[r] > xb;
+      if constexpr (decltype(nan_x)::value) gx = i + d < n ? gx : !(xa[r] < xb);
+      ntx += (on & ex) ? 1u : 0u;
+      nty += (on & ey) ? 1u : 0u;
+      nb += (on & ex & ey) ? 1u : 0u;
+      nd += (on & (gx != gy) & !(ex | ey)) ? 1u : 0u;
     }
-    top1[snap] = s_bad ? (uint8_t)255 : (uint8_t)(fxi == fyi);
+  };
+  const auto steps = [&](auto nan_x) {
+    for (uint32_t d = 1; 2u * d < n; ++d) step(nan_x, d, n);
+    if (n % 2u == 0u) step(nan_x, n / 2u, n / 2u);  // opposite entries: each pair from one side
+  };
+  bool nan = false;
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) nan = nan || xa[r] != xa[r];
+  if (__builtin_amdgcn_ballot_w64(nan)) steps(std::true_type{});
+  else steps(std::false_type{});
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    ntx += __shfl_xor(ntx, m);
+    nty += __shfl_xor(nty, m);
+    nb += __shfl_xor(nb, m);
+    nd += __shfl_xor(nd, m);
+  }
+  if (lane == 0 && want < n_snap) {
+    const uint64_t pairs = (uint64_t)n * (n - 1) / 2;
+    counts[(size_t)snap * 5 + 0] = pairs - nd - ntx - nty + nb;
+    counts[(size_t)snap * 5 + 1] = nd;
+    counts[(size_t)snap * 5 + 2] = ntx - nb;
+    counts[(size_t)snap * 5 + 3] = nty - nb;
+    counts[(size_t)snap * 5 + 4] = nb;
+    top1[snap] = bad ? (uint8_t)255 : (uint8_t)(bxi == byi);
   }
 }
 
@@ -1009,10 +1014,16 @@ hipError_t launch_kendall(uint32_t n_snap, uint32_t n_per, uint64_t n_x, const f
                           const uint64_t* y, const uint32_t* idx, uint64_t* counts, uint8_t* top1,
                           hipStream_t s) {
   if (n_snap == 0) return hipSuccess;
-  if (n_per < kKendallSortFrom) {
-    const size_t lds = (size_t)(n_per ? n_per : 1) * (sizeof(uint64_t) + sizeof(float));
-    hipLaunchKernelGGL(kendall_kernel, dim3(n_snap), dim3(kKendallBlock), lds, s, n_per, n_x, x, y,
-                       idx, counts, top1);
+  if (n_per <= kKendallPairsTo) {
+    const dim3 grid((uint32_t)(((uint64_t)n_snap + kKendallBlock / 64 - 1) / (kKendallBlock / 64)));
+    const dim3 block(kKendallBlock);
+    const auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, 0, s, n_snap, n_per, n_x, x, y, idx, counts, top1);
+    };
+    if (n_per <= 64) launch(kendall_pairs_kernel<1>);
+    else if (n_per <= 128) launch(kendall_pairs_kernel<2>);
+    else if (n_per <= 192) launch(kendall_pairs_kernel<3>);
+    else launch(kendall_pairs_kernel<4>);
   } else {
     uint32_t P = 2;
     while (P < n_per) P <<= 1;
@@ -1033,7 +1044,7 @@ uint32_t kendall_max_per() { return kKendallMax; }
 // The sort kernel's barrier plan, for host-side checks: 1 when the step is
 // followed by a workgroup barrier, 0 when by the wavefront-local fence.
 int kendall_barrier_after(uint32_t P, uint32_t step, uint32_t a, uint32_t b) {
-  if (P < kKendallSortFrom || P > kKendallMax || (P & (P - 1))) return -1;
+  if (P < kKendallPairsTo || P > kKendallMax || (P & (P - 1))) return -1;
   if (step == 0) {  // bitonic pass (k = a, j = b)
     if (a < 2 || a > P || (a & (a - 1)) || b == 0 || b >= a || (b & (b - 1))) return -1;
     return bitonic_barrier_after(P, a, b) ? 1 : 0;

@@ -81,3 +81,41 @@ def test_fixed_score_ranges(U, b_h, recip):
         y = U.score_fixed(U._dev(turn), U._dev(gq), U._dev(done), U._dev(d, np.uint32),
                           U._dev(c, np.uint32), b_h, p_z, recip)
         assert np.array_equal(U._host(y, np.uint64), oracle.score_fixed(turn, gq, done, d, c, b_h, p_z, recip)), p_z
+
+
+@pytest.mark.parametrize("n_per", [2, 5, 63, 64, 66, 127, 128, 130, 191, 192, 193, 254, 255, 256])
+@pytest.mark.parametrize("n_snap", [1, 6])
+def test_kendall_pairs_at_register_edges(U, n_per, n_snap):
+    """Snapshots on one wavefront each: sizes around the register edges, odd
+    and even (an even size has a half step), a last block with spare
+    wavefronts, ties, infinities, -0 beside +0 and an index out of range; a NaN
+    in x is tied with nothing and not greater than anything."""
+    rng = np.random.default_rng(31 * n_per + n_snap)
+    x = rng.integers(-3, max(2, n_per // 2), (n_snap, n_per)).astype(np.float32)
+    y = rng.integers(0, max(2, n_per // 3), (n_snap, n_per)).astype(np.uint64)
+    y += np.uint64(2 ** 33) * rng.integers(0, 2, (n_snap, n_per)).astype(np.uint64)
+    x[0, ::3] = np.inf
+    y[0, ::3] = 2 ** 64 - 1
+    x[-1, ::4] = -0.0
+    if n_snap > 1:
+        x[1] = rng.standard_normal(n_per).astype(np.float32)
+    c, t = U.kendall(U._dev(x.ravel()), U._dev(y.ravel()), None, n_snap, n_per)
+    oc, ot = oracle.kendall(x, y)
+    assert np.array_equal(U._host(c, np.uint64), oc)
+    assert np.array_equal(t.cpu().numpy(), ot)
+    idx = np.arange(n_snap * n_per, dtype=np.uint32).reshape(n_snap, n_per)[:, ::-1].copy()
+    idx[-1, n_per - 1] = n_snap * n_per
+    c2, t2 = U.kendall(U._dev(x.ravel()), U._dev(y.ravel()), U._dev(idx))
+    assert t2.cpu().numpy()[-1] == 255
+    if n_snap > 1:
+        oc2, ot2 = oracle.kendall(x[:-1, ::-1].copy(), y[:-1, ::-1].copy())
+        assert np.array_equal(U._host(c2, np.uint64)[:-1], oc2)
+        assert np.array_equal(t2.cpu().numpy()[:-1], ot2)
+    x[0, n_per // 2::5] = np.nan
+    c3, _ = U.kendall(U._dev(x.ravel()), U._dev(y.ravel()), None, n_snap, n_per)
+    i, j = np.triu_indices(n_per, 1)
+    xa, xb, ya, yb = x[0, i], x[0, j], y[0, i], y[0, j]
+    tx, ty = xa == xb, ya == yb
+    nd = int((~tx & ~ty & ((xa > xb) != (ya > yb))).sum())
+    want = [len(i) - nd - int((tx | ty).sum()), nd, int((tx & ~ty).sum()), int((ty & ~tx).sum()), int((tx & ty).sum())]
+    assert U._host(c3, np.uint64)[0].tolist() == want
