@@ -294,13 +294,15 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params);
  * policy_override is a UNISON_POLICY_* value applied to all simulations, or
  * UNISON_POLICY_PARAMS.  A batch with a dual-design row runs on variant 13
  * while no simulation can hold more than 512 residents and no dual row has
- * hazard_online set, else on the copies' streamed kernel (variant 11).  While no simulation can hold more than 512 residents
- * (min(N_sess, sessions)) a batch runs on one wavefront per simulation with
+ * hazard_online set, else on the copies' streamed kernel (variant 11).  While no simulation can
+ * hold more than 256 residents (min(N_sess, sessions); 512 where a row's hazard
+ * table grows online) a batch runs on one wavefront per simulation with
  * the residents sorted across its lanes (variant 13), except that tables of at
  * most 16 sessions take eight simulations to a wavefront above 4,096
- * simulations (variant 5).  Tables above the LDS-resident size run, while no
- * simulation can hold more than 4,096 residents, on one wavefront per
- * simulation with the residents in 24-byte LDS slots (variant 14); otherwise
+ * simulations (variant 5).  Up to 4,096 residents it runs on one wavefront per
+ * simulation with the residents in sorted lists in LDS (variant 14); with an
+ * online table, while the tables fit, on one wavefront with the table in LDS
+ * (variant 12), else in 24-byte LDS slots (variant 14).  Otherwise it runs
  * on workgroup kernels that keep one bit of LDS per session (the residency bits their scans visit): 128 KiB at
  * UNISON_MAX_SESSIONS; the LDS left holds up to 8 resident-cache slots of
  * 28 B per thread.  Asynchronous.
@@ -382,8 +384,8 @@ int unison_read_hazard(unison_ctx* ctx, uint32_t sim, uint32_t* d_out, uint32_t*
  * threads with the dual design's copies -- the only one that may be pinned for a
  * batch with a dual-design row; one wavefront per simulation with 13: the table in the
  * workspace and the residents sorted across the lanes, 1 to 8 per lane (at most
- * 512 residents), 14: the table in the workspace and the residents in LDS slots
- * (at most 4,096 residents)).  A variant too small for the traces or their
+ * 512 residents), 14: the table in the workspace and the residents in LDS (sorted
+ * lists, or slots for a batch with an online table; at most 4,096 residents)).  A variant too small for the traces or their
  * resident counts, or an unknown id, makes unison_run return
  * UNISON_E_CAPACITY. */
 int unison_debug_force_variant(unison_ctx* ctx, int variant);

@@ -178,6 +178,7 @@ struct unison_ctx {
   std::vector<uint8_t> eta_set;  // per trace: an ETA table was installed
   bool traces_loaded = false, params_set = false, ran = false;
   bool time44 = false;  // every trace time is below 2^44 - 1 ns
+  bool online = false;  // some row's hazard table grows online
   bool dual = false;    // some row uses the dual register-file design
   bool dual_lanes = false;  // and none of those rebuilds its hazard table online
   uint32_t max_sess_batch = 0;
@@ -473,9 +474,11 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
   }
   ctx->h_params.assign(params, params + ctx->dims.n_sims);
   ctx->dual = false;
+  ctx->online = false;
   ctx->dual_lanes = true;
   for (uint32_t i = 0; i < ctx->dims.n_sims; ++i) {
     ctx->dual = ctx->dual || params[i].dual_sync != 0;
+    ctx->online = ctx->online || params[i].hazard_online != 0;
     if (params[i].dual_sync && params[i].hazard_online) ctx->dual_lanes = false;
   }
   int rc = ctx->hip(hipMemcpyAsync(ctx->at<unison_sim_params>(ctx->L.params), ctx->h_params.data(),
@@ -596,6 +599,7 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
   a.policy_override = policy_override;
   a.time44 = ctx->time44 ? 1u : 0u;
   a.dual = ctx->dual ? 1u : 0u;
+  a.online = ctx->online ? 1u : 0u;
   int v = ctx->force_variant;
   // The dual design's copies live in the workspace: the lane kernel keeps them
   // while its residents fit and no dual row's table grows online (its copies'
@@ -619,6 +623,13 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
                      (unsigned long long)sim_variant_max_slots(v), (unsigned long long)max_res);
   if (v < 0) {
     v = sim_auto_variant(ctx->max_sess_batch, max_res);
+    // Sorted lists take no online table, whose every completion changes all
+    // keys: such a batch goes to the lane kernel while it fits (the paper-scale
+    // trace at 512 slots 112 ms against 167), then to the LDS table while that fits.
+    if (v == kWideKernel && ctx->online) {
+      if (max_res <= sim_variant_max_slots(kLaneKernel)) v = kLaneKernel;
+      else if (ctx->max_sess_batch <= sim_variant_capacity(kLdsWaveKernel)) v = kLdsWaveKernel;
+    }
     if (ctx->dual || (sim_variant_lanes(v) && a.n_sims <= kLaneSims)) v = kLaneKernel;
     if (sim_variant_capacity(v) < ctx->max_sess_batch)
       return ctx->fail(UNISON_E_CAPACITY, "%u sessions exceed every kernel variant (largest %u)",

@@ -27,6 +27,7 @@
 // SPEAR+TIDE and 0.33 under LRU, about 1,080 and 735 cycles in the chain and 60
 // in the window's preparation, against 1.28 for residents in unsorted register
 // slots with three wavefront reductions per event and the table in LDS.
+// Above 256 residents the order moves to sorted lists in LDS (ListSim).
 // 128 VGPRs keep four wavefronts on a SIMD: with 200 (sums and window
 // constants in registers) 4,096 simulations of 16 sessions took 225 us, now 167.
 #include <hip/hip_runtime.h>
@@ -93,6 +94,9 @@ __device__ __forceinline__ uint32_t le64(uint64_t a, uint64_t b) {
       : "scc");
   return r;
 }
+// The same wherever the values are: the list pool's bytes may sit in vector
+// registers, which the scalar form's operands cannot.
+__device__ __forceinline__ uint32_t le_u64(uint64_t a, uint64_t b) { return a <= b ? 1u : 0u; }
 // The lowest set bit's index, kNone for none.
 __device__ __forceinline__ uint32_t first_set(uint64_t m) {
   uint32_t r;
@@ -342,6 +346,10 @@ struct LaneSim : Spread<SPL> {
   using PT = Pol<POL, SMODE>;
   // fp32 scores are 32-bit keys; integer scores and times take 64 bits
   using KT = typename std::conditional<PT::spear && !PT::fixed, uint32_t, uint64_t>::type;
+  static constexpr bool kList = false;
+  static constexpr int kRegs = SPL;
+  static constexpr uint32_t kSlots = 64u * SPL;
+  using O = Order<SPL, KT>;
   static constexpr uint32_t kPref = 2u;         // slot flags: kSram and this
   static constexpr bool kGapEma = PT::spear || PT::belady;  // others read it for TIDE only
 
@@ -460,6 +468,356 @@ struct LaneSim : Spread<SPL> {
   }
 };
 
+// Pools of more residents than registers hold in order: two sorted lists, one
+// per tier, of leaves of up to 64 entries in LDS, an entry per lane.  A list's
+// directory -- its leaves in order, each with its first entry, its row and its
+// count -- sits in registers as an Order, so finding an entry's leaf is a
+// comparison per register, and an insertion or removal reads and writes one row.
+// The first entry of a list is in its directory: the scan victim is the better
+// of two fronts, TIDE's demotion candidate the SRAM list's.  A full leaf splits
+// in halves; when no row is free both lists are packed into full leaves.
+// A session's residency (slot, tier) lies in the workspace and, for the events
+// of the current window, in their lanes; a resident's KV bytes in its LDS slot.
+// Bound by the same chain as the register orders, with an LDS round trip or two
+// per change (about 0.8 us per event).  65,536 live sessions (16 simulations of
+// 300,000 events, about 1,100 resident of 4,096 slots): 613 ms with unsorted LDS
+// slots and three wavefront reductions per event, 247 here; the paper-scale trace
+// at 512 and 1,400 slots 112 ms (register orders) and 166 (table in LDS) before,
+// 67 at both here.
+constexpr int kDirRegs = 3;
+constexpr uint32_t kListSlotBits = 12;
+constexpr uint32_t kListResidents = 1u << kListSlotBits;
+constexpr uint32_t kListQueue = 256;  // queued records; a pass over the pool flushes in between
+constexpr uint32_t kStIn = 4u, kStSlot = 3u;  // a residency word: kSram, kPref, kStIn, slot << 3
+
+// Rows for the leaves of max_res residents: packed leaves fill a third of them.
+__host__ __device__ constexpr uint32_t list_rows(uint64_t max_res) {
+  const uint32_t full = (uint32_t)((max_res + 63) / 64);
+  return 3u * full + 8u < 152u ? 3u * full + 8u : 152u;
+}
+static_assert(list_rows(kListResidents) <= 64u * kDirRegs, "a directory holds every row");
+static_assert(list_rows(kListResidents) >= kListResidents / 64u + 4u, "packed leaves leave rows free");
+
+template <class KT>
+struct Dir : Order<kDirRegs, KT> {
+  using B = Order<kDirRegs, KT>;
+  using B::lane;
+  using B::skey;
+  using B::snot;
+  uint32_t leaf[kDirRegs];  // row << 7 | count
+  uint32_t n;               // leaves
+
+  __device__ __forceinline__ void reset(uint32_t l) {
+    this->init(l);
+#pragma unroll
+    for (int j = 0; j < kDirRegs; ++j) leaf[j] = 0;
+    n = 0;
+  }
+  // The leaf an entry belongs to: the last one whose first entry does not
+  // follow it, else the first.
+  __device__ __forceinline__ uint32_t find(KT key, uint32_t e) const {
+    uint32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < kDirRegs; ++j)
+      c += pop64(ballot(((skey[j] > key) | ((skey[j] == key) & (snot[j] >= e))) &
+                        ((uint32_t)j * 64u + lane < n)));
+    return c ? c - 1u : 0u;
+  }
+  // Leaves whose first key is larger than `key`.
+  __device__ __forceinline__ uint32_t above(KT key) const {
+    uint32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < kDirRegs; ++j)
+      c += pop64(ballot((skey[j] > key) & ((uint32_t)j * 64u + lane < n)));
+    return c;
+  }
+  __device__ __forceinline__ void put(uint32_t p, KT key, uint32_t e, uint32_t lf) {
+    B::set(skey, p, key);
+    B::set(snot, p, e);
+    B::set(leaf, p, lf);
+  }
+  __device__ __forceinline__ void open(uint32_t p, KT key, uint32_t e, uint32_t lf) {
+    bool before[kDirRegs];
+#pragma unroll
+    for (int j = 0; j < kDirRegs; ++j) before[j] = (uint32_t)j * 64u + lane < p;
+    B::open_gap(skey, before);
+    B::open_gap(snot, before);
+    B::open_gap(leaf, before);
+    put(p, key, e, lf);
+    ++n;
+  }
+  __device__ __forceinline__ void close(uint32_t p) {
+    this->template close_gap<false>(skey, p);
+    this->template close_gap<false>(snot, p);
+    this->template close_gap<false>(leaf, p);
+    --n;
+  }
+};
+
+template <uint32_t POL, uint32_t SMODE>
+struct ListSim {
+  using PT = Pol<POL, SMODE>;
+  using KT = typename std::conditional<PT::spear && !PT::fixed, uint32_t, uint64_t>::type;
+  using D = Dir<KT>;
+  static constexpr bool kList = true;
+  static constexpr uint32_t kSlots = kListResidents;
+  static constexpr uint32_t kPref = 2u;
+  static constexpr bool kGapEma = PT::spear || PT::belady;
+
+  uint32_t lane;
+  D hbm, sram;
+  KT* lkey;         // LDS [rows][64]
+  uint32_t* lent;   // LDS [rows][64]: session << 12 | slot, complemented
+  uint64_t* ssz;    // LDS [slots]: KV bytes
+  uint32_t* where;  // workspace [sessions]: residency words
+  uint32_t rows_free;          // per lane: bit b for row b * 64 + lane
+  uint64_t used, done, pref;   // per lane: bit b for slot b * 64 + lane
+
+  // LDS: the slots, the rows' keys, the rows' entries.
+  __device__ __forceinline__ void init(uint32_t l, uint64_t* lds, uint32_t slots, uint32_t rows, uint32_t* w) {
+    lane = l;
+    ssz = lds;
+    lkey = reinterpret_cast<KT*>(lds + slots);
+    lent = reinterpret_cast<uint32_t*>(lkey + rows * 64u);
+    where = w;
+    hbm.reset(l);
+    sram.reset(l);
+    rows_free = 0;
+    for (uint32_t b = 0; b < (uint32_t)kDirRegs; ++b) rows_free |= b * 64u + l < rows ? 1u << b : 0u;
+    used = slots < kListResidents ? ~0ull << (slots >> 6) : 0ull;  // slots is a multiple of 64
+    done = pref = 0;
+  }
+  __device__ __forceinline__ static KT key_from(const KeyCtx& K, bool fin, uint32_t turn, float g,
+                                                uint64_t gq, uint64_t t, uint64_t next) {
+    const uint32_t m = make_meta(fin ? kDoneP : kGap, kTierNone, turn);
+    return (KT)key_of<POL, SMODE>(K, m, hazard_of<POL, SMODE>(K, m), g, gq, t, next);
+  }
+  __device__ __forceinline__ static uint32_t entry_of(uint32_t sid, uint32_t slot) {
+    return ~((sid << kListSlotBits) | slot);
+  }
+  __device__ __forceinline__ static uint32_t sid_in(uint32_t e) { return ~e >> kListSlotBits; }
+  __device__ __forceinline__ static uint32_t slot_in(uint32_t e) { return ~e & (kListResidents - 1u); }
+  __device__ __forceinline__ uint64_t mine(uint32_t slot) const {
+    return lane == (slot & 63u) ? 1ull << (slot >> 6) : 0ull;
+  }
+  __device__ __forceinline__ static uint32_t bit(uint64_t m, uint32_t slot) {
+    return (uint32_t)(rl(m, slot & 63u) >> (slot >> 6)) & 1u;
+  }
+  // A free slot (residents never exceed the slots).
+  __device__ __forceinline__ uint32_t take_slot() {
+    const uint32_t l = first_set(ballot(used != ~0ull));
+    const uint32_t s = (uint32_t)__builtin_ctzll(~rl(used, l)) * 64u + l;
+    used |= mine(s);
+    done &= ~mine(s);
+    pref &= ~mine(s);
+    return s;
+  }
+  __device__ __forceinline__ void free_slot(uint32_t s) { used &= ~mine(s); }
+  // (The index in a vector register keeps the readfirstlane: of an address known
+  // to be uniform it is dropped, and the value stays out of the scalar registers.)
+  __device__ __forceinline__ uint64_t size(uint32_t slot) const { return uni64(ssz[in_vgpr(slot)]); }
+
+  __device__ __forceinline__ uint32_t take_row() {
+    const uint32_t l = first_set(ballot(rows_free != 0u));
+    const uint32_t b = (uint32_t)__builtin_ctz(rl(rows_free, l));
+    rows_free &= lane == l ? ~(1u << b) : ~0u;
+    return b * 64u + l;
+  }
+  __device__ __forceinline__ void give_row(uint32_t r) {
+    rows_free |= lane == (r & 63u) ? 1u << (r >> 6) : 0u;
+  }
+  // Every leaf full but the last.  Rows are refilled in order: a row is written
+  // once the rows before it and itself have been read.
+  __device__ __forceinline__ void pack(D& d) {
+    KT bk = 0;
+    uint32_t be = 0, nb = 0, out = 0;
+    const uint32_t was = d.n;
+    for (uint32_t p = 0; p < was; ++p) {
+      const uint32_t lf = D::get(d.leaf, p), c = lf & 127u, i = (lf >> 7) * 64u + lane;
+      const KT k = lkey[i];
+      const uint32_t e = lent[i];
+      const int from = (int)((lane - nb) & 63u);
+      const KT rk = (KT)__shfl((unsigned long long)k, from);
+      const uint32_t re = __shfl(e, from);
+      bk = lane < nb ? bk : rk;
+      be = lane < nb ? be : re;
+      nb += c;
+      if (nb >= 64u) {
+        const uint32_t row = D::get(d.leaf, out) >> 7;
+        lkey[row * 64u + lane] = bk;
+        lent[row * 64u + lane] = be;
+        d.put(out, rl(bk, 0u), rl(be, 0u), row << 7 | 64u);
+        ++out;
+        bk = rk;
+        be = re;
+        nb -= 64u;
+      }
+    }
+    if (nb) {
+      const uint32_t row = D::get(d.leaf, out) >> 7;
+      lkey[row * 64u + lane] = bk;
+      lent[row * 64u + lane] = be;
+      d.put(out, rl(bk, 0u), rl(be, 0u), row << 7 | nb);
+      ++out;
+    }
+    for (uint32_t p = out; p < was; ++p) give_row(D::get(d.leaf, p) >> 7);
+    d.n = out;
+  }
+  __device__ __forceinline__ void split(D& d, uint32_t p) {
+    const uint32_t row = D::get(d.leaf, p) >> 7, up = take_row();
+    const KT k = lkey[row * 64u + lane];
+    const uint32_t e = lent[row * 64u + lane];
+    const int from = (int)((lane + 32u) & 63u);
+    const KT uk = (KT)__shfl((unsigned long long)k, from);
+    const uint32_t ue = __shfl(e, from);
+    lkey[up * 64u + lane] = uk;
+    lent[up * 64u + lane] = ue;
+    D::set(d.leaf, p, row << 7 | 32u);
+    d.open(p + 1u, rl(k, 32u), rl(e, 32u), up << 7 | 32u);
+  }
+  __device__ __forceinline__ void insert(D& d, KT key, uint32_t e) {
+    if (ballot(rows_free != 0u) == 0ull) {
+      pack(hbm);
+      pack(sram);
+    }
+    if (d.n == 0u) {
+      const uint32_t row = take_row();
+      lkey[row * 64u + lane] = key;
+      lent[row * 64u + lane] = e;
+      d.open(0u, key, e, row << 7 | 1u);
+    } else {
+      uint32_t p = d.find(key, e);
+      uint32_t lf = D::get(d.leaf, p);
+      if ((lf & 127u) == 64u) {
+        split(d, p);
+        p = d.find(key, e);
+        lf = D::get(d.leaf, p);
+      }
+      const uint32_t i = (lf >> 7) * 64u + lane;
+      const KT k = lkey[i];
+      const uint32_t x = lent[i];
+      const bool before = (lane < (lf & 127u)) & ((k > key) | ((k == key) & (x > e)));
+      const uint32_t q = pop64(ballot(before));
+      const KT kb = from_below(k);
+      const uint32_t xb = from_below(x);
+      lkey[i] = before ? k : lane == q ? key : kb;
+      lent[i] = before ? x : lane == q ? e : xb;
+      D::set(d.leaf, p, lf + 1u);
+      if (q == 0u) {
+        D::set(d.skey, p, key);
+        D::set(d.snot, p, e);
+      }
+    }
+  }
+  // Entry q of leaf p leaves.
+  __device__ __forceinline__ void remove_at(D& d, uint32_t p, uint32_t q, uint32_t lf, KT k, uint32_t x) {
+    if ((lf & 127u) == 1u) {
+      give_row(lf >> 7);
+      d.close(p);
+    } else {
+      const KT ka = from_above(k);
+      const uint32_t xa = from_above(x), i = (lf >> 7) * 64u + lane;
+      k = lane < q ? k : ka;
+      x = lane < q ? x : xa;
+      lkey[i] = k;
+      lent[i] = x;
+      D::set(d.leaf, p, lf - 1u);
+      if (q == 0u) {
+        D::set(d.skey, p, rl(k, 0u));
+        D::set(d.snot, p, rl(x, 0u));
+      }
+    }
+  }
+  __device__ __forceinline__ void remove_at(D& d, uint32_t p, uint32_t q) {
+    const uint32_t lf = D::get(d.leaf, p), i = (lf >> 7) * 64u + lane;
+    remove_at(d, p, q, lf, lkey[i], lent[i]);
+  }
+  __device__ __forceinline__ void remove(D& d, KT key, uint32_t e) {
+    if (d.n) {
+      const uint32_t p = d.find(key, e), lf = D::get(d.leaf, p), i = (lf >> 7) * 64u + lane;
+      const KT k = lkey[i];
+      const uint32_t x = lent[i];
+      const uint32_t q = first_set(ballot((lane < (lf & 127u)) & (x == e)));
+      if (q != kNone) remove_at(d, p, q, lf, k, x);
+    }
+  }
+  // An entry whose key is not at hand, near the front.
+  __device__ __forceinline__ void remove_walking(D& d, uint32_t e) {
+    bool more = d.n != 0u;
+    for (uint32_t p = 0; more; ++p) {
+      const uint32_t lf = D::get(d.leaf, p), i = (lf >> 7) * 64u + lane;
+      const KT k = lkey[i];
+      const uint32_t x = lent[i];
+      const uint32_t q = first_set(ballot((lane < (lf & 127u)) & (x == e)));
+      more = q == kNone && p + 1u < d.n;
+      if (q != kNone) remove_at(d, p, q, lf, k, x);
+    }
+  }
+  // The smallest key, ties to the smaller id (d not empty): its leaf and position.
+  struct At {
+    uint32_t p, q, e;
+    KT key;
+  };
+  __device__ __forceinline__ At back(const D& d) const {
+    At r;
+    r.p = d.n - 1u;
+    uint32_t lf = D::get(d.leaf, r.p), i = (lf >> 7) * 64u + lane;
+    KT k = lkey[i];
+    uint32_t x = lent[i];
+    r.key = rl(k, (lf & 127u) - 1u);
+    r.q = first_set(ballot((lane < (lf & 127u)) & (k == r.key)));
+    r.e = rl(x, r.q);
+    if (r.q == 0u && r.p) {
+      // the tie may begin in an earlier leaf: inside the last one that begins
+      // with a larger key, or with the leaf after that
+      const uint32_t c = d.above(r.key);
+      r.p = c;
+      r.e = D::get(d.snot, c);
+      if (c) {
+        lf = D::get(d.leaf, c - 1u);
+        i = (lf >> 7) * 64u + lane;
+        k = lkey[i];
+        x = lent[i];
+        const uint32_t q = first_set(ballot((lane < (lf & 127u)) & (k == r.key)));
+        if (q != kNone) {
+          r.p = c - 1u;
+          r.q = q;
+          r.e = rl(x, q);
+        }
+      }
+    }
+    return r;
+  }
+  // The scan victim is the better of the two fronts (none: empty()).
+  // (Uniform conditions that outlive a branch are words: as truth values the
+  // compiler keeps lane masks of them and selects in vector registers.)
+  __device__ __forceinline__ uint32_t empty() const { return (hbm.n | sram.n) == 0u ? 1u : 0u; }
+  __device__ __forceinline__ uint32_t front_in_sram() const {
+    const KT hk = rl(hbm.skey[0], 0u), sk = rl(sram.skey[0], 0u);
+    const uint32_t he = rl(hbm.snot[0], 0u), se = rl(sram.snot[0], 0u);
+    const uint32_t ge = hk <= sk ? 1u : 0u;
+    uint32_t first = hk == sk ? (se > he ? 1u : 0u) : ge;
+    first = hbm.n == 0u ? 1u : first;
+    return sram.n == 0u ? 0u : first;
+  }
+  __device__ __forceinline__ uint32_t front(uint32_t in_sram) const {
+    return in_sram ? rl(sram.snot[0], 0u) : rl(hbm.snot[0], 0u);
+  }
+  // The smallest id with a key above th, as its entry's complement (kNone: none).
+  __device__ __forceinline__ uint32_t fired(const D& d, KT th) const {
+    uint32_t best = kNone;
+    const uint32_t n = d.above(th);
+    for (uint32_t p = 0; p < n; ++p) {
+      const uint32_t lf = D::get(d.leaf, p), i = (lf >> 7) * 64u + lane;
+      const uint32_t x = ~lent[i];
+      const uint32_t v = ((lane < (lf & 127u)) & (lkey[i] > th)) ? x : kNone;
+      const uint32_t m = uni32(wave_ext32<false>(v));
+      best = m < best ? m : best;
+    }
+    return best;
+  }
+};
+
 // The wavefront's 64-bit sums, 64 words each in LDS.
 enum : uint32_t { kSTok, kSComp, kSExtra, kSMiss, kSHitS, kSPrevS, kSHitH, kSPrevH, kSEvals, kSResEvals,
                   kSDigest, kSVictim, kSums };
@@ -477,17 +835,15 @@ struct Totals {
 };
 
 // Events [e_io, end) of one simulation.
-template <int SPL, uint32_t POL, uint32_t SMODE, bool DUAL>
+template <uint32_t POL, uint32_t SMODE, bool DUAL, class LS>
 __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_params& P,
                                             const KeyCtx& K, const TraceView& tr, size_t tb,
                                             const uint32_t* kvb_of, uint64_t* view, uint2* queue, uint64_t* sums,
-                                            LaneSim<SPL, POL, SMODE, DUAL>& T,
+                                            LS& T,
                                             Pool& pool, Totals& W, const LogSink& L, uint64_t& e_io,
                                             uint64_t end) {
   using PT = Pol<POL, SMODE>;
-  using LS = LaneSim<SPL, POL, SMODE, DUAL>;
   using KT = typename LS::KT;
-  using O = Order<SPL, KT>;
   constexpr uint64_t kGolden = 0x9e3779b97f4a7c15ull;
   const uint32_t lane = T.lane;
   const uint64_t below = (1ull << lane) - 1ull;
@@ -541,7 +897,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
   const bool ema = LS::kGapEma || tide;
   const uint64_t cap_s = uni64(P.cap_sram_B), cap_h = uni64(P.cap_hbm_B);
   const uint64_t slots = uni64(P.n_slots);
-  const uint32_t n_slots = slots < 64u * SPL ? (uint32_t)slots : 64u * SPL;  // residents fit the slots
+  const uint32_t n_slots = slots < LS::kSlots ? (uint32_t)slots : LS::kSlots;  // residents fit the slots
 
   uint64_t used_s = pool.used_s, used_h = pool.used_h, dma_free = pool.dma_free;
   uint32_t n_res = uni32(pool.n_res), n_table = uni32(pool.n_table);
@@ -741,6 +1097,20 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
       if (m_sync) c.put(kCSync, (uint64_t)(base + 64u - (uint32_t)__builtin_clzll(m_sync)));
       c.put(kCReq, (uint64_t)(c.u64(kCReq) + pop64(m_arr)));
     }
+    // a list finds an arriving session's entry by the key of its last gap onset
+    // and its size by the length before the event
+    KT key_in = 0;
+    uint64_t size_in = 0;
+    uint32_t st = 0;
+    if constexpr (LS::kList) {
+      st = T.where[sid];
+      const KT pk = (KT)__shfl((unsigned long long)key, prev < 0 ? (int)lane : prev);
+      key_in = LS::key_from(key_ctx(), false, meta_turn((uint32_t)tab.mg),
+                            __uint_as_float((uint32_t)(tab.mg >> 32)), tab.gq, tab.last,
+                            PT::nextkey ? c.ptr<uint64_t>(kCNext)[sid] : ~0ull);
+      key_in = prev < 0 ? key_in : pk;
+      size_in = (uint64_t)len_in * tab.kvb;
+    }
     const uint64_t size = (uint64_t)ln * tab.kvb;
     uint64_t budget = 0;
     if (tide) {
@@ -795,29 +1165,211 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
       queue[q_n] = make_uint2(k | (op << 6) | (y << 12), x);
       ++q_n;
     };
+    // (Without a divergent branch, so that it may stand inside the chain's loops:
+    // lanes past the end read, hash and store the last record again.)
     const auto flush = [&]() {
       wave_sync();
       for (uint32_t q0 = 0; q0 < q_n; q0 += 64u) {
-        const bool in = q0 + lane < q_n;
-        const uint2 r = queue[in ? q0 + lane : 0u];
+        const uint32_t m = q_n - q0 < 64u ? q_n - q0 : 64u;
+        const bool in = lane < m;
+        const uint2 r = queue[q0 + (in ? lane : m - 1u)];
         const uint32_t op = in ? (r.x >> 6) & 7u : 0u;
         const uint32_t ev = (uint32_t)base + (r.x & 63u);
-        const uint32_t y = op == kOpPlace || op == kOpSwap ? r.x >> 12 : kNone;
+        const auto second = [](uint32_t x) {
+          const uint32_t o = (x >> 6) & 7u;
+          return o == kOpPlace || o == kOpSwap ? x >> 12 : kNone;
+        };
         // placements and bypasses are hashed from the window, an event per lane
-        if (in && op != kOpVictim && op != kOpPlace && op != kOpBypass) add(kSDigest, rec_hash(ev, op, r.y, y));
+        const uint64_t hash = rec_hash(ev, op, r.y, second(r.x));
+        const uint64_t mask = 0ull - (uint64_t)(in & (op != kOpVictim) & (op != kOpPlace) & (op != kOpBypass));
+        add(kSDigest, hash & mask);
         n_evict += op == kOpEvict ? 1u : 0u;
         n_exp += op == kOpExpire ? 1u : 0u;
         n_pro += op == kOpPromote ? 1u : 0u;
         n_swap += op == kOpSwap ? 1u : 0u;
-        if (L.on) {
-          if (in && log_len + lane < c.u32(kCLogCap))
-            c.ptr<unison_record>(kCLog)[log_len + lane] = unison_record{ev, op, r.y, y};
-          log_len += q_n - q0 < 64u ? q_n - q0 : 64u;
+        if (log_on) {
+          const uint64_t at = uni64(log_len), cap = c.u32(kCLogCap);
+          if (at < cap) {
+            const uint64_t fit = cap - at < m ? cap - at : m;
+            const uint32_t i = lane < (uint32_t)fit ? lane : (uint32_t)fit - 1u;
+            const uint2 w = queue[q0 + i];
+            c.ptr<unison_record>(kCLog)[at + i] =
+                unison_record{(uint32_t)base + (w.x & 63u), (w.x >> 6) & 7u, w.y, second(w.x)};
+          }
+          log_len += m;
         }
       }
       wave_sync();
       q_n = 0;
     };
+    if constexpr (LS::kList) {
+    const auto set_state = [&](uint32_t v, uint32_t w) {
+      st = sid == v ? w : st;
+      T.where[v] = w;
+    };
+    const auto leave = [&](uint32_t x, uint32_t in_sram) {
+      const uint32_t slot = LS::slot_in(x);
+      const uint64_t sz = T.size(slot), m = 0ull - (uint64_t)in_sram;
+      used_s -= sz & m;
+      used_h -= sz & ~m;
+      --n_res;
+      n_table -= LS::bit(T.done, slot);  // a completed session leaves the table
+      T.free_slot(slot);
+      set_state(LS::sid_in(x), 0u);
+    };
+    // ---- the chain, one event after the other (every branch is uniform) ----
+    for (uint32_t k = 0; k < cnt; ++k) {
+      const uint32_t wd = rl(word, k);
+      const uint32_t s = wd & (kWArrive - 1u);
+      if (q_n >= kQueueFlush) flush();
+      if constexpr (PT::timeout) {
+        // TTL timers that fired since the previous event, smallest id first
+        const KT th = rl(thr, k);
+        bool more = T.hbm.above(th) + T.sram.above(th) != 0u;
+        while (more) {
+          const uint32_t ch = T.fired(T.hbm, th), cs = T.fired(T.sram, th);
+          const uint32_t in_sram = cs < ch ? 1u : 0u;
+          const uint32_t c = in_sram ? cs : ch;
+          emit(k, kOpExpire, c >> kListSlotBits, 0u);
+          leave(~c, in_sram);
+          if (in_sram) T.remove_walking(T.sram, ~c);
+          else T.remove_walking(T.hbm, ~c);
+          if (q_n >= kListQueue - 4u) flush();
+          more = T.hbm.above(th) + T.sram.above(th) != 0u;
+        }
+      }
+      const uint32_t at = rl(st, k);  // the session's residency
+      if (wd & kWArrive) {
+        n_table += (wd >> kWNewBit) & 1u;
+        w_evals += n_table;
+        w_res += n_res;
+        uint32_t code = 0;
+        if (at & kStIn) {
+          const uint64_t sz = rl(size_in, k);
+          const uint32_t slot = at >> kStSlot;
+          used_s -= at & kSram ? sz : 0ull;
+          used_h -= at & kSram ? 0ull : sz;
+          code = at & kSram ? at & 3u : 4u;
+          --n_res;
+          T.free_slot(slot);
+          if (at & kSram) T.remove(T.sram, rl(key_in, k), LS::entry_of(s, slot));
+          else T.remove(T.hbm, rl(key_in, k), LS::entry_of(s, slot));
+        }
+        uint32_t none = T.empty(), in_sram = T.front_in_sram();
+        uint32_t x = T.front(in_sram);
+        const uint32_t v0 = none ? kNone : LS::sid_in(x);
+        o_vic = wl(o_vic, k, v0);
+        if (log_victims) emit(k, kOpVictim, v0, 0u);
+        // Alg. 1 capacity branch: evict the argmax victim until the session fits
+        uint32_t place = 0;  // the tier, 0: bypassed
+        const uint64_t sz = rl(size, k);
+        const uint32_t want_h = code >> 2;
+        if (!(wd & kWBig)) {
+          for (;;) {
+            const uint32_t room = (n_res - n_slots) >> 31;  // n_res < n_slots
+            const uint32_t fit_s = room & le_u64(used_s + sz, cap_s);
+            const uint32_t fit_h = room & le_u64(used_h + sz, cap_h);
+            // SRAM first, for an HBM resident's request HBM first
+            place = fit_s + 2u * (fit_h & ((fit_s ^ 1u) | want_h));
+            place = place == 3u ? kTierHbm : place;
+            if (place | none) break;
+            emit(k, kOpEvict, LS::sid_in(x), 0u);
+            leave(x, in_sram);
+            if (in_sram) T.remove_at(T.sram, 0u, 0u);
+            else T.remove_at(T.hbm, 0u, 0u);
+            none = T.empty();
+            in_sram = T.front_in_sram();
+            x = T.front(in_sram);
+            if (q_n >= kListQueue - 4u) flush();
+          }
+        }
+        o_code = wl(o_code, k, code | (place << 4));
+        if (log_on) emit(k, place ? kOpPlace : kOpBypass, s, place);
+        if (place) {
+          used_s += place & 1u ? sz : 0ull;
+          used_h += place & 1u ? 0ull : sz;
+          ++n_res;
+          const uint32_t f = T.take_slot();
+          T.ssz[f] = sz;
+          set_state(s, kStIn | (f << kStSlot) | (place & 1u));
+        } else if (at & kStIn) {
+          set_state(s, 0u);
+        }
+      } else {
+        const bool onset = (wd & kWOnset) != 0u;
+        if (at & kStIn) {
+          const uint32_t slot = at >> kStSlot;
+          if (!onset) T.done |= T.mine(slot);
+          if (at & kSram) T.insert(T.sram, rl(key, k), LS::entry_of(s, slot));
+          else T.insert(T.hbm, rl(key, k), LS::entry_of(s, slot));
+        }
+        w_evals += n_table;
+        w_res += n_res;
+        const uint32_t v0 = T.empty() ? kNone : LS::sid_in(T.front(T.front_in_sram()));
+        o_vic = wl(o_vic, k, v0);
+        if (log_victims) emit(k, kOpVictim, v0, 0u);
+        n_table -= !onset && !(at & kStIn) ? 1u : 0u;
+        if ((m_free >> k) & 1ull) {
+          uint64_t left = rl(budget, k), moved = 0;
+          ++passes;
+          bool more = T.hbm.n != 0u;
+          while (more) {
+            more = false;
+            const auto b = T.back(T.hbm);
+            const uint32_t ps = LS::slot_in(b.e);
+            const uint64_t sp = T.size(ps);
+            // past the budget or the SRAM, neither a promotion nor a swap is legal
+            uint32_t may = le_u64(sp, left) & le_u64(sp, cap_s);
+            if constexpr (PT::has_inf) may &= b.key != (KT)PT::inf_key ? 1u : 0u;
+            if (may) {
+              uint64_t sd = 0;
+              more = le_u64(used_s + sp, cap_s) != 0u;
+              const bool swap = !more && T.sram.n != 0u;
+              const KT dk = rl(T.sram.skey[0], 0u);
+              const uint32_t de = rl(T.sram.snot[0], 0u);
+              if (swap) {
+                sd = T.size(LS::slot_in(de));
+                more = ((b.key < dk ? 1u : 0u) & le_u64(sd, left - sp) &
+                        le_u64(used_s - sd + sp, cap_s) & le_u64(used_h - sp + sd, cap_h)) != 0u;
+              }
+              if (more) {
+                used_s = used_s - sd + sp;
+                used_h = used_h - sp + sd;
+                T.remove_at(T.hbm, b.p, b.q);
+                if (swap) {
+                  const uint32_t ds = LS::slot_in(de);
+                  T.remove_at(T.sram, 0u, 0u);
+                  T.insert(T.hbm, dk, de);
+                  set_state(LS::sid_in(de), kStIn | (ds << kStSlot) | (LS::bit(T.pref, ds) ? LS::kPref : 0u));
+                }
+                T.insert(T.sram, b.key, b.e);
+                T.pref |= T.mine(ps);
+                set_state(LS::sid_in(b.e), kStIn | (ps << kStSlot) | kSram | LS::kPref);
+                left -= sp + sd;
+                moved += sp + sd;
+                emit(k, swap ? kOpSwap : kOpPromote, LS::sid_in(b.e), swap ? LS::sid_in(de) : 0u);
+                if (q_n >= kListQueue - 4u) flush();
+              }
+            }
+            more = more && T.hbm.n != 0u;
+          }
+          if (moved) {
+            // DMA busy for ceil(moved * 1000 / B) ns
+            const uint64_t b = c.u64(kCDma);
+            const uint64_t busy = moved < (1ull << 53) && b < (1ull << 53)
+                                      ? div_by(moved * 1000u + b - 1u, b, c.u64(kCDmaInv))
+                                      : dma_ns(moved, b);
+            dma_free = sat_add(rl(now, k), busy);
+            m_free = ballot(valid && onset_l && now >= dma_free);
+            dma_bytes += moved;
+          }
+        }
+      }
+    }
+    flush();
+    } else {
+    constexpr int SPL = LS::kRegs;
+    using O = typename LS::O;
     // A resident leaves the pool: its bytes, its slot.
     const auto leave = [&](uint32_t x) {
       const uint32_t slot = O::slot_in(x);
@@ -999,6 +1551,7 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
       }
       flush();
     }
+    }
 
     // ---- the window's accounting, an event per lane: eq. (hr-amat), eq. (prered) ----
     add(kSEvals, lane == 0 ? w_evals : 0u);
@@ -1062,10 +1615,10 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
   W.victim_digest = sum(kSVictim);
 }
 
-template <int SPL, uint32_t POL, uint32_t SMODE, bool DUAL>
+// lds, cap: a list pool's LDS and its slots.
+template <uint32_t POL, uint32_t SMODE, bool DUAL, class LS>
 __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const KeyCtx& K0,
-                                         uint2* queue, uint64_t* sums) {
-  using LS = LaneSim<SPL, POL, SMODE, DUAL>;
+                                         uint2* queue, uint64_t* sums, uint64_t* lds, uint32_t cap) {
   using KT = typename LS::KT;
   using PT = Pol<POL, SMODE>;
   // each instance computes its own addresses: shared ones would be hoisted
@@ -1092,8 +1645,13 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
   uint64_t e = 0;
   bool ok = true;
   LS T;
-  T.lane = lane;
-  T.init();
+  if constexpr (LS::kList) {
+    T.init(lane, lds, cap, list_rows(cap), a.t_slot + tb);
+    for (uint32_t i = lane; i < n_sess; i += 64) T.where[i] = 0u;
+  } else {
+    T.lane = lane;
+    T.init();
+  }
   if (cont) {
     e = uni64(a.state[sim].next_event);
     ok = uni64(a.counters[sim].error) == 0ull;
@@ -1110,7 +1668,7 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
   // residents never exceed min(N_sess, sessions): the launcher picks a kernel that holds them
   const uint64_t max_res = P.n_slots < n_sess ? P.n_slots : n_sess;
   const bool dual_ok = DUAL ? a.views && !P.hazard_online : !P.dual_sync;
-  bool fits = dual_ok && max_res <= 64u * SPL;
+  bool fits = dual_ok && max_res <= (LS::kList ? cap : LS::kSlots);
   uint64_t* const view = DUAL ? a.views + (size_t)sim * 8 * a.max_sessions : nullptr;
   ok = ok && fits;
 
@@ -1141,7 +1699,7 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
       if (in && meta_tier(m) != kTierNone)
         *reinterpret_cast<uint32_t*>(a.t_mg + tb + i) = with_tier(m, kTierNone) & ~kPrefetched;
       for (uint64_t bits = ballot(in && meta_tier(m) != kTierNone); bits; bits &= bits - 1u) {
-        if (n >= 64u * SPL) {
+        if (n >= (LS::kList ? cap : LS::kSlots)) {
           ok = fits = false;
           break;
         }
@@ -1149,6 +1707,17 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
         const uint32_t mm = rl(m, l), s = b + l;
         const uint32_t fl = (meta_tier(mm) == kTierSram ? kSram : 0u) |
                             ((mm & kPrefetched) ? LS::kPref : 0u);
+        if constexpr (LS::kList) {
+          const uint32_t f = T.take_slot(), e = LS::entry_of(s, f);
+          T.ssz[f] = rl(sz, l);
+          T.where[s] = kStIn | (f << kStSlot) | fl;
+          if (fl & LS::kPref) T.pref |= T.mine(f);
+          if (meta_phase(mm) == kDoneP) T.done |= T.mine(f);
+          if (meta_phase(mm) != kServing) {
+            if (fl & kSram) T.insert(T.sram, rl(key, l), e);
+            else T.insert(T.hbm, rl(key, l), e);
+          }
+        } else {
         LS::set(T.ssid, n, s);
         LS::set(T.sfl, n, fl);
         LS::set(T.ssz, n, rl(sz, l));
@@ -1157,6 +1726,7 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
         if (meta_phase(mm) != kServing)
           T.insert(rl(key, l), DUAL ? rl(copy_key, l) : (KT)0, (s << kSidShift) | (n << 2) |
                                    (meta_phase(mm) == kDoneP ? kDoneB : 0u) | (fl & kSram));
+        }
         ++n;
       }
     }
@@ -1200,7 +1770,7 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
       bad = bad_at + 1;
     }
     if (e < end)
-      lane_events<SPL, POL, SMODE, DUAL>(a, P, K, tr, tb, a.sess_kvb + sb, view, queue, sums, T, pool, W, L, e, end);
+      lane_events<POL, SMODE, DUAL>(a, P, K, tr, tb, a.sess_kvb + sb, view, queue, sums, T, pool, W, L, e, end);
     __syncthreads();
     if constexpr (DUAL) {
       // both copies as the latest refresh left them
@@ -1219,13 +1789,23 @@ __device__ __forceinline__ void lane_run(const SimArgs& a, uint32_t sim, const K
     }
     // the residents' tiers into the table
     __syncthreads();
+    if constexpr (LS::kList) {
+      for (uint32_t i = lane; i < n_sess; i += 64) {
+        const uint32_t st = T.where[i];
+        if (st & kStIn) {
+          uint32_t* w = reinterpret_cast<uint32_t*>(a.t_mg + tb + i);
+          *w = with_tier(*w, (st & kSram) ? kTierSram : kTierHbm) | ((st & LS::kPref) ? kPrefetched : 0u);
+        }
+      }
+    } else {
 #pragma unroll
-    for (int j = 0; j < SPL; ++j)
+    for (int j = 0; j < LS::kRegs; ++j)
       if (T.ssid[j] != kNone) {
         uint32_t* w = reinterpret_cast<uint32_t*>(a.t_mg + tb + T.ssid[j]);
         *w = with_tier(*w, (T.sfl[j] & kSram) ? kTierSram : kTierHbm) |
              ((T.sfl[j] & LS::kPref) ? kPrefetched : 0u);
       }
+    }
   }
   store_hazard(a, P, sim, K, lane, 64);
   if (lane == 0) {
@@ -1283,11 +1863,11 @@ __device__ __forceinline__ void lane_row(const SimArgs& a, uint32_t sim, const K
                                          uint2* queue, uint64_t* sums) {
   if constexpr (DUAL) {
     if (uni32(a.params[sim].dual_sync)) {
-      lane_run<SPL, POL, SMODE, true>(a, sim, K, queue, sums);
+      lane_run<POL, SMODE, true, LaneSim<SPL, POL, SMODE, true>>(a, sim, K, queue, sums, nullptr, 0u);
       return;
     }
   }
-  lane_run<SPL, POL, SMODE, false>(a, sim, K, queue, sums);
+  lane_run<POL, SMODE, false, LaneSim<SPL, POL, SMODE, false>>(a, sim, K, queue, sums, nullptr, 0u);
 }
 
 // DUAL: a batch with rows of the dual design (the others run as ever).
@@ -1322,6 +1902,44 @@ void sim_lane_kernel(SimArgs a) {
   }
 }
 
+// Residents in sorted lists (ListSim).  Rows with an online hazard table, whose
+// keys all change with every completed session, are left to the wide-table kernel.
+__global__ __launch_bounds__(64, 1) void sim_list_kernel(SimArgs a, uint32_t cap) {
+  __shared__ float s_hf[52];
+  __shared__ uint32_t s_hq[52];
+  __shared__ uint32_t s_hd[52];
+  __shared__ uint32_t s_hn[52];
+  __shared__ uint2 s_queue[kListQueue];
+  __shared__ uint64_t s_sums[kSums * 64u];
+  extern __shared__ uint64_t s_pool[];
+  const uint32_t sim = blockIdx.x;
+  const unison_sim_params& P = a.params[sim];
+  KeyCtx K{};
+  K.hf = s_hf;
+  K.hq = s_hq;
+  K.hd = s_hd;
+  K.hn = s_hn;
+  K.lambda = (1u << P.b_h) - 1u;
+  load_hazard(a, P, sim, K, threadIdx.x, 64);
+  __syncthreads();
+  const auto go = [&](auto pol, auto mode) {
+    constexpr uint32_t POL = decltype(pol)::value, SMODE = decltype(mode)::value;
+    lane_run<POL, SMODE, false, ListSim<POL, SMODE>>(a, sim, K, s_queue, s_sums, s_pool, cap);
+  };
+  using std::integral_constant;
+  constexpr integral_constant<uint32_t, 0> zero{};
+  switch (sim_policy(a, P)) {
+    case kSpear:
+      if (P.score_mode) go(integral_constant<uint32_t, kSpear>{}, integral_constant<uint32_t, 1>{});
+      else go(integral_constant<uint32_t, kSpear>{}, zero);
+      break;
+    case kLru: go(integral_constant<uint32_t, kLru>{}, zero); break;
+    case kTimeout: go(integral_constant<uint32_t, kTimeout>{}, zero); break;
+    case kBelady: go(integral_constant<uint32_t, kBelady>{}, zero); break;
+    default: go(integral_constant<uint32_t, kEta>{}, zero); break;
+  }
+}
+
 template <bool DUAL>
 hipError_t launch_width(const SimArgs& a, uint64_t max_res, hipStream_t stream) {
   const dim3 grid(a.n_sims), block(64);
@@ -1338,6 +1956,16 @@ hipError_t launch_width(const SimArgs& a, uint64_t max_res, hipStream_t stream) 
 // max_res: the most residents any simulation can hold, at most 512.
 hipError_t launch_lanes(const SimArgs& a, uint64_t max_res, hipStream_t stream) {
   return a.dual ? launch_width<true>(a, max_res, stream) : launch_width<false>(a, max_res, stream);
+}
+
+// max_res: the most residents any simulation can hold, at most kListResidents.
+// No row has an online table or the dual design.
+hipError_t launch_lists(const SimArgs& a, uint64_t max_res, hipStream_t stream) {
+  if (max_res > kListResidents) return hipErrorInvalidValue;
+  const uint32_t cap = (uint32_t)((max_res ? max_res : 1) + 63) / 64u * 64u;
+  const size_t lds = (size_t)cap * 8u + (size_t)list_rows(cap) * 64u * 12u;
+  hipLaunchKernelGGL(sim_list_kernel, dim3(a.n_sims), dim3(64), lds, stream, a, cap);
+  return hipGetLastError();
 }
 
 }  // namespace unison

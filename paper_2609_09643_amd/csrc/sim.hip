@@ -35,6 +35,7 @@
 namespace unison {
 
 hipError_t launch_lanes(const SimArgs& a, uint64_t max_res, hipStream_t stream);
+hipError_t launch_lists(const SimArgs& a, uint64_t max_res, hipStream_t stream);
 
 // Event records one event ahead: the next record's loads are in flight while
 // the current event is processed.
@@ -979,7 +980,8 @@ struct LaneQueue {
 
 };
 
-// One wavefront per simulation for tables too large for LDS.  The session
+// One wavefront per simulation for batches with an online hazard table that are
+// too large for the lane kernel and for LDS.  The session
 // table stays in the workspace; the residents (at most 64 * rows of them,
 // bounded by N_sess, eq. (cap)) sit in LDS slots: slot s holds (key, session
 // id, meta) and the KV bytes, and belongs to lane s % 64; the table records
@@ -2502,12 +2504,15 @@ constexpr Variant kVariants[] = {{16, 1}, {64, 1}, {64, 4}, {0, 0}, {4, 4},
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kBlock = 256;
 constexpr int kLdsVariant = 9;
-constexpr int kLdsWaveVariant = 12;  // the table in LDS, one wavefront per simulation
+constexpr int kLdsWaveVariant = kLdsWaveKernel;  // the table in LDS, one wavefront per simulation
 constexpr int kDualVariant = 11;  // streamed, 512 threads, with the dual design's copies
 constexpr int kLaneVariant = kLaneKernel;  // residents sorted across one wavefront's lanes (lane.hip)
 constexpr uint64_t kLaneMaxResidents = 512;  // 8 per lane
-constexpr int kWideVariant = 14;  // the table in the workspace, residents in LDS slots, one wavefront
-constexpr uint64_t kWideMaxResidents = 4096;  // 96 KiB of slots
+constexpr uint64_t kLaneAutoResidents = 256;  // up to here it is faster than the lists
+// The table in the workspace, one wavefront: residents in sorted lists in LDS
+// (lane.hip), or in unsorted LDS slots where a row's hazard table grows online.
+constexpr int kWideVariant = kWideKernel;
+constexpr uint64_t kWideMaxResidents = 4096;  // 146 KiB of lists, 96 KiB of slots
 constexpr uint32_t kLdsBytesPerSession = 4 * 8 + 2 * 4;  // mg, last, gq, next; len, kvb
 
 // LDS of the workgroup kernels' residency bits: one bit per session, in whole
@@ -2565,16 +2570,17 @@ uint32_t sim_variant_lanes(int v) {
 // kLaneSims).  Measured, each kernel against the next: the lane kernel takes a
 // third to a half of the register tables' time from 17 sessions on (4,096
 // simulations of 64 and 200 sessions 0.64 and 2.1 ms against 1.35 and 13.9;
-// 16,384 of 40 sessions 2.0 against 3.1) and, with up to 512 residents, 0.2
-// to 0.67 of the LDS table's (the paper-scale trace at 64 and 512 slots 32
-// and 112 ms against 161 and 167).  Above that the LDS table up to its
-// capacity (one wavefront per simulation), then the wide-table kernel, then
-// the 512-thread streamed table.
+// 16,384 of 40 sessions 2.0 against 3.1).  Its time grows with the registers the
+// residents fill, that of the lists (kWideVariant) hardly at all: the paper-scale
+// trace at 64, 256 and 512 slots takes 32, 66 and 114 ms on the lane kernel, 67
+// on the lists at any count (the LDS table 162 to 168).  Beyond 4,096 residents
+// the LDS table up to its capacity (one wavefront per simulation), then the
+// 512-thread streamed table.
 int sim_auto_variant(uint32_t max_sess, uint64_t max_slots) {
   if (max_sess <= 16) return 5;
-  if (max_slots <= kLaneMaxResidents) return kLaneVariant;
-  if (max_sess <= sim_variant_capacity(kLdsWaveVariant)) return kLdsWaveVariant;
+  if (max_slots <= kLaneAutoResidents) return kLaneVariant;
   if (max_slots <= kWideMaxResidents) return kWideVariant;
+  if (max_sess <= sim_variant_capacity(kLdsWaveVariant)) return kLdsWaveVariant;
   return 10;
 }
 
@@ -2622,6 +2628,7 @@ hipError_t launch_sim(const SimArgs& a, uint32_t max_sess_in_batch, uint64_t max
       return launch_lanes(a, max_slots, stream);
     case kWideVariant: {
       if (max_slots > kWideMaxResidents) return hipErrorInvalidValue;
+      if (!a.online) return launch_lists(a, max_slots, stream);
       const uint32_t cap = (uint32_t)((max_slots ? max_slots : 1) + 63) / 64u * 64u;
       hipLaunchKernelGGL(sim_wide_kernel, dim3(a.n_sims), dim3(64),
                          (size_t)cap * kWideSlotBytes + kWideStageBytes, stream, a, cap);

@@ -242,6 +242,7 @@ struct SimArgs {
                              // null for group g = simulation g
   uint32_t n_slots;        // lane groups the register-table grid covers
   uint32_t dual;           // some row uses the dual register-file design
+  uint32_t online;         // some row's hazard table grows online
 };
 
 // The kernel that sorts the residents across one wavefront's lanes, and up to
@@ -253,6 +254,7 @@ struct SimArgs {
 // round of wavefronts starts (8,192: 308 us), while the register tables, eight
 // simulations to a wavefront, still fit one (220 us).
 constexpr int kLaneKernel = 13;
+constexpr int kLdsWaveKernel = 12, kWideKernel = 14;
 constexpr uint32_t kLaneSims = 4096;
 
 // Most lane groups of a wavefront (the 4-lane register table's 16).
