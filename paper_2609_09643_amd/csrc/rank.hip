@@ -848,8 +848,8 @@ constexpr uint8_t kWideMark = 254;
 template <bool NARROW>
 __global__ __launch_bounds__(kSortBlock, NARROW ? 8 : 4)
 void kendall_sort_kernel(uint32_t n_per, uint32_t P, uint64_t n_x, const float* x,
-                         const uint64_t* y, const uint32_t* idx, uint64_t* counts,
-                         uint8_t* top1) {
+                         const uint64_t* y, const uint32_t* idx, uint32_t quads,
+                         uint64_t* counts, uint8_t* top1) {
   // one (NARROW, and 2 kMergeGap 4-byte words) or two buffers of P + P/8
   // 8-byte entries (and 2 kWideGap entries): 36 or 72 KiB at 4,096 entries
   extern __shared__ __attribute__((aligned(16))) uint64_t s_dyn[];
@@ -881,26 +881,60 @@ void kendall_sort_kernel(uint32_t n_per, uint32_t P, uint64_t n_x, const float* 
   const uint32_t i0 = tid * kSortE;
   uint32_t kx[kSortE];
   uint64_t ky[kSortE];
-  bool wide = false;
+  bool wide = false, bad = false;
+  // A snapshot that needs the wide form is mostly told by one y per thread, before
+  // the rest is gathered (10,000 snapshots of 4,096 in the wide form: 1,590 us before, 1,252 now).
+  const auto found_wide = [&](uint64_t v) {
+    if (!__syncthreads_or(v != ~0ull && v >= 0xFFFFFFFFull)) return false;
+    if (tid == 0) top1[snap] = kWideMark;
+    return true;
+  };
+  // Every load of a step is issued before the first is waited for: threads past
+  // the end read the last entry, an index outside x / y entry 0.
+  if (idx) {
+    uint32_t e[kSortE];
+    if (quads && i0 + kSortE <= n) {
+      const uint4* const q = reinterpret_cast<const uint4*>(idx + base + i0);
+      const uint4 u = q[0], v = q[1];
+      e[0] = u.x; e[1] = u.y; e[2] = u.z; e[3] = u.w;
+      e[4] = v.x; e[5] = v.y; e[6] = v.z; e[7] = v.w;
+    } else {
+#pragma unroll
+      for (uint32_t c = 0; c < kSortE; ++c) e[c] = idx[base + (i0 + c < n ? i0 + c : n - 1u)];
+    }
+#pragma unroll
+    for (uint32_t c = 0; c < kSortE; ++c) {
+      const bool out = e[c] >= n_x;
+      bad = bad || out;
+      e[c] = out ? 0u : e[c];
+    }
+    if (NARROW && found_wide(y[e[0]])) return;
+#pragma unroll
+    for (uint32_t c = 0; c < kSortE; ++c) {
+      kx[c] = __float_as_uint(x[e[c]]);
+      ky[c] = y[e[c]];
+    }
+  } else {
+    if (NARROW && found_wide(y[base + (i0 < n ? i0 : n - 1u)])) return;
+#pragma unroll
+    for (uint32_t c = 0; c < kSortE; ++c) {
+      const size_t e = base + (i0 + c < n ? i0 + c : n - 1u);
+      kx[c] = __float_as_uint(x[e]);
+      ky[c] = y[e];
+    }
+  }
+  if (bad) s_bad = 1;
 #pragma unroll
   for (uint32_t c = 0; c < kSortE; ++c) {
     const uint32_t i = i0 + c;
-    kx[c] = 0xFFFFFFFFu;
-    ky[c] = ~0ull;
-    if (i < n) {
-      size_t e = idx ? (size_t)idx[base + i] : base + i;
-      if (e >= n_x) {
-        s_bad = 1;
-        e = 0;
-      }
-      const float xv = x[e];
-      const uint64_t yv = y[e];
-      kx[c] = float_key(__float_as_uint(xv));
-      ky[c] = yv;
-      wide = wide || (yv != ~0ull && yv >= 0xFFFFFFFFull);
-      if (bxi == kNone || fbetter(xv, i, bx, bxi)) { bx = xv; bxi = i; }
-      if (byi == kNone || ubetter(yv, i, by, byi)) { by = yv; byi = i; }
-    }
+    const float xv = __uint_as_float(kx[c]);
+    const uint64_t yv = ky[c];
+    const bool in = i < n;
+    wide = wide || (in && yv != ~0ull && yv >= 0xFFFFFFFFull);
+    if (in && (bxi == kNone || fbetter(xv, i, bx, bxi))) { bx = xv; bxi = i; }
+    if (in && (byi == kNone || ubetter(yv, i, by, byi))) { by = yv; byi = i; }
+    kx[c] = in ? float_key(kx[c]) : 0xFFFFFFFFu;
+    ky[c] = in ? yv : ~0ull;
   }
   if (wide) s_wide = 1;
 #pragma unroll
@@ -1027,14 +1061,16 @@ hipError_t launch_kendall(uint32_t n_snap, uint32_t n_per, uint64_t n_x, const f
   } else {
     uint32_t P = 2;
     while (P < n_per) P <<= 1;
+    // a thread's 8 indexes start on 16 bytes
+    const uint32_t quads = n_per % 4 == 0 && aligned(idx, 16) ? 1u : 0u;
     // the packed form first; then the snapshots it left marked
     const size_t lds = (size_t)sort_buf(P) * sizeof(uint64_t);
     hipLaunchKernelGGL(kendall_sort_kernel<true>, dim3(n_snap), dim3(kSortBlock),
                        lds + 2 * kMergeGap * sizeof(uint32_t), s, n_per, P,
-                       n_x, x, y, idx, counts, top1);
+                       n_x, x, y, idx, quads, counts, top1);
     hipLaunchKernelGGL(kendall_sort_kernel<false>, dim3(n_snap), dim3(kSortBlock),
                        2 * lds + 2 * kWideGap * sizeof(uint64_t), s, n_per,
-                       P, n_x, x, y, idx, counts, top1);
+                       P, n_x, x, y, idx, quads, counts, top1);
   }
   return hipGetLastError();
 }
