@@ -294,16 +294,17 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params);
  * policy_override is a UNISON_POLICY_* value applied to all simulations, or
  * UNISON_POLICY_PARAMS.  A batch with a dual-design row runs on variant 13
  * while no simulation can hold more than 512 residents and no dual row has
- * hazard_online set, else on the copies' streamed kernel (variant 11).  While no simulation can
- * hold more than 256 residents (min(N_sess, sessions); 512 where a row's hazard
- * table grows online) a batch runs on one wavefront per simulation with
- * the residents sorted across its lanes (variant 13), except that tables of at
- * most 16 sessions take eight simulations to a wavefront above 4,096
- * simulations (variant 5).  Up to 4,096 residents it runs on one wavefront per
- * simulation with the residents in sorted lists in LDS (variant 14); with an
+ * hazard_online set, else on the copies' streamed kernel (variant 11).  While
+ * no simulation can hold more than 256 residents (min(N_sess, sessions); 512
+ * where a row's hazard table grows online) a batch runs on one wavefront per
+ * simulation with the residents sorted across its lanes (variant 13), except
+ * that tables of at most 16 sessions take eight simulations to a wavefront above
+ * 4,096 simulations (variant 5).  Up to 4,096 residents it runs on one wavefront
+ * per simulation with the residents in sorted lists in LDS (variant 14); with an
  * online table, while the tables fit, on one wavefront with the table in LDS
- * (variant 12), else in 24-byte LDS slots (variant 14).  Otherwise it runs
- * on workgroup kernels that keep one bit of LDS per session (the residency bits their scans visit): 128 KiB at
+ * (variant 12), else in 24-byte LDS slots (variant 14).  Otherwise it runs on
+ * workgroup kernels that keep one bit of LDS per session (the residency bits
+ * their scans visit): 128 KiB at
  * UNISON_MAX_SESSIONS; the LDS left holds up to 8 resident-cache slots of
  * 28 B per thread.  Asynchronous.
  * Errors: UNISON_E_NOT_READY (also: an ETA simulation whose trace has no ETA
