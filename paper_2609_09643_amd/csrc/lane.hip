@@ -34,6 +34,7 @@
 
 #include <type_traits>
 
+#include "list_entry.h"
 #include "sim_device.h"
 
 #pragma clang fp contract(off)
@@ -485,18 +486,9 @@ struct LaneSim : Spread<SPL> {
 // at 512 and 1,400 slots 112 ms (register orders) and 166 (table in LDS) before,
 // 67 at both here.
 constexpr int kDirRegs = 3;
-constexpr uint32_t kListSlotBits = 12;
-constexpr uint32_t kListResidents = 1u << kListSlotBits;
 constexpr uint32_t kListQueue = 256;  // queued records; a pass over the pool flushes in between
 constexpr uint32_t kStIn = 4u, kStSlot = 3u;  // a residency word: kSram, kPref, kStIn, slot << 3
-
-// Rows for the leaves of max_res residents: packed leaves fill a third of them.
-__host__ __device__ constexpr uint32_t list_rows(uint64_t max_res) {
-  const uint32_t full = (uint32_t)((max_res + 63) / 64);
-  return 3u * full + 8u < 152u ? 3u * full + 8u : 152u;
-}
 static_assert(list_rows(kListResidents) <= 64u * kDirRegs, "a directory holds every row");
-static_assert(list_rows(kListResidents) >= kListResidents / 64u + 4u, "packed leaves leave rows free");
 
 template <class KT>
 struct Dir : Order<kDirRegs, KT> {
@@ -593,10 +585,10 @@ struct ListSim {
     return (KT)key_of<POL, SMODE>(K, m, hazard_of<POL, SMODE>(K, m), g, gq, t, next);
   }
   __device__ __forceinline__ static uint32_t entry_of(uint32_t sid, uint32_t slot) {
-    return ~((sid << kListSlotBits) | slot);
+    return ~list_word(sid, slot);
   }
-  __device__ __forceinline__ static uint32_t sid_in(uint32_t e) { return ~e >> kListSlotBits; }
-  __device__ __forceinline__ static uint32_t slot_in(uint32_t e) { return ~e & (kListResidents - 1u); }
+  __device__ __forceinline__ static uint32_t sid_in(uint32_t e) { return list_sid(~e); }
+  __device__ __forceinline__ static uint32_t slot_in(uint32_t e) { return list_slot(~e); }
   __device__ __forceinline__ uint64_t mine(uint32_t slot) const {
     return lane == (slot & 63u) ? 1ull << (slot >> 6) : 0ull;
   }
@@ -803,10 +795,10 @@ struct ListSim {
   __device__ __forceinline__ uint32_t front(uint32_t in_sram) const {
     return in_sram ? rl(sram.snot[0], 0u) : rl(hbm.snot[0], 0u);
   }
-  // The smallest id with a key above th, as its entry's complement (kNone: none).
-  __device__ __forceinline__ uint32_t fired(const D& d, KT th) const {
+  // The smallest id with a key above th, as its entry's complement: in the first n
+  // leaves, d.above(th) of them (0: kNone, which may also be an entry).
+  __device__ __forceinline__ uint32_t fired(const D& d, KT th, uint32_t n) const {
     uint32_t best = kNone;
-    const uint32_t n = d.above(th);
     for (uint32_t p = 0; p < n; ++p) {
       const uint32_t lf = D::get(d.leaf, p), i = (lf >> 7) * 64u + lane;
       const uint32_t x = ~lent[i];
@@ -1225,17 +1217,18 @@ __device__ __forceinline__ void lane_events(const SimArgs& a, const unison_sim_p
       if constexpr (PT::timeout) {
         // TTL timers that fired since the previous event, smallest id first
         const KT th = rl(thr, k);
-        bool more = T.hbm.above(th) + T.sram.above(th) != 0u;
-        while (more) {
-          const uint32_t ch = T.fired(T.hbm, th), cs = T.fired(T.sram, th);
-          const uint32_t in_sram = cs < ch ? 1u : 0u;
+        uint32_t in_h = T.hbm.above(th), in_s = T.sram.above(th);
+        while (in_h + in_s != 0u) {
+          const uint32_t ch = T.fired(T.hbm, th, in_h), cs = T.fired(T.sram, th, in_s);
+          const uint32_t in_sram = fired_in_sram(in_h, in_s, ch, cs);
           const uint32_t c = in_sram ? cs : ch;
           emit(k, kOpExpire, c >> kListSlotBits, 0u);
           leave(~c, in_sram);
           if (in_sram) T.remove_walking(T.sram, ~c);
           else T.remove_walking(T.hbm, ~c);
           if (q_n >= kListQueue - 4u) flush();
-          more = T.hbm.above(th) + T.sram.above(th) != 0u;
+          in_h = T.hbm.above(th);
+          in_s = T.sram.above(th);
         }
       }
       const uint32_t at = rl(st, k);  // the session's residency

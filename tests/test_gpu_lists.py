@@ -8,6 +8,7 @@ import pytest
 from paper_2609_09643_amd import synth
 from parity import compare_counters, oracle_counters, oracle_log, same_log
 from test_gpu_lane import Sim, workload
+from tracekit import trace_from_events
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +70,46 @@ def test_chosen_kernel_on_both_sides_of_the_line(n_slots, online):
     s.run(max_events=500)
     s.run(flags=1)
     compare_counters(s.counters(), oracle_counters(w), label="auto %d online %d" % (n_slots, online))
+
+
+@pytest.mark.parametrize("tide", [0, 1])
+def test_the_largest_session_expires_from_the_last_slot(tide):
+    """Session 2^20 - 1 in slot 4,095 of a full pool of 4,096: its entry is the
+    word 0xFFFFFFFF.  Its timer fires alone, and beside others in either tier."""
+    top, n = (1 << 20) - 1, 4095
+
+    def workload_with(last):
+        ev = [(10 + i, i, synth.KIND_ARRIVE, 0, 20) for i in range(n)]
+        ev.append((10_000, last, synth.KIND_ARRIVE, 0, 5))      # the last free slot
+        ev.append((10_001, last, synth.KIND_GAP_START, 0, 0))
+        ev += [(10_002 + i, s, synth.KIND_GAP_START, 0, 0) for i, s in enumerate((7, 3, 4000))]
+        ev.append((10_100, 9, synth.KIND_GAP_START, 0, 0))
+        ev.append((10_101, 7, synth.KIND_ARRIVE, 1, 21))       # 7 is gone or resident, by the row
+        ev.append((30_000, last, synth.KIND_ARRIVE, 1, 6))
+        ev.append((30_001, last, synth.KIND_DONE, 1, 0))
+        ev.append((60_000, 3, synth.KIND_ARRIVE, 1, 20))
+        tr = trace_from_events(ev, last + 1)
+        rows = []
+        for cap_s in (0, 10, 1 << 40):   # all in HBM; only the last session in SRAM; all in SRAM
+            for ttl in (0, 98, 100, 1000):
+                p = synth.default_params(1)
+                p["policy"], p["tide"], p["ttl_ns"] = synth.POLICY_TIMEOUT, tide, ttl
+                p["cap_sram_B"], p["cap_hbm_B"], p["n_slots"] = cap_s, 1 << 40, 4096
+                rows.append(p[0])
+        return synth.Workload("top", [tr], [tr.turns], np.array(rows, dtype=synth.SIM_PARAMS_DTYPE))
+
+    s = Sim(workload_with(top), log_cap=1 << 13)
+    s.run(flags=2)
+    got = s.counters()
+    # The oracle runs the same trace with the last session as number 4,095 (its
+    # scans of 2^20 entries would take minutes): ids keep their order, so only
+    # that id differs in the records.
+    small = workload_with(n)
+    want = oracle_counters(small)
+    assert all(c["expire"] >= 5 and c["error"] == 0 for c in want)
+    got["digest"] = got["victim_digest"] = 0
+    compare_counters(got, [dict(c, digest=0, victim_digest=0) for c in want], label="top")
+    for i in range(small.n_sims):
+        log = oracle_log(small, i).copy()
+        log["a"][log["a"] == n] = top
+        assert same_log(s.log(i), log), "sim %d log" % i
