@@ -298,6 +298,8 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params);
  * no simulation can hold more than 256 residents (min(N_sess, sessions); 512
  * where a row's hazard table grows online) a batch runs on one wavefront per
  * simulation with the residents sorted across its lanes (variant 13), except
+ * that online tables of 257 to 384 residents and under three turns a session run
+ * on the table in LDS (variant 12), and
  * that tables of at most 16 sessions take eight simulations to a wavefront above
  * 4,096 simulations (variant 5).  Up to 4,096 residents it runs on one wavefront
  * per simulation with the residents in sorted lists in LDS (variant 14); with an

@@ -183,6 +183,8 @@ struct unison_ctx {
   bool dual_lanes = false;  // and none of those rebuilds its hazard table online
   uint32_t max_sess_batch = 0;
   uint64_t max_slots_batch = 0;  // largest N_sess of the parameter rows
+  uint64_t max_ev_batch = 0;     // events of the longest trace the rows replay
+  bool few_turns = false;        // and it has under three turns a session
   int force_variant = -1;
   int force_cache_slots = -1;  // test hook: resident-cache slots of the streamed tables
   // the register-table kernels' lane-group -> simulation map (slot_map)
@@ -455,7 +457,7 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
   UNISON_LIVE(ctx);
   if (!ctx->traces_loaded) return ctx->fail(UNISON_E_NOT_READY, "load traces before parameters");
   uint32_t max_sess = 0;
-  uint64_t max_slots = 0;
+  uint64_t max_slots = 0, max_ev = 0, ev_sess = 0;
   for (uint32_t i = 0; i < ctx->dims.n_sims; ++i) {
     const unison_sim_params& p = params[i];
     if (p.dual_sync > UNISON_DUAL_GAP || (p.dual_sync && !ctx->dims.views))
@@ -471,6 +473,11 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
     const uint64_t ns = ctx->h_sess_off[p.trace + 1] - ctx->h_sess_off[p.trace];
     max_sess = std::max<uint32_t>(max_sess, (uint32_t)ns);
     max_slots = std::max<uint64_t>(max_slots, p.n_slots);
+    const uint64_t ne = ctx->h_ev_off[p.trace + 1] - ctx->h_ev_off[p.trace];
+    if (ne >= max_ev) {
+      max_ev = ne;
+      ev_sess = ns;
+    }
   }
   ctx->h_params.assign(params, params + ctx->dims.n_sims);
   ctx->dual = false;
@@ -490,6 +497,8 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
   if (rc) return rc;
   ctx->max_sess_batch = max_sess;
   ctx->max_slots_batch = max_slots;
+  ctx->max_ev_batch = max_ev;
+  ctx->few_turns = max_ev < 6u * ev_sess;
   ctx->params_set = true;
   ctx->params_gen++;
   return UNISON_OK;
@@ -624,11 +633,18 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
   if (v < 0) {
     v = sim_auto_variant(ctx->max_sess_batch, max_res);
     // Sorted lists take no online table, whose every completion changes all
-    // keys: such a batch goes to the lane kernel while it fits (the paper-scale
-    // trace at 512 slots 112 ms against 167), then to the LDS table while that fits.
+    // keys: such a batch goes to the lane kernel while it fits, then to the LDS
+    // table while that fits.  The LDS table also takes up to 384 residents of
+    // sessions of one or two turns, whose completions come often: 300 residents,
+    // 1 / 2 / 4 / 24 turns a session 2.4 / 4.9 / 7.9 / 27 ms on the lane kernel,
+    // 1.8 / 4.6 / 9.6 / 48 on the LDS table; 512 residents 4.8 / 9.9 / 18 / 53
+    // and 4.7 / 10.1 / 22 / 105.
     if (v == kWideKernel && ctx->online) {
-      if (max_res <= sim_variant_max_slots(kLaneKernel)) v = kLaneKernel;
-      else if (ctx->max_sess_batch <= sim_variant_capacity(kLdsWaveKernel)) v = kLdsWaveKernel;
+      const bool lds = ctx->max_sess_batch <= sim_variant_capacity(kLdsWaveKernel);
+      if (max_res <= sim_variant_max_slots(kLaneKernel) && !(lds && max_res <= 384 && ctx->few_turns))
+        v = kLaneKernel;
+      else if (lds)
+        v = kLdsWaveKernel;
     }
     if (ctx->dual || (sim_variant_lanes(v) && a.n_sims <= kLaneSims)) v = kLaneKernel;
     if (sim_variant_capacity(v) < ctx->max_sess_batch)

@@ -20,11 +20,11 @@ def Sim(*a, **k):
     return Simulator(*a, **k)
 
 
-def workload(n_sessions=90, n_slots=64, seed=11, sids=None):
+def workload(n_sessions=90, n_slots=64, seed=11, sids=None, mean=5):
     """Every policy and score form, with and without TIDE and online tables,
     on one trace whose pool keeps evicting."""
     rng = np.random.Generator(np.random.PCG64(seed))
-    turns = synth.geometric_turns(rng, n_sessions, 5)
+    turns = synth.geometric_turns(rng, n_sessions, mean)
     kvb = np.array([64, 128, 160], dtype=np.uint32)[rng.permutation(n_sessions) % 3] * synth.KIB
     tr = synth.build_trace(rng, turns, synth.poisson_arrivals(rng, n_sessions, 20.0),
                            synth.gaps_mixture, kvb)
@@ -138,3 +138,28 @@ def test_small_tables_choose_by_batch_size():
     b.run()
     ca, cb = a.counters(), b.counters()
     assert np.array_equal(ca.view(np.uint64), cb[:4096].view(np.uint64))
+
+
+@pytest.mark.parametrize("mean", [1, 2])
+@pytest.mark.parametrize("n_slots", [2, 64, 65, 128, 200, 257, 512])
+def test_online_tables_that_change_at_every_turn(n_slots, mean):
+    """Sessions of one or two turns under online tables: a completion every few
+    events, each changing every resident's key and the order of a full pool."""
+    w = workload(n_sessions=n_slots + 20, n_slots=n_slots, seed=n_slots + mean, mean=mean)
+    rows = [r for r in w.params if r["hazard_online"]]
+    for r in list(rows):
+        for cap in (0, 3, n_slots // 2):
+            q = r.copy()
+            q["online_sessions"] = cap
+            rows.append(q)
+    w.params = np.array(rows, dtype=synth.SIM_PARAMS_DTYPE)
+    w.params["cap_sram_B"] = n_slots * 100 * synth.MIB
+    w.params["cap_hbm_B"] = n_slots * 1000 * synth.MIB
+    want = oracle_counters(w)
+    for variant in (LANE, None):   # 257 to 384 residents of few turns have a rule of their own
+        s = Sim(w, log_cap=1 << 13, variant=variant)
+        s.run(flags=2, max_events=w.traces[0].n_events // 3)
+        s.run(flags=3)
+        compare_counters(s.counters(), want, label="online %d mean %d" % (n_slots, mean))
+        for i in range(w.n_sims):
+            assert same_log(s.log(i), oracle_log(w, i)), "sim %d log" % i
