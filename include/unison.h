@@ -292,23 +292,26 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params);
  * under the parameter row and policy it ran with (state a policy never
  * reads, such as the gap EMA of LRU or timeout without TIDE, is not kept).
  * policy_override is a UNISON_POLICY_* value applied to all simulations, or
- * UNISON_POLICY_PARAMS.  A batch with a dual-design row runs on variant 13
- * while no simulation can hold more than 512 residents and no dual row has
- * hazard_online set, else on the copies' streamed kernel (variant 11).  While
- * no simulation can hold more than 256 residents (min(N_sess, sessions); 512
- * where a row's hazard table grows online) a batch runs on one wavefront per
- * simulation with the residents sorted across its lanes (variant 13), except
- * that online tables of 257 to 384 residents and under three turns a session run
- * on the table in LDS (variant 12), and
- * that tables of at most 16 sessions take eight simulations to a wavefront above
- * 4,096 simulations (variant 5).  Up to 4,096 residents it runs on one wavefront
- * per simulation with the residents in sorted lists in LDS (variant 14); with an
- * online table, while the tables fit, on one wavefront with the table in LDS
- * (variant 12), else in 24-byte LDS slots (variant 14).  Otherwise it runs on
- * workgroup kernels that keep one bit of LDS per session (the residency bits
- * their scans visit): 128 KiB at
- * UNISON_MAX_SESSIONS; the LDS left holds up to 8 resident-cache slots of
- * 28 B per thread.  Asynchronous.
+ * UNISON_POLICY_PARAMS.
+ * The kernel is chosen for the batch, by its largest trace, the most residents
+ * a simulation can hold (min(N_sess, sessions)) and the events of the launch.
+ * With a dual-design row: variant 13 up to 512 residents while no dual row has
+ * hazard_online set, else the copies' streamed kernel (variant 11).  Else up to
+ * 256 residents (512 where a row's hazard table grows online): one wavefront per
+ * simulation with the residents sorted across its lanes (variant 13), except that
+ * tables of at most 16 sessions take eight simulations to a wavefront above 4,096
+ * simulations (variant 5), and online tables of 257 to 384 residents and under
+ * three turns a session the table in LDS (variant 12).  Up to 4,096 residents: one
+ * wavefront per simulation with the residents in sorted lists in LDS (variant 14);
+ * with an online table, while the tables fit, with the table in LDS (variant 12),
+ * else with the residents in 24-byte LDS slots (variant 15).  Otherwise: workgroup
+ * kernels that keep one bit of LDS per session (the residency bits their scans
+ * visit): 128 KiB at UNISON_MAX_SESSIONS; the LDS left holds up to 8 resident-cache
+ * slots of 28 B per thread.  A launch of few events (max_events, up to tens for
+ * small pools, a few hundred for the largest), for which putting the residents in
+ * order does not pay, runs in register tables (variants 5, 7, 8), with the table
+ * in LDS (12), in LDS slots (15) or on the streamed kernels (10, 11).  The results
+ * never depend on the kernel.  Asynchronous.
  * Errors: UNISON_E_NOT_READY (also: an ETA simulation whose trace has no ETA
  * table), UNISON_E_INVALID (also: a register-table
  * variant forced on a batch with a dual-design row), UNISON_E_CAPACITY (the
@@ -378,17 +381,18 @@ int unison_kendall(void* hip_stream, uint32_t n_snap, uint32_t n_per, uint64_t n
  * range, null pointer), UNISON_E_NOT_READY (no run yet). */
 int unison_read_hazard(unison_ctx* ctx, uint32_t sim, uint32_t* d_out, uint32_t* n_out);
 
-/* Test hook: pins the simulation kernel variant (-1 = chosen by the largest
- * trace, the largest resident count and the batch; register tables of lanes x sessions
+/* Test hook: pins the simulation kernel variant (-1 = chosen, see unison_run;
+ * register tables of lanes x sessions
  * per lane 0: 16 x 1, 1: 64 x 1, 2: 64 x 4, 4: 4 x 4, 5: 8 x 2, 7: 16 x 4,
  * 8: 32 x 8 (6 is retired); one workgroup per simulation with the table 3:
  * streamed from the workspace by 256 threads, 10: by 512 threads, 9: held in
  * LDS (256 threads), 12: held in LDS by one wavefront, 11: streamed by 512
  * threads with the dual design's copies -- the only one that may be pinned for a
- * batch with a dual-design row; one wavefront per simulation with 13: the table in the
- * workspace and the residents sorted across the lanes, 1 to 8 per lane (at most
- * 512 residents), 14: the table in the workspace and the residents in LDS (sorted
- * lists, or slots for a batch with an online table; at most 4,096 residents)).  A variant too small for the traces or their
+ * batch with a dual-design row; one wavefront per simulation with the table in the
+ * workspace 13: the residents sorted across the lanes, 1 to 8 per lane (at most 512
+ * residents), 14: the residents in sorted lists in LDS (slots, as 15, for a batch with
+ * an online table; at most 4,096 residents), 15: the residents in unsorted LDS slots
+ * (at most 4,096)).  A variant too small for the traces or their
  * resident counts, or an unknown id, makes unison_run return
  * UNISON_E_CAPACITY. */
 int unison_debug_force_variant(unison_ctx* ctx, int variant);

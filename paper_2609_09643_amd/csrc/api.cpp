@@ -452,6 +452,110 @@ int unison_set_hazard(unison_ctx* ctx, uint32_t lut, const uint32_t* d, const ui
   return UNISON_OK;
 }
 
+// Register-table kernels run a group of `lanes` lanes per simulation, 64 /
+// lanes groups to a wavefront, and a wavefront executes every path any of
+// its simulations takes.  The map puts simulations that share policy, score
+// form and trace side by side and starts a new wavefront where they change
+// (the groups left over stay empty), so a wavefront never serialises two
+// policies or two traces' event kinds.  A batch already in that order keeps
+// the identity map (no map at all).
+static uint64_t slot_key(const unison_ctx* ctx, uint32_t policy_override, uint32_t lanes) {
+  return (ctx->params_gen << 16) ^ ((uint64_t)policy_override << 8) ^ lanes;
+}
+static int slot_map(unison_ctx* ctx, uint32_t policy_override, uint32_t lanes) {
+  const uint64_t key = slot_key(ctx, policy_override, lanes);
+  if (ctx->slots_for == key) return UNISON_OK;
+  const uint32_t n = ctx->dims.n_sims;
+  const uint32_t gpw = 64u / lanes;
+  if (gpw == 1) {  // one simulation per wavefront: nothing to group
+    ctx->slots_identity = true;
+    ctx->n_slots = n;
+    ctx->slots_for = key;
+    return UNISON_OK;
+  }
+  auto sort_key = [&](uint32_t i) {
+    const unison_sim_params& p = ctx->h_params[i];
+    const uint32_t pol = policy_override == UNISON_POLICY_PARAMS ? p.policy : policy_override;
+    const uint32_t mode = pol == UNISON_POLICY_SPEAR ? p.score_mode : 0u;
+    return ((uint64_t)pol << 40) | ((uint64_t)mode << 32) | p.trace;
+  };
+  std::vector<uint32_t> order(n);
+  for (uint32_t i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](uint32_t a, uint32_t b) { return sort_key(a) < sort_key(b); });
+  ctx->h_slots.clear();
+  for (uint32_t j = 0; j < n; ++j) {
+    if (j && sort_key(order[j]) != sort_key(order[j - 1]))
+      while (ctx->h_slots.size() % gpw) ctx->h_slots.push_back(0xFFFFFFFFu);
+    ctx->h_slots.push_back(order[j]);
+  }
+  bool identity = ctx->h_slots.size() == n;
+  for (uint32_t j = 0; identity && j < n; ++j) identity = ctx->h_slots[j] == j;
+  ctx->slots_identity = identity;
+  ctx->n_slots = identity ? n : (uint32_t)ctx->h_slots.size();
+  if (!identity) {
+    int rc = ctx->hip(hipMemcpyAsync(ctx->at<uint32_t>(ctx->L.slots), ctx->h_slots.data(),
+                                     sizeof(uint32_t) * ctx->h_slots.size(), hipMemcpyHostToDevice,
+                                     ctx->stream),
+                      "copy lane-group map");
+    if (rc) return rc;
+    rc = ctx->hip(hipStreamSynchronize(ctx->stream), "synchronise after lane-group map");
+    if (rc) return rc;
+  }
+  ctx->slots_for = key;
+  return UNISON_OK;
+}
+
+// The register tables that hold n sessions, or -1.
+static int regs_for(uint32_t n) { return n <= 16 ? 5 : n <= 64 ? 7 : n <= 256 ? 8 : -1; }
+
+// The kernel of a launch of at most n_ev events a simulation, v being the one
+// for long launches.  The lane and list kernels prepare a window, sum it up and,
+// resuming, put every resident back in order (about 0.2 us each in lanes, 0.7 in
+// lists) and walk the table 64 sessions at a time, which a few events do not pay
+// for; the older kernels load the table side by side or work on it in place.  The
+// line for each lies where the launches take as long, n sessions, r residents
+// at most, S simulations; us at 1 / 4 / 16 / 64 events, lane or list against the other:
+//   n 16,  S 2     10 / 12 / 18 / 37      8 / 14 / 34 / 107    register tables
+//   n 16,  S 4,096 18 / 20 / 29 / 58      11 / 15 / 33 / 108
+//   n 64,  S 4,096 21 / 24 / 36 / 81      18 / 26 / 59 / 192
+//   n 200, S 6     27 / 31 / 41 / 98      19 / 29 / 69 / 230
+//   n 300, r 200   27 / 31 / 42 / 98      14 / 29 / 79 / 296   table in LDS
+//   n 300, r 300   38 / 45 / 55 / 115     12 / 26 / 87 / 326
+//   n 3,500, r n   509 / 515 / 531 / 578  41 / 76 / 223 / 818
+//   n 10,000, r 256       208 / 225 / 276 at 1 / 16 / 64     16 / 89 / 330   streamed
+//   n 65,536, r 64        775 / 783 / 804                    29 / 92 / 296
+//   n 65,536, r 4,096     4,394 / 4,412 / 4,465              58 / 157 / 474
+//   dual, r 200, S 8      35 / 40 / 53 / 121     16 / 39 / 118 / 444
+//   dual, r 512, S 8      145 / 139 / 172 / 279  18 / 45 / 149 / 583
+// With few residents yet the crossing comes later; the lines are no higher than
+// what holds for a full pool.  The streamed table takes 512 threads a simulation, so
+// its events slow down from 256 simulations on.  There the slots of the wide-table
+// kernel resume sooner: 65,536 sessions, 64 residents 243 / 294 / 450 us at 1 / 16 / 64
+// events; and with a third of the lists' LDS more of them at a time: 10,000 sessions, 1,000
+// residents, 1,024 simulations 1.34 and 2.06 ms at 64 and 256 events, lists 1.84 and 2.27.
+static int short_launch(const unison_ctx* ctx, uint64_t n_ev, uint64_t r, uint32_t policy_override, int v) {
+  const uint64_t n = ctx->max_sess_batch, S = ctx->dims.n_sims;
+  if (v != kLaneKernel && v != kListKernel) return v;
+  if (ctx->dual) {
+    const uint64_t line = S <= 64 ? (r <= 64 ? 3 : r <= 256 ? 5 : 20) : r <= 64 ? 0 : S <= 1024 ? (r <= 256 ? 2 : 8) : r <= 256 ? 0 : 3;
+    return n_ev < line ? kDualKernel : v;
+  }
+  if (const int g = regs_for((uint32_t)n); g >= 0) {
+    const uint64_t line = n <= 16 ? 4 + S / 512 : n <= 64 ? 3 + S / 2048 : r <= 64 ? 0 : 10;
+    // (never a map of its own: a launch may be under capture)
+    const bool ready = ctx->slots_for == slot_key(ctx, policy_override, sim_variant_lanes(g));
+    return n_ev < line && ready ? g : v;
+  }
+  if (n <= sim_variant_capacity(kLdsWaveKernel)) {
+    const uint64_t line = r <= 64 ? 0 : r <= 256 ? 10 : v == kLaneKernel ? 64 : 24 + r / 96 + S / 256;
+    return n_ev < line ? kLdsWaveKernel : v;
+  }
+  if (n_ev < (16 + n / 400 + r / 64) / (1 + S / 256)) return kStreamKernel;
+  const uint64_t line = v == kLaneKernel ? n / 350 : S > 512 && r < 1280 ? r / 2 : 0;
+  return n_ev < line ? kWideKernel : v;
+}
+
 int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
   if (!ctx || !params) return UNISON_E_INVALID;
   UNISON_LIVE(ctx);
@@ -501,58 +605,9 @@ int unison_set_params(unison_ctx* ctx, const unison_sim_params* params) {
   ctx->few_turns = max_ev < 6u * ev_sess;
   ctx->params_set = true;
   ctx->params_gen++;
-  return UNISON_OK;
-}
-
-// Register-table kernels run a group of `lanes` lanes per simulation, 64 /
-// lanes groups to a wavefront, and a wavefront executes every path any of
-// its simulations takes.  The map puts simulations that share policy, score
-// form and trace side by side and starts a new wavefront where they change
-// (the groups left over stay empty), so a wavefront never serialises two
-// policies or two traces' event kinds.  A batch already in that order keeps
-// the identity map (no map at all).
-static int slot_map(unison_ctx* ctx, uint32_t policy_override, uint32_t lanes) {
-  const uint64_t key = (ctx->params_gen << 16) ^ ((uint64_t)policy_override << 8) ^ lanes;
-  if (ctx->slots_for == key) return UNISON_OK;
-  const uint32_t n = ctx->dims.n_sims;
-  const uint32_t gpw = 64u / lanes;
-  if (gpw == 1) {  // one simulation per wavefront: nothing to group
-    ctx->slots_identity = true;
-    ctx->n_slots = n;
-    ctx->slots_for = key;
-    return UNISON_OK;
-  }
-  auto sort_key = [&](uint32_t i) {
-    const unison_sim_params& p = ctx->h_params[i];
-    const uint32_t pol = policy_override == UNISON_POLICY_PARAMS ? p.policy : policy_override;
-    const uint32_t mode = pol == UNISON_POLICY_SPEAR ? p.score_mode : 0u;
-    return ((uint64_t)pol << 40) | ((uint64_t)mode << 32) | p.trace;
-  };
-  std::vector<uint32_t> order(n);
-  for (uint32_t i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](uint32_t a, uint32_t b) { return sort_key(a) < sort_key(b); });
-  ctx->h_slots.clear();
-  for (uint32_t j = 0; j < n; ++j) {
-    if (j && sort_key(order[j]) != sort_key(order[j - 1]))
-      while (ctx->h_slots.size() % gpw) ctx->h_slots.push_back(0xFFFFFFFFu);
-    ctx->h_slots.push_back(order[j]);
-  }
-  bool identity = ctx->h_slots.size() == n;
-  for (uint32_t j = 0; identity && j < n; ++j) identity = ctx->h_slots[j] == j;
-  ctx->slots_identity = identity;
-  ctx->n_slots = identity ? n : (uint32_t)ctx->h_slots.size();
-  if (!identity) {
-    int rc = ctx->hip(hipMemcpyAsync(ctx->at<uint32_t>(ctx->L.slots), ctx->h_slots.data(),
-                                     sizeof(uint32_t) * ctx->h_slots.size(), hipMemcpyHostToDevice,
-                                     ctx->stream),
-                      "copy lane-group map");
-    if (rc) return rc;
-    rc = ctx->hip(hipStreamSynchronize(ctx->stream), "synchronise after lane-group map");
-    if (rc) return rc;
-  }
-  ctx->slots_for = key;
-  return UNISON_OK;
+  // short launches of small tables run in register tables (short_launch)
+  const int g = regs_for(max_sess);
+  return g < 0 ? UNISON_OK : slot_map(ctx, UNISON_POLICY_PARAMS, sim_variant_lanes(g));
 }
 
 int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64_t max_events) {
@@ -618,8 +673,8 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
   if (ctx->dual) {
     if (v < 0 && !(ctx->dual_lanes && std::min<uint64_t>(ctx->max_slots_batch, ctx->max_sess_batch) <=
                                           sim_variant_max_slots(kLaneKernel)))
-      v = 11;
-    if (v >= 0 && v != 11)
+      v = kDualKernel;
+    if (v >= 0 && v != kDualKernel)
       return ctx->fail(UNISON_E_INVALID, "dual register files run on variant 11, not %d", v);
   }
   if (v >= 0 && (sim_variant_capacity(v) == 0 || sim_variant_capacity(v) < ctx->max_sess_batch))
@@ -639,14 +694,15 @@ int unison_run(unison_ctx* ctx, uint32_t policy_override, uint32_t flags, uint64
     // 1 / 2 / 4 / 24 turns a session 2.4 / 4.9 / 7.9 / 27 ms on the lane kernel,
     // 1.8 / 4.6 / 9.6 / 48 on the LDS table; 512 residents 4.8 / 9.9 / 18 / 53
     // and 4.7 / 10.1 / 22 / 105.
-    if (v == kWideKernel && ctx->online) {
+    if (v == kListKernel && ctx->online) {
       const bool lds = ctx->max_sess_batch <= sim_variant_capacity(kLdsWaveKernel);
       if (max_res <= sim_variant_max_slots(kLaneKernel) && !(lds && max_res <= 384 && ctx->few_turns))
         v = kLaneKernel;
-      else if (lds)
-        v = kLdsWaveKernel;
+      else
+        v = lds ? kLdsWaveKernel : kWideKernel;
     }
     if (ctx->dual || (sim_variant_lanes(v) && a.n_sims <= kLaneSims)) v = kLaneKernel;
+    v = short_launch(ctx, std::min(max_events, ctx->max_ev_batch), max_res, policy_override, v);
     if (sim_variant_capacity(v) < ctx->max_sess_batch)
       return ctx->fail(UNISON_E_CAPACITY, "%u sessions exceed every kernel variant (largest %u)",
                        ctx->max_sess_batch, sim_variant_capacity(v));

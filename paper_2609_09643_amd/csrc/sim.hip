@@ -2500,19 +2500,21 @@ struct Variant {
 // faulted the GPU on a randomised batch without a cause found.
 constexpr Variant kVariants[] = {{16, 1}, {64, 1}, {64, 4}, {0, 0}, {4, 4},
                                  {8, 2},  {-1, 0}, {16, 4}, {32, 8}, {0, 1}, {0, 0}, {0, 0},
-                                 {0, 1},  {0, 2},  {0, 3}};
+                                 {0, 1},  {0, 2},  {0, 3}, {0, 3}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kBlock = 256;
 constexpr int kLdsVariant = 9;
 constexpr int kLdsWaveVariant = kLdsWaveKernel;  // the table in LDS, one wavefront per simulation
-constexpr int kDualVariant = 11;  // streamed, 512 threads, with the dual design's copies
+constexpr int kDualVariant = kDualKernel;  // streamed, 512 threads, with the dual design's copies
 constexpr int kLaneVariant = kLaneKernel;  // residents sorted across one wavefront's lanes (lane.hip)
 constexpr uint64_t kLaneMaxResidents = 512;  // 8 per lane
 constexpr uint64_t kLaneAutoResidents = 256;  // up to here it is faster than the lists
-// The table in the workspace, one wavefront: residents in sorted lists in LDS
-// (lane.hip), or in unsorted LDS slots where a row's hazard table grows online.
+// The table in the workspace, one wavefront, up to 4,096 residents: in sorted lists
+// in LDS (lane.hip, 146 KiB), or in unsorted LDS slots (sim_wide_kernel, 96 KiB),
+// which also take rows whose hazard table grows online.
+constexpr int kListVariant = kListKernel;
 constexpr int kWideVariant = kWideKernel;
-constexpr uint64_t kWideMaxResidents = 4096;  // 146 KiB of lists, 96 KiB of slots
+constexpr uint64_t kWideMaxResidents = 4096;
 constexpr uint32_t kLdsBytesPerSession = 4 * 8 + 2 * 4;  // mg, last, gq, next; len, kvb
 
 // LDS of the workgroup kernels' residency bits: one bit per session, in whole
@@ -2536,12 +2538,13 @@ static uint32_t lds_limit() {
   return (uint32_t)cached > static_bytes ? (uint32_t)cached - static_bytes : 0u;
 }
 
-static uint32_t block_of(int v) { return v == 10 || v == kDualVariant ? 512u : (uint32_t)kBlock; }
+static uint32_t block_of(int v) { return v == kStreamKernel || v == kDualVariant ? 512u : (uint32_t)kBlock; }
 
 uint32_t sim_variant_capacity(int v) {
   if (v < 0 || v >= kNumVariants) return 0;
   const uint32_t lim = lds_limit();
-  if (v == kLaneVariant || v == kWideVariant) return UNISON_MAX_SESSIONS;  // the table stays in the workspace
+  if (v == kLaneVariant || v == kListVariant || v == kWideVariant)
+    return UNISON_MAX_SESSIONS;  // the table stays in the workspace
   if (v == kLdsVariant || v == kLdsWaveVariant) {
     // the table and its residency bits
     uint32_t n = lim / kLdsBytesPerSession;
@@ -2571,7 +2574,7 @@ uint32_t sim_variant_lanes(int v) {
 // third to a half of the register tables' time from 17 sessions on (4,096
 // simulations of 64 and 200 sessions 0.64 and 2.1 ms against 1.35 and 13.9;
 // 16,384 of 40 sessions 2.0 against 3.1).  Its time grows with the registers the
-// residents fill, that of the lists (kWideVariant) hardly at all: the paper-scale
+// residents fill, that of the lists (kListVariant) hardly at all: the paper-scale
 // trace at 64, 256 and 512 slots takes 32, 66 and 114 ms on the lane kernel, 67
 // on the lists at any count (the LDS table 162 to 168).  Beyond 4,096 residents
 // the LDS table up to its capacity (one wavefront per simulation), then the
@@ -2579,15 +2582,15 @@ uint32_t sim_variant_lanes(int v) {
 int sim_auto_variant(uint32_t max_sess, uint64_t max_slots) {
   if (max_sess <= 16) return 5;
   if (max_slots <= kLaneAutoResidents) return kLaneVariant;
-  if (max_slots <= kWideMaxResidents) return kWideVariant;
+  if (max_slots <= kWideMaxResidents) return kListVariant;
   if (max_sess <= sim_variant_capacity(kLdsWaveVariant)) return kLdsWaveVariant;
-  return 10;
+  return kStreamKernel;
 }
 
 // Largest N_sess a variant holds (UNISON_MAX_SESSIONS: no limit of its own).
 uint64_t sim_variant_max_slots(int v) {
   if (v == kLaneVariant) return kLaneMaxResidents;
-  if (v == kWideVariant) return kWideMaxResidents;
+  if (v == kListVariant || v == kWideVariant) return kWideMaxResidents;
   return UNISON_MAX_SESSIONS;
 }
 
@@ -2626,9 +2629,12 @@ hipError_t launch_sim(const SimArgs& a, uint32_t max_sess_in_batch, uint64_t max
   switch (v) {
     case kLaneVariant:
       return launch_lanes(a, max_slots, stream);
-    case kWideVariant: {
+    case kListVariant:  // (a batch with an online row: below)
       if (max_slots > kWideMaxResidents) return hipErrorInvalidValue;
       if (!a.online) return launch_lists(a, max_slots, stream);
+      [[fallthrough]];
+    case kWideVariant: {
+      if (max_slots > kWideMaxResidents) return hipErrorInvalidValue;
       const uint32_t cap = (uint32_t)((max_slots ? max_slots : 1) + 63) / 64u * 64u;
       hipLaunchKernelGGL(sim_wide_kernel, dim3(a.n_sims), dim3(64),
                          (size_t)cap * kWideSlotBytes + kWideStageBytes, stream, a, cap);
@@ -2653,7 +2659,7 @@ hipError_t launch_sim(const SimArgs& a, uint32_t max_sess_in_batch, uint64_t max
       hipLaunchKernelGGL((sim_block_kernel<64, true, false>), dim3(a.n_sims), dim3(64), lds, stream, a);
       break;
     }
-    case 10: {
+    case kStreamKernel: {
       SimArgs b = with_cache(a, max_sess_in_batch, 512, force_cache_slots);
       hipLaunchKernelGGL((sim_block_kernel<512, false, false>), dim3(a.n_sims), dim3(512),
                          b.rc_off + cache_bytes(b.rc_slots, 512), stream, b);

@@ -254,7 +254,7 @@ struct SimArgs {
 // round of wavefronts starts (8,192: 308 us), while the register tables, eight
 // simulations to a wavefront, still fit one (220 us).
 constexpr int kLaneKernel = 13;
-constexpr int kLdsWaveKernel = 12, kWideKernel = 14;
+constexpr int kStreamKernel = 10, kDualKernel = 11, kLdsWaveKernel = 12, kListKernel = 14, kWideKernel = 15;
 constexpr uint32_t kLaneSims = 4096;
 
 // Most lane groups of a wavefront (the 4-lane register table's 16).
