@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void score_fp32_kernel(uint32_t n, const uint8
       reinterpret_cast<float4*>(out)[i] = make_float4(score(t.x, v.x, d.x), score(t.y, v.y, d.y),
                                                       score(t.z, v.z, d.z), score(t.w, v.w, d.w));
     }
-    const uint32_t r = n4 * 4u + first;
+    const uint64_t r = (uint64_t)n4 * 4u + first;  // (passes 2^32 for the largest n)
     if (r < n) out[r] = score(turn[r], g[r], done[r]);
   } else {
     for (uint64_t i = first; i < n; i += stride) out[i] = score(turn[i], g[i], done[i]);
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) void score_fixed_kernel(uint32_t n, const uint
       reinterpret_cast<ulonglong2*>(out)[2 * (size_t)i] = x;
       reinterpret_cast<ulonglong2*>(out)[2 * (size_t)i + 1] = y;
     }
-    const uint32_t r = n4 * 4u + first;
+    const uint64_t r = (uint64_t)n4 * 4u + first;  // (passes 2^32 for the largest n)
     if (r < n) out[r] = score(turn[r], gq[r], done[r]);
   } else {
     for (uint64_t i = first; i < n; i += stride) out[i] = score(turn[i], gq[i], done[i]);

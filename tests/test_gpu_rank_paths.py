@@ -119,3 +119,36 @@ def test_kendall_pairs_at_register_edges(U, n_per, n_snap):
     nd = int((~tx & ~ty & ((xa > xb) != (ya > yb))).sum())
     want = [len(i) - nd - int((tx | ty).sum()), nd, int((tx & ~ty).sum()), int((ty & ~tx).sum()), int((tx & ty).sum())]
     assert U._host(c3, np.uint64)[0].tolist() == want
+
+
+@pytest.mark.parametrize("fixed", [0, 1])
+def test_scores_in_place_of_nearly_2_to_the_32_sessions(fixed):
+    """The output over the input, with a remainder of the four-session loads whose
+    index lies within a grid of 2^32: every session is scored once."""
+    import torch
+    from paper_2609_09643_amd import unison as U
+    n = (1 << 32) - 1001
+    head, tail = 1 << 20, 4096
+    turn = torch.full((n,), 3, dtype=torch.uint8, device="cuda")
+    done = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    d, nn = U.hazard_counts(torch.arange(1, 60, dtype=torch.int32, device="cuda"))
+    v = torch.empty(n, dtype=torch.int64 if fixed else torch.float32, device="cuda").fill_(5)
+    v[:head] = torch.arange(head, device="cuda")
+    v[-tail:] = torch.arange(tail, device="cuda")
+    ends = torch.cat([v[:head], v[-tail:]]).clone()
+    k = ends.numel()
+    L = U.lib()
+    if fixed:
+        want = U.score_fixed(turn[:k].clone(), ends, done[:k].clone(), d, nn, 12, 1000, 0)
+        rc = L.unison_score_fixed(U._stream(), n, U._ptr(turn), U._ptr(v), U._ptr(done), U._ptr(d), U._ptr(nn),
+                                  12, 1000, 0, U._ptr(v))
+    else:
+        want = U.score_fp32(turn[:k].clone(), ends, done[:k].clone(), d, nn, 1000.0)
+        rc = L.unison_score_fp32(U._stream(), n, U._ptr(turn), U._ptr(v), U._ptr(done), U._ptr(d), U._ptr(nn),
+                                 1000.0, U._ptr(v))
+    assert rc == 0
+    assert torch.equal(v[:head], want[:head])
+    assert torch.equal(v[-tail:], want[head:])
+    assert bool((v[head:-tail:4097] == v[head]).all())
+    del v, turn, done
+    torch.cuda.empty_cache()
