@@ -215,6 +215,10 @@ constexpr uint32_t kKendallMax = 4096;  // sort-based path: 18 B of LDS per entr
 // form); pairs grow with the square, and from 384 on the packed sort is ahead
 // (284 us).
 constexpr uint32_t kKendallPairsTo = 256;
+// Up to here a snapshot of more than 192 entries has a workgroup's four wavefronts:
+// 256 entries, 1 / 512 / 1,024 snapshots 10 / 14 / 21 us, on one wavefront each 28 /
+// 31 / 32 (sorted 25 / 27 / 33, wide form 28 / 31 / 56).
+constexpr uint32_t kKendallSplitTo = 1024;
 
 __device__ __forceinline__ bool fbetter(float a, uint32_t ia, float b, uint32_t ib) {
   return a > b || (a == b && ia < ib);
@@ -231,7 +235,9 @@ __device__ __forceinline__ bool ubetter(uint64_t a, uint32_t ia, uint64_t b, uin
 // snapshots of 64 entries: 60 us with a 256-thread workgroup per snapshot (three
 // of its wavefronts idle, every row walking all j > i), 20 now; of 255: 207 and
 // 137.
-template <int R>
+// SPLIT: a workgroup per snapshot, its wavefronts taking every fourth step each, while
+// the snapshots do not fill the chip (kKendallSplitTo).
+template <int R, bool SPLIT>
 __global__ __launch_bounds__(kKendallBlock) void kendall_pairs_kernel(
     uint32_t n_snap, uint32_t n, uint64_t n_x, const float* x, const uint64_t* y,
     const uint32_t* idx, uint64_t* counts, uint8_t* top1) {
@@ -239,7 +245,9 @@ __global__ __launch_bounds__(kKendallBlock) void kendall_pairs_kernel(
   __shared__ uint64_t s_y[kKendallBlock / 64][kSpan];
   __shared__ float s_x[kKendallBlock / 64][kSpan];
   const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  const uint32_t want = blockIdx.x * (kKendallBlock / 64) + w;
+  constexpr uint32_t kParts = SPLIT ? kKendallBlock / 64 : 1u;
+  const uint32_t part = SPLIT ? w : 0u;
+  const uint32_t want = SPLIT ? blockIdx.x : blockIdx.x * (kKendallBlock / 64) + w;
   const uint32_t snap = want < n_snap ? want : n_snap - 1u;  // the last block's spare wavefronts
   const size_t base = (size_t)snap * n;
   float xa[R];
@@ -310,8 +318,9 @@ __global__ __launch_bounds__(kKendallBlock) void kendall_pairs_kernel(
     }
   };
   const auto steps = [&](auto nan_x) {
-    for (uint32_t d = 1; 2u * d < n; ++d) step(nan_x, d, n);
-    if (n % 2u == 0u) step(nan_x, n / 2u, n / 2u);  // opposite entries: each pair from one side
+    for (uint32_t d = 1u + part; 2u * d < n; d += kParts) step(nan_x, d, n);
+    // opposite entries: each pair from one side
+    if (n % 2u == 0u && (n / 2u - 1u) % kParts == part) step(nan_x, n / 2u, n / 2u);
   };
   bool nan = false;
 #pragma unroll
@@ -325,7 +334,19 @@ __global__ __launch_bounds__(kKendallBlock) void kendall_pairs_kernel(
     nb += __shfl_xor(nb, m);
     nd += __shfl_xor(nd, m);
   }
-  if (lane == 0 && want < n_snap) {
+  if constexpr (SPLIT) {
+    __shared__ uint4 s_part[kParts];
+    if (lane == 0) s_part[w] = make_uint4(nd, ntx, nty, nb);
+    __syncthreads();
+    nd = ntx = nty = nb = 0;
+    for (uint32_t k = 0; k < kParts; ++k) {
+      nd += s_part[k].x;
+      ntx += s_part[k].y;
+      nty += s_part[k].z;
+      nb += s_part[k].w;
+    }
+  }
+  if (lane == 0 && part == 0 && want < n_snap) {
     const uint64_t pairs = (uint64_t)n * (n - 1) / 2;
     counts[(size_t)snap * 5 + 0] = pairs - nd - ntx - nty + nb;
     counts[(size_t)snap * 5 + 1] = nd;
@@ -1049,15 +1070,15 @@ hipError_t launch_kendall(uint32_t n_snap, uint32_t n_per, uint64_t n_x, const f
                           hipStream_t s) {
   if (n_snap == 0) return hipSuccess;
   if (n_per <= kKendallPairsTo) {
-    const dim3 grid((uint32_t)(((uint64_t)n_snap + kKendallBlock / 64 - 1) / (kKendallBlock / 64)));
-    const dim3 block(kKendallBlock);
-    const auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, grid, block, 0, s, n_snap, n_per, n_x, x, y, idx, counts, top1);
+    const auto launch = [&](auto kernel, uint32_t per_block) {
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)(((uint64_t)n_snap + per_block - 1) / per_block)),
+                         dim3(kKendallBlock), 0, s, n_snap, n_per, n_x, x, y, idx, counts, top1);
     };
-    if (n_per <= 64) launch(kendall_pairs_kernel<1>);
-    else if (n_per <= 128) launch(kendall_pairs_kernel<2>);
-    else if (n_per <= 192) launch(kendall_pairs_kernel<3>);
-    else launch(kendall_pairs_kernel<4>);
+    if (n_per <= 64) launch(kendall_pairs_kernel<1, false>, kKendallBlock / 64);
+    else if (n_per <= 128) launch(kendall_pairs_kernel<2, false>, kKendallBlock / 64);
+    else if (n_per <= 192) launch(kendall_pairs_kernel<3, false>, kKendallBlock / 64);
+    else if (n_snap > kKendallSplitTo) launch(kendall_pairs_kernel<4, false>, kKendallBlock / 64);
+    else launch(kendall_pairs_kernel<4, true>, 1);
   } else {
     uint32_t P = 2;
     while (P < n_per) P <<= 1;

@@ -121,6 +121,23 @@ def test_kendall_pairs_at_register_edges(U, n_per, n_snap):
     assert U._host(c3, np.uint64)[0].tolist() == want
 
 
+@pytest.mark.parametrize("n_per", [193, 200, 255, 256])
+def test_kendall_on_both_sides_of_the_split(U, n_per):
+    """Up to 1,024 snapshots of more than 192 entries share a workgroup's
+    wavefronts, above that each has one (here with two spare in the last block)."""
+    rng = np.random.default_rng(n_per)
+    n_snap = 1026
+    x = rng.integers(-3, n_per // 2, (n_snap, n_per)).astype(np.float32)
+    y = rng.integers(0, n_per // 3, (n_snap, n_per)).astype(np.uint64)
+    x[::7, ::3] = np.inf
+    x[::5, ::4] = -0.0
+    oc, ot = oracle.kendall(x, y)
+    for m in (n_snap, 1025, 1024, 3):
+        c, t = U.kendall(U._dev(x[:m].ravel()), U._dev(y[:m].ravel()), None, m, n_per)
+        assert np.array_equal(U._host(c, np.uint64), oc[:m])
+        assert np.array_equal(t.cpu().numpy(), ot[:m])
+
+
 @pytest.mark.parametrize("fixed", [0, 1])
 def test_scores_in_place_of_nearly_2_to_the_32_sessions(fixed):
     """The output over the input, with a remainder of the four-session loads whose
