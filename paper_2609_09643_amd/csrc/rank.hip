@@ -104,6 +104,11 @@ __global__ __launch_bounds__(256) void ema_replay_kernel(uint32_t n, uint32_t ma
 // 28.5 -> 17.9 us (fp32, 10 bytes each), 56 -> 27 us (integer, exact divider,
 // 18 bytes) and 45 -> 24 us (reciprocal table).
 constexpr uint32_t kScoreBlocks = 2048;
+// The integer scorer takes four sessions a thread only from here, where every
+// thread of the grid has work either way: in a smaller pool they are four 128-bit
+// divisions one after the other where gq passes 2^47 (65,536 sessions 27 us against
+// 10 with one each; 1,048,576 62 against 58, of ordinary gaps 5.8 against 5.5).
+constexpr uint32_t kFixedVecFrom = 4u * kScoreBlocks * 256u;
 
 template <bool VEC>
 __global__ __launch_bounds__(256) void score_fp32_kernel(uint32_t n, const uint8_t* turn,
@@ -1056,7 +1061,7 @@ hipError_t launch_score_fixed(uint32_t n, const uint8_t* turn, const uint64_t* g
                               uint32_t b_h, uint64_t p_z, uint32_t recip_bits, uint64_t* out,
                               hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (aligned(turn, 4) && aligned(done, 4) && aligned(gq, 16) && aligned(out, 16))
+  if (n >= kFixedVecFrom && aligned(turn, 4) && aligned(done, 4) && aligned(gq, 16) && aligned(out, 16))
     hipLaunchKernelGGL(score_fixed_kernel<true>, dim3(score_blocks(n, 1024)), dim3(256), 0, s, n, turn,
                        gq, done, d, nn, b_h, p_z, recip_bits, out);
   else

@@ -138,6 +138,24 @@ def test_kendall_on_both_sides_of_the_split(U, n_per):
         assert np.array_equal(t.cpu().numpy(), ot[:m])
 
 
+@pytest.mark.parametrize("more", [-1, 0, 1, 3])
+@pytest.mark.parametrize("b_h,recip", [(6, 0), (12, 0), (16, 0), (12, 16), (16, 32)])
+def test_fixed_scores_of_pools_with_four_sessions_a_load(U, more, b_h, recip):
+    """The integer scorer's vector loads start at 2^21 sessions."""
+    n = (1 << 21) + more
+    rng = np.random.Generator(np.random.PCG64(b_h + recip))
+    gq = rng.integers(0, 1 << 30, n, dtype=np.uint64)
+    edges = [v + k for v in (1 << 34, 1 << 38, 1 << 47, 1 << 50, 1 << 53, 1 << 63) for k in (-1, 0, 1)]
+    gq[np.arange(len(edges)) * 1067 + 500] = np.array(edges, np.uint64)
+    gq[-1] = np.uint64((1 << 64) - 1)
+    turn = rng.integers(0, 60, n).astype(np.uint8)
+    done = (rng.random(n) < 0.02).astype(np.uint8)
+    d, c = oracle.hazard_counts(synth.hazard_population(9, 128))
+    y = U.score_fixed(U._dev(turn), U._dev(gq), U._dev(done), U._dev(d, np.uint32), U._dev(c, np.uint32),
+                      b_h, 500_000_000, recip)
+    assert np.array_equal(U._host(y, np.uint64), oracle.score_fixed(turn, gq, done, d, c, b_h, 500_000_000, recip))
+
+
 @pytest.mark.parametrize("fixed", [0, 1])
 def test_scores_in_place_of_nearly_2_to_the_32_sessions(fixed):
     """The output over the input, with a remainder of the four-session loads whose
