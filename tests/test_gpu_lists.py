@@ -1,7 +1,7 @@
 """The sorted-list kernel (variant 14 for batches without online tables) where
-its shapes change: leaves that split, empty and are packed, windows cut
-anywhere, ties that run over several leaves, timers that fire in numbers.
-Every result against the oracle."""
+its shapes change: leaves that split and empty, windows cut anywhere, ties that
+run over several leaves, timers that fire in numbers.  Every result against the
+oracle."""
 import numpy as np
 import pytest
 
@@ -46,7 +46,8 @@ def test_resident_counts_around_leaf_sizes(n_slots):
 @pytest.mark.parametrize("sram,hbm", [(40, 4000), (2000, 2000), (4000, 40)])
 def test_large_pools_with_ties(sram, hbm):
     """Pools of hundreds of residents in either tier: equal keys over several
-    leaves (turn-0 sessions share a SPEAR key), rows that run out and are packed."""
+    leaves (turn-0 sessions share a SPEAR key).  (Rows that run out and are
+    packed: test_list_rows.py.)"""
     w = offline(workload(n_sessions=700, n_slots=600, seed=sram))
     w.params["cap_sram_B"] = sram * 40 * synth.MIB
     w.params["cap_hbm_B"] = hbm * 40 * synth.MIB
