@@ -177,40 +177,44 @@ def test_random_large_batch_on_the_retired_variant():
 
 
 @pytest.mark.parametrize("name", sorted(BATCHES))
-def test_random_batches_on_the_slot_kernel(name):
-    """The slot kernel holds residents in VGPR slots sized by N_sess (at
-    most 512): the batches with N_sess capped there, in one launch and split
+def test_random_batches_on_the_lane_kernel(name):
+    """The lane kernel holds residents in registers sized by N_sess (at most
+    512): the batches with N_sess capped there, in one launch and split
     by CONTINUE."""
     seed, lo, hi, _ = BATCHES[name]
     w = batch(seed, lo, hi)
     w.params["n_slots"] = np.minimum(w.params["n_slots"], 512)
     want = oracle_counters(w)
-    say("random %s on the slot kernel: %d sims" % (name, w.n_sims))
+    say("random %s on the lane kernel: %d sims" % (name, w.n_sims))
     s = Sim(w, variant=13)
     s.run()
-    compare_counters(s.counters(), want, label="random %s slot kernel" % name)
+    compare_counters(s.counters(), want, label="random %s lane kernel" % name)
     longest = max(t.n_events for t in w.traces)
     s.run(max_events=max(1, longest // 5))
     s.run(flags=1)
-    compare_counters(s.counters(), want, label="random %s slot kernel split" % name)
+    compare_counters(s.counters(), want, label="random %s lane kernel split" % name)
 
 
+@pytest.mark.parametrize("variant", [14, 15])
 @pytest.mark.parametrize("name", sorted(BATCHES))
-def test_random_batches_on_the_wide_kernel(name):
+def test_random_batches_on_the_list_and_wide_kernels(name, variant):
     """The wide-table kernel (table in the workspace, residents in LDS slots,
     the next entry loaded one event ahead): every batch, in one launch and
-    split by CONTINUE."""
+    split by CONTINUE.  The list kernel: the batches' rows without online
+    tables (with one, variant 14 is the wide-table kernel)."""
     seed, lo, hi, _ = BATCHES[name]
     w = batch(seed, lo, hi)
+    if variant == 14:
+        w.params = w.params[w.params["hazard_online"] == 0].copy()
     want = oracle_counters(w)
-    say("random %s on the wide kernel: %d sims" % (name, w.n_sims))
-    s = Sim(w, variant=14)
+    say("random %s on variant %d: %d sims" % (name, variant, w.n_sims))
+    s = Sim(w, variant=variant)
     s.run()
-    compare_counters(s.counters(), want, label="random %s wide kernel" % name)
+    compare_counters(s.counters(), want, label="random %s variant %d" % (name, variant))
     longest = max(t.n_events for t in w.traces)
     s.run(max_events=max(1, longest // 7))
     s.run(flags=1)
-    compare_counters(s.counters(), want, label="random %s wide kernel split" % name)
+    compare_counters(s.counters(), want, label="random %s variant %d split" % (name, variant))
 
 
 def test_random_dual_rows():

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 RETIRED = pytest.mark.skip(reason="variant 6 (64 x 24) is retired: one of its launches faulted "
                                   "the GPU on a randomised batch and no cause was found; the "
                                   "library refuses it (test_retired_variant_is_refused)")
-VARIANTS = (0, 1, 2, 3, 4, 5, pytest.param(6, marks=RETIRED), 7, 8, 9, 10, 11, 12, 13, 14)
+VARIANTS = (0, 1, 2, 3, 4, 5, pytest.param(6, marks=RETIRED), 7, 8, 9, 10, 11, 12, 13, 14, 15)
 
 
 def say(*a):
@@ -88,7 +88,7 @@ def test_c3_decision_logs(c3):
         assert same_log(s.log(k), oracle_log(c3, i)), "c3 sim %d log" % i
 
 
-@pytest.mark.parametrize("variant", [None, 3, 9, 12, 10, 13, 14])
+@pytest.mark.parametrize("variant", [None, 3, 9, 12, 10, 13, 14, 15])
 def test_continue_matches_single_run(c3, c3_want, variant):
     sims = list(range(5, c3.n_sims, 61))
     w = subset(c3, sims)
@@ -112,7 +112,7 @@ def test_determinism(c3):
     assert np.array_equal(a.view(np.uint64), b.view(np.uint64))
 
 
-@pytest.mark.parametrize("variant", [None, 12, 13, 14])
+@pytest.mark.parametrize("variant", [None, 12, 13, 14, 15])
 def test_c2_paper_scale(variant):
     w = synth.c2_paper_scale()
     say("c2: 4 sims x %d events, variant %s" % (w.traces[0].n_events, variant))
@@ -123,12 +123,12 @@ def test_c2_paper_scale(variant):
 
 
 @pytest.mark.parametrize("slots", [64, 65, 200, 512])
-def test_c2_on_the_slot_kernel_at_each_slot_width(slots):
-    """The slot kernel sizes its VGPR slots by the largest N_sess (1, 2, 4 or
-    8 per lane); every width, across a CONTINUE, against the oracle."""
+def test_c2_on_the_lane_kernel_at_each_width(slots):
+    """The lane kernel's residents take 1, 2, 4 or 8 registers by the largest
+    N_sess; every width, across a CONTINUE, against the oracle."""
     w = synth.c2_paper_scale()
     w.params["n_slots"] = slots
-    say("c2 slot kernel: N_sess %d" % slots)
+    say("c2 lane kernel: N_sess %d" % slots)
     s = Sim(w, variant=13)
     n = w.traces[0].n_events
     s.run(max_events=n // 3)
@@ -136,20 +136,21 @@ def test_c2_on_the_slot_kernel_at_each_slot_width(slots):
     compare_counters(s.counters(), oracle_counters(w), label="c2 slots %d" % slots)
 
 
-def test_wide_kernel_refuses_more_than_4096_residents():
-    """The wide-table kernel holds up to 4,096 residents in LDS slots; a batch
-    whose N_sess and sessions both pass that runs elsewhere or is refused."""
+@pytest.mark.parametrize("variant", [14, 15])
+def test_list_and_wide_kernel_refuse_more_than_4096_residents(variant):
+    """The lists and the wide-table kernel's LDS slots hold up to 4,096 residents;
+    a batch whose N_sess and sessions both pass that runs elsewhere or is refused."""
     from paper_2609_09643_amd.unison import E_CAPACITY, UnisonError
     w = synth.c4_large(n_traces=1)
     ww = subset(w, [0])
     ww.params["n_slots"] = 4097
-    s = Sim(ww, variant=14)
+    s = Sim(ww, variant=variant)
     with pytest.raises(UnisonError) as e:
         s.run(max_events=10)
     assert e.value.code == E_CAPACITY
 
 
-def test_slot_kernel_refuses_more_than_512_slots():
+def test_lane_kernel_refuses_more_than_512_residents():
     from paper_2609_09643_amd.unison import E_CAPACITY, UnisonError
     w = synth.c2_paper_scale()
     w.params["n_slots"] = 513
@@ -159,7 +160,7 @@ def test_slot_kernel_refuses_more_than_512_slots():
     assert e.value.code == E_CAPACITY
 
 
-@pytest.mark.parametrize("variant", [None, 10])
+@pytest.mark.parametrize("variant", [None, 10, 15])
 def test_c4_large_live_set_prefix(variant):
     w = synth.c4_large(n_traces=1)
     sims = [0, 3]
@@ -187,7 +188,7 @@ def test_c4_longer_prefix_in_the_timed_configuration():
     compare_counters(s.counters(), oracle_counters(ww, max_events=40_000), label="c4 40k")
 
 
-@pytest.mark.parametrize("variant", [None, 10])
+@pytest.mark.parametrize("variant", [None, 10, 15])
 def test_c4_golden_prefix_in_the_timed_configuration(variant):
     """The 65,536-session trace on the kernel the bench times, resumed by
     CONTINUE to 100,000, 200,000, 300,000 and 400,000 events, against the
@@ -211,6 +212,31 @@ def test_c4_golden_prefix_in_the_timed_configuration(variant):
         done = n
         compare_counters(s.counters(), gold["counters"][str(n)], label="c4 golden %d" % n)
     assert max(gold["table_entries"][str(done)]) > 50_000
+
+
+@pytest.mark.parametrize("variant", [None, 15])
+def test_c4_online_tables(variant):
+    """What the wide-table kernel is chosen for: a row whose hazard table grows
+    online among 65,536 sessions with about 1,400 residents, several slots to a
+    lane, in three launches."""
+    w = synth.c4_large(n_traces=1)
+    ww = subset(w, [0, 1, 2, 3, 4])
+    for i, (pol, mode) in enumerate(((POLICY_SPEAR, 0), (POLICY_SPEAR, 1), (POLICY_LRU, 0), (POLICY_BELADY, 0),
+                                     (POLICY_TIMEOUT, 0))):
+        synth.set_policy(ww.params[i:i + 1], pol)
+        ww.params["score_mode"][i] = mode
+    ww.params["hazard_online"][:2] = 1
+    ww.params["cap_sram_B"] = 40 * synth.GIB
+    ww.params["ttl_ns"] = 6 * synth.NS
+    n = 9000
+    say("c4 online: 5 sims, %d events, variant %s (the oracle needs ~9 s)" % (n, variant))
+    s = Sim(ww, variant=variant, log_cap=1 << 15)
+    for k, m in enumerate((5000, 777, n - 5777)):
+        s.run(flags=3 if k else 2, max_events=m)
+    want = oracle_counters(ww, max_events=n)
+    assert want[0]["resident_evals"] > 1000 * n and want[0]["promote"] + want[0]["swap"] > 0
+    compare_counters(s.counters(), want, label="c4 online")
+    assert same_log(s.log(1), oracle_log(ww, 1, log_cap=1 << 15, max_events=n)), "c4 online log"
 
 
 def test_c4_full_trace_properties():
