@@ -370,7 +370,7 @@ int unison_score_fixed(void* hip_stream, uint32_t n, const uint8_t* turn, const 
  * is not read: the snapshot's top1 is then 255 and its counts are void.
  * x holds scores, never NaN (a NaN has no rank; its snapshot's counts are
  * unspecified).  2 <= n_per <= 4096; above 256 entries the counts come
- * from sorting the snapshot in LDS (O(n log^2 n)), below it pair by pair. */
+ * from sorting the snapshot in LDS (O(n log^2 n)), up to it pair by pair. */
 int unison_kendall(void* hip_stream, uint32_t n_snap, uint32_t n_per, uint64_t n_x, const float* x,
                    const uint64_t* y, const uint32_t* idx, uint64_t* counts, uint8_t* top1);
 
@@ -405,7 +405,8 @@ int unison_debug_force_variant(unison_ctx* ctx, int variant);
 int unison_debug_cache_slots(unison_ctx* ctx, int slots);
 
 /* Test hook, host only (no GPU work): the barrier plan of the sorted Kendall
- * path for a snapshot padded to n_pad entries (a power of two, 256..4096).
+ * path for a snapshot padded to n_pad entries (a power of two, 256..4096; 256
+ * is a plan that no call takes, snapshots up to there are counted by pairs).
  * step 0: bitonic pass of stage a (= k) and stride b (= j); step 1: merge
  * level that merges runs of a entries (a >= 8: shorter runs are merged in
  * registers).  Bitonic passes run in groups of up to three in registers, one

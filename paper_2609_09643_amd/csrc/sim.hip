@@ -981,9 +981,9 @@ struct LaneQueue {
 };
 
 // One wavefront per simulation for batches with an online hazard table that are
-// too large for the lane kernel and for LDS.  The session
-// table stays in the workspace; the residents (at most 64 * rows of them,
-// bounded by N_sess, eq. (cap)) sit in LDS slots: slot s holds (key, session
+// too large for the lane kernel and for LDS, and for some short launches of tables
+// too large for LDS.  The session table stays in the workspace; the residents (at
+// most 64 * rows of them, bounded by N_sess, eq. (cap)) sit in LDS slots: slot s holds (key, session
 // id, meta) and the KV bytes, and belongs to lane s % 64; the table records
 // each resident's slot.  For each of the three reductions the engine asks
 // for -- argmax over every evictable resident (the scan victim), argmin over
@@ -2495,6 +2495,8 @@ struct Variant {
 // Register-table shapes (lanes per simulation x sessions per lane); ids 3
 // and 10 stream the table with 256 and 512 threads, id 9 keeps it in LDS,
 // id 11 streams it with 512 threads and also keeps the dual design's copies.
+// Ids 0, 1, 2, 3, 4 and 9 are never chosen: they run only when pinned, as checks
+// of the engine in other shapes (7 and 8 take short launches of small tables).
 // Id 6 (64 x 24, 1,536 sessions in registers) is retired: it spilled almost
 // 2 KB per lane, lost to the LDS table on its sizes, and one of its launches
 // faulted the GPU on a randomised batch without a cause found.

@@ -10,6 +10,8 @@ segment no entry one wavefront writes may be read or written by another.
 This test rebuilds every step's per-wavefront read and write sets from the
 kernel's index maps and checks that rule for every padded size, with the
 barrier plan the library itself reports (unison_debug_kendall_barrier).
+Snapshots of more than 256 entries are sorted, so the launches' sizes are 512
+to 4,096; the plan also covers 256.
 
 The bitonic passes run in groups of up to three in registers: a group loads
 its entries before its first pass and stores them after its last.  The sort
