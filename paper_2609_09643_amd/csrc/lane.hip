@@ -556,7 +556,7 @@ struct LaneSim : Spread<SPL> {
 // Bound by the same chain as the register orders, with an LDS round trip or two
 // per change (about 0.8 us per event).  65,536 live sessions (16 simulations of
 // 300,000 events, about 1,100 resident of 4,096 slots): 613 ms with unsorted LDS
-// slots and three wavefront reductions per event, 247 here; the paper-scale trace
+// slots and three wavefront reductions per event, 243 here; the paper-scale trace
 // at 512 and 1,400 slots 112 ms (register orders) and 166 (table in LDS) before,
 // 67 at both here.
 constexpr int kDirRegs = 3;

@@ -109,3 +109,27 @@ def test_short_launches_by_batch_size():
         for e in range(0, max(t.n_events for t in w.traces), step):
             s.run(flags=1 if e else 0, max_events=step)
         assert np.array_equal(s.counters().view(np.uint64), want), step
+
+
+@pytest.mark.parametrize("n_sessions,n_slots", [(16, 12), (60, 40), (200, 150), (300, 200), (420, 300)])
+def test_short_and_long_launches_under_capture(n_sessions, n_slots):
+    """A fresh short launch, a long one and the rest recorded into one graph:
+    no launch waits for the stream, and every replay gives the eager result."""
+    import torch
+    w = workload(n_sessions=n_sessions, n_slots=n_slots, seed=n_sessions + 2)
+    want = oracle_counters(w)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        s = Sim(w)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            s.run(max_events=2)
+            s.run(flags=1, max_events=100)
+            s.run(flags=1, max_events=1)
+            s.run(flags=1)
+        for k in range(3):
+            g.replay()
+            compare_counters(s.counters(), want, label="replay %d" % k)
+            s.run(max_events=5)      # the eager path's own use of the same tables
+            torch.cuda.synchronize()
